@@ -27,6 +27,10 @@ HIPCC_FLAGS = [
     "-target-feature",
     "-Xclang",
     "-packed-fp32-ops",
+    # MFMA results in ordinary registers: the factor kernels read them with VALU instructions, and copies out
+    # of accumulation registers cost a tenth of their VALU work
+    "-mllvm",
+    "-amdgpu-mfma-vgpr-form=1",
 ]
 
 

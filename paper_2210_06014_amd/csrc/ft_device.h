@@ -3,10 +3,9 @@
 //
 //
 // Lane layouts:
-//  * factor pass: a 16-lane DPP row owns one work item; lane l holds element
-//    j = l (+16 e) of every J-vector (row of A(m), shared intermediate g, a
-//    column of a chunk map) and element r = l (+16 q) of w; values of other
-//    lanes are read with DPP row_newbcast, row sums with DPP butterflies;
+//  * factor pass: a wavefront owns one work item and takes it in blocks of 16
+//    elements (ft_factor.hip); values of other lanes are read with DPP
+//    row_newbcast and through LDS;
 //  * core, loss, gradient passes: a segment of a row per wavefront, R/4 lanes
 //    per element, each lane gathering a 16-byte slice of every C(n) row;
 //  * C refresh: v_mfma_f32_16x16x4_f32 tiles of 16 rows.
@@ -72,7 +71,6 @@ __device__ __forceinline__ float group_sum(float v) {
 #define FT_BC(n) " row_newbcast:" #n " row_mask:0xf bank_mask:0xf\n\t"
 #define FT_DOT(n, op) "v_fmac_f32_dpp %0, %1, %" #op FT_BC(n)
 #define FT_AXPY(n, op) "v_fmac_f32_dpp %" #op ", %16, %17" FT_BC(n)
-#define FT_AXPY8(n, op) "v_fmac_f32_dpp %" #op ", %8, %9" FT_BC(n)
 
 // acc += sum_{i<16} src[lane i] * v[i]
 __device__ __forceinline__ void dot_bcast16(float& acc, float src, const float* v) {
@@ -99,22 +97,10 @@ __device__ __forceinline__ void axpy_bcast16(float* v, float src, float t) {
                  "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), "+v"(v[14]), "+v"(v[15])
                : "v"(src), "v"(t));
 }
-// v[i] += src[lane i] * t, i < 8
-__device__ __forceinline__ void axpy_bcast8(float* v, float src, float t) {
-  asm volatile("s_nop 4\n\t" FT_AXPY8(0, 0) FT_AXPY8(1, 1) FT_AXPY8(2, 2) FT_AXPY8(3, 3) FT_AXPY8(4, 4)
-                   FT_AXPY8(5, 5) FT_AXPY8(6, 6) FT_AXPY8(7, 7)
-               : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7])
-               : "v"(src), "v"(t));
-}
 template <int K>
 __device__ __forceinline__ void dot_bcast(float& acc, float src, const float* v) {
   static_assert(K == 8 || K == 16, "row broadcasts cover 8 or 16 lanes");
   if constexpr (K == 16) dot_bcast16(acc, src, v); else dot_bcast8(acc, src, v);
-}
-template <int K>
-__device__ __forceinline__ void axpy_bcast(float* v, float src, float t) {
-  static_assert(K == 8 || K == 16, "row broadcasts cover 8 or 16 lanes");
-  if constexpr (K == 16) axpy_bcast16(v, src, t); else axpy_bcast8(v, src, t);
 }
 
 // Parameter storage: float (FP32) or uint16_t holding BF16 bits.  BF16 is

@@ -10,13 +10,39 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 // Factor pass.  Each element x of a row, in order:
 //     w = prod_{n != m} C(n)[i_n, :],  g = B(m) w,  e = x - a.g,
 //     a <- a + (-lr lam) a + (lr e) g                       (Eq. (9), (10))
-// The decay is applied as an increment so that its rounding does not build
-// up over long rows.
 //
-// Per batch of 16 elements the lanes of a row first gather the C rows of all
-// 16 elements (phase 1, latency overlapped), then run the 16 dependent steps.
-// Steps past the end of an item use w = 0 and no decay, which leaves every
-// state unchanged, so the wavefront needs no divergent control flow.
+// The steps of a row are serial, but their expensive parts are not: a wavefront
+// takes a row in blocks of 16 elements and solves a block's 16 steps at once.
+// With rho = 1 - lr lam, gp = lr / rho, a_0 the row at the block's start, G the
+// block's 16 x J matrix of g and e~_t = rho^-t e_t (t = 0..15), the steps are
+//     (I + gp tril(G G^T, -1)) e~ = (rho^-t x_t) - G a_0,
+//     a_nb = rho^nb (a_0 + gp G^T e~),
+// the same result in another order of operations.  G and K = G G^T do not
+// depend on a_0: they are matrix products (v_mfma_f32_16x16x4_f32) formed a
+// block ahead; what stays serial is one product G a_0, a 16 x 16 forward
+// substitution and one product G^T e~.
+//
+// What bounds it: at J = R = 32 the matrix cores (24 MFMA of 32 cycles per
+// block to form G and K, 64 where a chunk map is carried too), at J <= 16 the
+// VALU work of the serial part.  One item per wavefront, because a block's
+// MFMA then serves one chain and the chain is 4 times shorter than with an
+// item per 16 lanes.  Against one step per element on 16 lanes (g by row
+// broadcasts), us per launch: Netflix-shaped 8M elements, J = R = 32, modes
+// 1 and 2: 1048 -> 652; order 4 (3M, J = R = 32) 934 -> 468; order 6 (1M, BF16)
+// 157 -> 55; order 8 (1M, J = 8, R = 16) 334 -> 101; Netflix-shaped 5M, J = R =
+// 16: 267 -> 259.
+//
+// Lane l = 16 g + i of the wavefront holds:
+//   Gu[k]  G[i][jbase(g) + k], k < J / 4   (as the MFMA that forms G leaves it,
+//          and as the operand of K = G G^T and of G N)
+//   Gr[k]  G[sbase(g) + k][j], j = the lane's state index (through LDS)
+//   L[s]   -gp K[i][s] for s < i, else 0   (through LDS, all rows of 16 alike)
+//   a      the row's element j = 16 (g % 2) + i (J = 32), i % J otherwise, FP64:
+//          the decay lr lam a is about a hundred ulps of a and nearly constant,
+//          so rounding the running row to FP32 would accumulate coherently.
+// Values of other lanes are read by DPP row broadcasts, so a state vector is
+// also kept rotated per row of 16: broadcast k then gives lane row g its
+// jbase(g) + k.  Slots past the end of an item hold x = 0 and G = 0.
 
 // Byte offset of row i of a C table, unsigned 32-bit: plan creation refuses
 // I_n * R * 4 >= 2^31, so the product never wraps.
@@ -25,452 +51,687 @@ __device__ __forceinline__ uint32_t row_bytes(int32_t i) {
   return (uint32_t)i * (uint32_t)(R * sizeof(T));
 }
 
-// value at byte offset `off` of a C table (uniform base + 32-bit offset: the
-// scalar-base addressing form)
-template <class T>
-__device__ __forceinline__ float at_byte(const T* base, uint32_t off) {
-  return to_f(*reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + off));
-}
+// K floats at byte offset `off` of a table (K * sizeof(T) bytes, aligned to
+// that size: C rows are whole multiples of it), as loaded
+template <int BYTES>
+struct RawOf;
+template <>
+struct RawOf<4> {
+  typedef uint32_t type;
+};
+template <>
+struct RawOf<8> {
+  typedef uint2 type;
+};
+template <>
+struct RawOf<16> {
+  typedef uint4 type;
+};
+template <>
+struct RawOf<32> {
+  struct type {
+    uint4 a, b;
+  };
+};
 
-// ixb[k]: byte offset of element (lane t)'s row in the k-th other C table
-template <int N, int R, class T>
-__device__ __forceinline__ void gather_w(const CPtrs<N, T>& cp, const int (&ixb)[N > 1 ? N - 1 : 1], int l, int t0,
-                                         int len, float (&w)[16][R >= 16 ? R / 16 : 1]) {
-  constexpr int RE = R >= 16 ? R / 16 : 1;
-  static_for<0, 16>([&](auto S) {
-    constexpr int s = decltype(S)::value;
-    uint32_t ib[N - 1];
-#pragma unroll
-    for (int k = 0; k < N - 1; ++k) ib[k] = (uint32_t)bcast16i<s>(ixb[k]);
-    const bool sv = (t0 + s) < len;
-#pragma unroll
-    for (int q = 0; q < RE; ++q) {
-      const uint32_t rb = (uint32_t)((R >= 16 ? l + 16 * q : (l % R)) * sizeof(T));
-      float prod = at_byte(cp.p[0], ib[0] + rb);
-#pragma unroll
-      for (int k = 1; k < N - 1; ++k) prod *= at_byte(cp.p[k], ib[k] + rb);
-      w[s][q] = sv ? prod : 0.f;
+template <class T, int K>
+struct Slice {
+  typename RawOf<K * (int)sizeof(T)>::type raw;
+  __device__ __forceinline__ void load(const T* base, uint32_t off) {
+    const char* p = reinterpret_cast<const char*>(base) + off;
+    if constexpr (K * sizeof(T) == 32) {
+      raw.a = *reinterpret_cast<const uint4*>(p);
+      raw.b = *reinterpret_cast<const uint4*>(p + 16);
+    } else {
+      raw = *reinterpret_cast<const typename RawOf<K * (int)sizeof(T)>::type*>(p);
     }
-  });
+  }
+  __device__ __forceinline__ void widen(float (&o)[K]) const {
+    uint32_t w[(K * sizeof(T)) / 4];
+    __builtin_memcpy(w, &raw, sizeof(w));
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) o[k] = __uint_as_float(w[k]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < K / 2; ++k) {
+        o[2 * k] = __uint_as_float(w[k] << 16);
+        o[2 * k + 1] = __uint_as_float(w[k] & 0xFFFF0000u);
+      }
+    }
+  }
+};
+
+// Powers of rho that the blocks need, formed on the host in FP64.
+struct RhoPow {
+  double p[17];   // rho^nb
+  float inv[16];  // rho^-t
+};
+
+template <int J>
+struct Geo {
+  static constexpr int JT = (J + 15) / 16;      // 16-wide tiles of j
+  static constexpr int VJ = J >= 16 ? 4 : J / 4;  // j per lane and tile
+  static constexpr int NG = J / 4;              // values of Gu
+  static constexpr int NS = J >= 32 ? 8 : 4;    // values of Gr
+  static constexpr int GS = J + 4;              // LDS row stride of G in floats
+  static constexpr int LS = 20;                 // LDS row stride of L in floats
+  __device__ static int jbase(int g) { return J >= 32 ? 16 * (g & 1) + 8 * (g >> 1) : (J / 4) * g; }
+  __device__ static int sbase(int g) { return J >= 32 ? 8 * (g >> 1) : 4 * g; }
+  __device__ static int jlane(int i, int g) { return J >= 32 ? 16 * (g & 1) + i : i % J; }
+  // j of row (or column) r of tile jt of an MFMA result, -1 where J = 8 leaves it empty
+  __device__ static int jmap(int jt, int r) {
+    return (r & 3) < VJ ? jbase(r >> 2) + VJ * jt + (r & 3) : -1;
+  }
+};
+
+template <int J>
+struct __align__(16) WaveLds {
+  float G[16 * Geo<J>::GS];
+  float L[16 * Geo<J>::LS];
+};
+
+// `v` with the lanes of row g of 16 rotated so that lane i holds the value of
+// lane (i + STEP g) % 16; J = 32 rotates rows 2 and 3 by 8
+template <int C1, int C2, int C3>
+__device__ __forceinline__ float rotate_rows(float v) {
+  int r = __builtin_bit_cast(int, v);
+  const int s = r;
+  if constexpr (C1 != 0) r = __builtin_amdgcn_update_dpp(r, s, 0x120 + C1, 0x2, 0xf, false);
+  if constexpr (C2 != 0) r = __builtin_amdgcn_update_dpp(r, s, 0x120 + C2, 0x4, 0xf, false);
+  if constexpr (C3 != 0) r = __builtin_amdgcn_update_dpp(r, s, 0x120 + C3, 0x8, 0xf, false);
+  return __builtin_bit_cast(float, r);
+}
+template <int J>
+__device__ __forceinline__ float rotate_state(float v) {
+  if constexpr (J >= 32) return rotate_rows<0, 8, 8>(v);
+  else if constexpr (J >= 16) return rotate_rows<12, 8, 4>(v);
+  else return rotate_rows<14, 12, 10>(v);
+}
+template <int J>
+__device__ __forceinline__ float rotate_slots(float v) {
+  if constexpr (J >= 32) return rotate_rows<0, 8, 8>(v);
+  else return rotate_rows<12, 8, 4>(v);
 }
 
-// g = B(m) w for this lane's elements j = l + 16 e; w_r comes from lane r % 16.
-template <int J, int R>
-__device__ __forceinline__ void shared_g(const float (&Bw)[J >= 16 ? J / 16 : 1][R], const float (&ws)[R >= 16 ? R / 16 : 1],
-                                         float (&g)[J >= 16 ? J / 16 : 1]) {
-  constexpr int E = J >= 16 ? J / 16 : 1;
-  constexpr int RE = R >= 16 ? R / 16 : 1;
-  constexpr int RK = R >= 16 ? 16 : R;
+// sums over lanes l, l ^ 32 and over l, l ^ 16; every lane ends with the same bits
+__device__ __forceinline__ float sum_halves(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float sum_rows(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// acc + sum_{k<K} src[lane k of the row] * v[k].  The trailing s_nop covers a
+// consumer that reads the result through DPP, a permute or an MFMA: the
+// compiler does not see the VALU write inside the block.
+#define FT_BSUM_END "s_nop 1"
+template <int K>
+__device__ __forceinline__ float bsum(float src, const float* v) {
+  float acc = 0.f;
+  if constexpr (K == 8) {
+    asm("s_nop 4\n\t" FT_DOT(0, 2) FT_DOT(1, 3) FT_DOT(2, 4) FT_DOT(3, 5) FT_DOT(4, 6) FT_DOT(5, 7) FT_DOT(6, 8)
+            FT_DOT(7, 9) FT_BSUM_END
+        : "+v"(acc)
+        : "v"(src), "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]));
+  } else if constexpr (K == 4) {
+    asm("s_nop 4\n\t" FT_DOT(0, 2) FT_DOT(1, 3) FT_DOT(2, 4) FT_DOT(3, 5) FT_BSUM_END
+        : "+v"(acc)
+        : "v"(src), "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]));
+  } else {
+    static_assert(K == 2, "2, 4 or 8 broadcasts");
+    asm("s_nop 4\n\t" FT_DOT(0, 2) FT_DOT(1, 3) FT_BSUM_END : "+v"(acc) : "v"(src), "v"(v[0]), "v"(v[1]));
+  }
+  return acc;
+}
+
+// Forward substitution: z_i += L[s] z_s for s = 0..14 in turn (L[s] = 0 in
+// lanes i <= s).  Each step reads the step before through DPP: two wait states.
+#define FT_SUB(n, op) "v_fmac_f32_dpp %0, %0, %" #op FT_BC(n) "s_nop 1\n\t"
+__device__ __forceinline__ float forward_substitute(float z, const float (&L)[16]) {
+  asm("s_nop 4\n\t" FT_SUB(0, 1) FT_SUB(1, 2) FT_SUB(2, 3) FT_SUB(3, 4) FT_SUB(4, 5) FT_SUB(5, 6) FT_SUB(6, 7)
+          FT_SUB(7, 8) FT_SUB(8, 9) FT_SUB(9, 10) FT_SUB(10, 11) FT_SUB(11, 12) FT_SUB(12, 13) FT_SUB(13, 14)
+              FT_SUB(14, 15)
+      : "+v"(z)
+      : "v"(L[0]), "v"(L[1]), "v"(L[2]), "v"(L[3]), "v"(L[4]), "v"(L[5]), "v"(L[6]), "v"(L[7]), "v"(L[8]), "v"(L[9]),
+        "v"(L[10]), "v"(L[11]), "v"(L[12]), "v"(L[13]), "v"(L[14]));
+  return z;
+}
+
+// y[0..S-1] += (lane S's L[0..S-1]) * y[S]: one step of the rows of
+// (I + gp tril(K, -1))^-1, lane i holding row i
+template <int S>
+__device__ __forceinline__ void inverse_step(float (&y)[16], const float (&L)[16]) {
+#define FT_INV(n) asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:" #n " row_mask:0xf bank_mask:0xf" : "+v"(y[s]) : "v"(L[s]), "v"(y[S]))
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    g[e] = 0.f;
+  for (int s = 0; s < S; ++s) {
+    if constexpr (S == 1) FT_INV(1);
+    if constexpr (S == 2) FT_INV(2);
+    if constexpr (S == 3) FT_INV(3);
+    if constexpr (S == 4) FT_INV(4);
+    if constexpr (S == 5) FT_INV(5);
+    if constexpr (S == 6) FT_INV(6);
+    if constexpr (S == 7) FT_INV(7);
+    if constexpr (S == 8) FT_INV(8);
+    if constexpr (S == 9) FT_INV(9);
+    if constexpr (S == 10) FT_INV(10);
+    if constexpr (S == 11) FT_INV(11);
+    if constexpr (S == 12) FT_INV(12);
+    if constexpr (S == 13) FT_INV(13);
+    if constexpr (S == 14) FT_INV(14);
+    if constexpr (S == 15) FT_INV(15);
+  }
+#undef FT_INV
+}
+
+// This lane's part of B(m) as the left operand of G^T = B W^T: row r of tile
+// jt is factor index jmap(jt, r); the k values of lane (i, g) are the
+// contiguous rank indices KR g + s, so that W comes as contiguous slices.
+template <int J, int R, class T>
+__device__ __forceinline__ void load_b(const T* __restrict__ Bm, int i, int g, float (&b)[Geo<J>::JT][R / 4]) {
+  constexpr int KR = R / 4;
 #pragma unroll
-    for (int q = 0; q < RE; ++q) dot_bcast<RK>(g[e], ws[q], &Bw[e][16 * q]);
+  for (int jt = 0; jt < Geo<J>::JT; ++jt) {
+    const int j = Geo<J>::jmap(jt, i);
+#pragma unroll
+    for (int k = 0; k < KR; ++k) b[jt][k] = j >= 0 ? to_f(Bm[j * R + KR * g + k]) : 0.f;
   }
 }
 
+// G^T = B W^T of 16 slots: lane (i, g) gets G[i][jbase(g) + k], k < J / 4.
+// The one place where g is formed, so that every caller gets the same bits.
+template <int J, int R>
+__device__ __forceinline__ void form_g(const float (&b)[Geo<J>::JT][R / 4], const float (&w)[R / 4],
+                                       float (&G)[Geo<J>::NG]) {
+  constexpr int VJ = Geo<J>::VJ;
+  floatx4 acc[Geo<J>::JT];
+#pragma unroll
+  for (int jt = 0; jt < Geo<J>::JT; ++jt) acc[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < R / 4; ++k)
+#pragma unroll
+    for (int jt = 0; jt < Geo<J>::JT; ++jt)
+      acc[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[jt][k], w[k], acc[jt], 0, 0, 0);
+#pragma unroll
+  for (int jt = 0; jt < Geo<J>::JT; ++jt)
+#pragma unroll
+    for (int v = 0; v < VJ; ++v) G[VJ * jt + v] = acc[jt][v];
+}
+
+// Source of the blocks' G: the C rows of an element's other modes (w, then
+// B(m) w), its fiber's g, or (NC, order 3 and J = R = 16) C rows formed from
+// A and B on use.  `Idx` is what a lane loads for its slot, `Raw` the slices
+// gathered with it; both are loaded blocks ahead of their use.
+template <int N, int J, int R, class T, bool FIB, bool NC>
+struct Source {
+  static constexpr int KR = R / 4;
+  static constexpr int NI = FIB ? 1 : N - 1;
+  static constexpr int RK = FIB ? Geo<J>::NG : KR;
+  using E = typename std::conditional<FIB, float, T>::type;  // element type of the gathered table
+  struct Idx {
+    uint32_t o[NI];
+    float x;
+  };
+  struct Raw {
+    Slice<E, RK> s[NI];
+  };
+  const int32_t* idx;
+  int64_t nnz;
+  const float* val;
+  CPtrs<N, T> cp;
+  const int32_t* fid;
+  const float* gfib;
+  NoC<N> nc;
+  float b[Geo<J>::JT][KR];
+  float bn[NC ? N - 1 : 1][4];  // B(n) of the other modes as left operands (NC)
+  int i, g;
+
+  __device__ __forceinline__ void init(const T* Bm, int lane) {
+    i = lane & 15;
+    g = lane >> 4;
+    if constexpr (!FIB) load_b<J, R, T>(Bm, i, g, b);
+    if constexpr (NC)
+#pragma unroll
+      for (int k = 0; k < N - 1; ++k)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) bn[k][s] = nc.B[k][(4 * g + s) * R + i];
+  }
+  // slot i of the block at position p0 of an item ending before pe (clamped to its last element)
+  __device__ __forceinline__ void index(int64_t p0, int64_t pe, Idx& a) const {
+    const int64_t p = min(p0 + i, pe - 1);
+    a.x = val[p];
+    if constexpr (FIB) {
+      a.o[0] = (uint32_t)fid[p];
+    } else {
+#pragma unroll
+      for (int k = 0; k < N - 1; ++k) a.o[k] = (uint32_t)idx[(int64_t)k * nnz + p];
+    }
+  }
+  __device__ __forceinline__ void gather(const Idx& a, Raw& r) const {
+    if constexpr (FIB) {
+      // fibers number up to nnz: 64-bit offsets
+      const float* row = gfib + (int64_t)a.o[0] * J;
+      r.s[0].load(row, (uint32_t)(Geo<J>::jbase(g) * sizeof(float)));
+    } else if constexpr (NC) {
+#pragma unroll
+      for (int k = 0; k < N - 1; ++k) r.s[k].load(nc.A[k] + (int64_t)a.o[k] * 16, (uint32_t)(4 * g * sizeof(float)));
+    } else {
+#pragma unroll
+      for (int k = 0; k < N - 1; ++k)
+        r.s[k].load(cp.p[k], row_bytes<R, T>((int32_t)a.o[k]) + (uint32_t)(KR * g * sizeof(T)));
+    }
+  }
+  // G of the block (zero in slots from nb on)
+  __device__ __forceinline__ void form(const Raw& r, int nb, float (&G)[Geo<J>::NG]) const {
+    const bool ok = i < nb;
+    if constexpr (FIB) {
+      r.s[0].widen(G);
+#pragma unroll
+      for (int k = 0; k < Geo<J>::NG; ++k) G[k] = ok ? G[k] : 0.f;
+    } else {
+      float w[KR];
+      if constexpr (NC) {
+#pragma unroll
+        for (int k = 0; k < N - 1; ++k) {
+          float av[4];
+          r.s[k].widen(av);
+          floatx4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f32_16x16x4f32(bn[k][s], av[s], c, 0, 0, 0);
+#pragma unroll
+          for (int s = 0; s < 4; ++s) w[s] = k == 0 ? c[s] : w[s] * c[s];
+        }
+      } else {
+        r.s[0].widen(w);
+#pragma unroll
+        for (int k = 1; k < N - 1; ++k) {
+          float t[KR];
+          r.s[k].widen(t);
+#pragma unroll
+          for (int s = 0; s < KR; ++s) w[s] *= t[s];
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < KR; ++s) w[s] = ok ? w[s] : 0.f;
+      form_g<J, R>(b, w, G);
+    }
+  }
+};
+
 // The shared intermediate of Section 3.2: g_f = B(m) w_f once per mode-m
 // fiber f (w_f = prod_{n != m} C(n)[i_n, :] is the same for every element of
-// the fiber).  Same lane layout and operation order as the per-element path,
-// so the factor pass gives the same bits either way.  Each 16-lane group takes
-// fiber_batches batches of 16 fibers and issues all their gathers first (one
-// batch when the gathered values of two would not fit in registers).
-template <int N, int R>
-constexpr int fiber_batches() {
-  return (N - 1) * (R >= 16 ? R / 16 : 1) > 8 ? 1 : 2;
-}
+// the fiber), formed by the same code as the per-element path, so the factor
+// pass gives the same bits either way.  A wavefront takes kFiberBlocks blocks
+// of 16 fibers and gathers one block ahead.
+constexpr int kFiberBlocks = 4;
 
 template <int N, int J, int R, class T>
 __global__ __launch_bounds__(256) void k_fiber_g(const int32_t* __restrict__ fib_idx, int64_t nfib, CPtrs<N, T> cp,
                                                  const T* __restrict__ Bm, float* __restrict__ gfib) {
-  constexpr int E = J >= 16 ? J / 16 : 1;
-  constexpr int RE = R >= 16 ? R / 16 : 1;
-  constexpr int FB = fiber_batches<N, R>();
-  const int l = threadIdx.x & 15;
-  const int64_t f00 = ((int64_t)blockIdx.x * 16 + (threadIdx.x >> 4)) * 16 * FB;
-  float Bw[E][R];
+  using Src = Source<N, J, R, T, false, false>;
+  Src src;
+  src.nnz = nfib;
+  src.cp = cp;
+  src.init(Bm, threadIdx.x & 63);
+  const int64_t f0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * (16 * kFiberBlocks);
+  if (f0 >= nfib) return;
+  auto index = [&](int64_t f, typename Src::Idx& a) {
+    const int64_t p = min(f + src.i, nfib - 1);
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int j = l + 16 * e;
-#pragma unroll
-    for (int r = 0; r < R; ++r) Bw[e][r] = j < J ? to_f(Bm[j * R + r]) : 0.f;
-  }
-  int len[FB];
-  int ixb[FB][N - 1];
-#pragma unroll
-  for (int b = 0; b < FB; ++b) {
-    const int64_t f0 = f00 + 16 * b;
-    len[b] = (int)max<int64_t>(0, min<int64_t>(16, nfib - f0));
-    const int64_t f = min(f0 + l, nfib - 1);
-#pragma unroll
-    for (int k = 0; k < N - 1; ++k)
-      ixb[b][k] = len[b] > 0 ? (int)row_bytes<R, T>(fib_idx[(int64_t)k * nfib + f]) : 0;
-  }
-  float w[FB][16][RE];
-#pragma unroll
-  for (int b = 0; b < FB; ++b) gather_w<N, R, T>(cp, ixb[b], l, 0, len[b], w[b]);
-#pragma unroll
-  for (int b = 0; b < FB; ++b) {
-    const int64_t f0 = f00 + 16 * b;
-    static_for<0, 16>([&](auto S) {
-      constexpr int s = decltype(S)::value;
-      float g[E];
-      shared_g<J, R>(Bw, w[b][s], g);
-      if (s < len[b]) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          const int j = l + 16 * e;
-          if (j < J) gfib[(f0 + s) * J + j] = g[e];
-        }
-      }
-    });
-  }
-}
-
-// Heads write the row's head vector, or A(m) itself when hvec is null (the
-// relaxed passes).  With RLX the items are the chunks of long rows under
-// FT_RELAXED: each runs from the row as its head left it, a_H (in A(m); the
-// merge that follows is the only other writer) and stores its increment
-// beyond the decay of a_H, weighted by the decay of the row's later elements,
-//     rho^T (a - rho^len a_H),   T = elements of the row after the chunk,
-// and the sum of ||g||^2 over its steps, J + 1 floats per chunk slot.
-template <int N, int J, int R, class T, bool FIB, bool NC = false, bool RLX = false>
-__device__ __forceinline__ void apply_item(int64_t gid, const FItem* __restrict__ items, int64_t n_items,
-                                           const int32_t* __restrict__ idx, int64_t nnz, const float* __restrict__ val,
-                                           const CPtrs<N, T>& cp, const T* __restrict__ Bm, float* __restrict__ Am,
-                                           float* __restrict__ hvec, float lr, float c1,
-                                           const int32_t* __restrict__ fid, const float* __restrict__ gfib,
-                                           const NoC<N>& nc, float* __restrict__ incr,
-                                           const int64_t* __restrict__ row_ptr, double rho) {
-  constexpr int E = J >= 16 ? J / 16 : 1;
-  constexpr int RE = R >= 16 ? R / 16 : 1;
-  const int l = threadIdx.x & 15;
-  float Bw[E][R];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int j = l + 16 * e;
-#pragma unroll
-    for (int r = 0; r < R; ++r) Bw[e][r] = (!FIB && j < J) ? to_f(Bm[j * R + r]) : 0.f;
-  }
-  static_assert(!NC || (J == 16 && R == 16 && !FIB), "the no-C-cache variant is built for J = R = 16");
-  float Bc[N > 1 ? N - 1 : 1][16];
-  if constexpr (NC) load_nc_cols<N>(nc, l, Bc);
-  FItem it{0, 0, 0, 0, 0};
-  if (gid < n_items) it = items[gid];
-  // The row is carried in FP64 registers and rounded to FP32 once when
-  // stored: the decay step lr*lam*a is about a hundred ulps of a, nearly the
-  // same every step, so FP32 rounding of the running state would accumulate
-  // coherently (up to k/2 ulps after k steps) instead of averaging out.
-  double a[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int j = l + 16 * e;
-    a[e] = (it.len > 0 && j < J) ? (double)Am[(int64_t)it.row * J + j] : 0.0;
-  }
-  int maxlen = it.len;
-  maxlen = max(maxlen, __shfl_xor(maxlen, 16));
-  maxlen = max(maxlen, __shfl_xor(maxlen, 32));
-  // Software pipeline over batches of 16 elements: while the 16 dependent
-  // steps of batch b run, the gathers of batch b + 1 and the index loads of
-  // batch b + 2 are in flight, so a long serial item waits on arithmetic, not
-  // on memory.  Past the end, positions clamp to the item's last element (a
-  // valid address) and steps are neutralised (w = 0, no decay).
-  constexpr int WD = FIB ? E : RE;
-  constexpr int NI = N > 1 ? N - 1 : 1;
-  auto stage_a = [&](int t0, float& xv, int (&ix)[NI]) {
-    const int64_t p = it.start + min(t0 + l, max(it.len - 1, 0));
-    xv = it.len > 0 ? val[p] : 0.f;
-    if constexpr (FIB) {
-      ix[0] = it.len > 0 ? fid[p] : 0;
-    } else {
-#pragma unroll
-      for (int k = 0; k < N - 1; ++k)
-        ix[k] = it.len > 0 ? (NC ? idx[(int64_t)k * nnz + p] : (int)row_bytes<R, T>(idx[(int64_t)k * nnz + p])) : 0;
-    }
+    for (int k = 0; k < N - 1; ++k) a.o[k] = (uint32_t)fib_idx[(int64_t)k * nfib + p];
   };
-  auto stage_b = [&](int t0, const int (&ix)[NI], float (&w)[16][WD]) {
-    if constexpr (FIB) {
-      static_for<0, 16>([&](auto S) {
-        constexpr int s = decltype(S)::value;
-        const int64_t fb = (int64_t)bcast16i<s>(ix[0]) * J;
-        const bool sv = (t0 + s) < it.len;
+  typename Src::Idx ix[kFiberBlocks];
+  typename Src::Raw raw;
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-          // unconditional load (a valid fiber, the column clamped) so that all
-          // 16 loads are in flight together; masked afterwards
-          const int j = l + 16 * e;
-          const float gv = gfib[fb + min(j, J - 1)];
-          w[s][e] = (sv && j < J) ? gv : 0.f;
-        }
-      });
-    } else if constexpr (NC) {
-      gather_w_nc<N>(nc, Bc, ix, l, t0, it.len, w);
-    } else {
-      gather_w<N, R, T>(cp, ix, l, t0, it.len, w);
-    }
-  };
-  // (high orders keep one batch in registers: two would spill)
-  constexpr bool PIPE = (N - 1) * WD <= 4;
-  float gg = 0.f;  // sum of ||g||^2 over the steps (RLX)
-  float xv0, xv1 = 0.f;
-  int ix1[NI];
-  float w0[16][WD];
-  if constexpr (PIPE) {
-    int ix0[NI];
-    stage_a(0, xv0, ix0);
-    stage_b(0, ix0, w0);
-    stage_a(16, xv1, ix1);
-  }
-  for (int t0 = 0; t0 < maxlen; t0 += 16) {
-    float wn[16][WD];
-    float xv2 = 0.f;
-    int ix2[NI];
-    if constexpr (PIPE) {
-      stage_b(t0 + 16, ix1, wn);
-      stage_a(t0 + 32, xv2, ix2);
-    } else {
-      int ixc[NI];
-      stage_a(t0, xv0, ixc);
-      stage_b(t0, ixc, w0);
-    }
-    static_for<0, 16>([&](auto S) {
-      constexpr int s = decltype(S)::value;
-      float g[E];
-      if constexpr (FIB) {
+  for (int b = 0; b < kFiberBlocks; ++b) index(f0 + 16 * b, ix[b]);
+  src.gather(ix[0], raw);
 #pragma unroll
-        for (int e = 0; e < E; ++e) g[e] = w0[s][e];
+  for (int b = 0; b < kFiberBlocks; ++b) {
+    const typename Src::Raw cur = raw;
+    if (b + 1 < kFiberBlocks) src.gather(ix[b + 1], raw);
+    float G[Geo<J>::NG];
+    src.form(cur, 16, G);
+    const int64_t f = f0 + 16 * b + src.i;
+    if (f < nfib) {
+      float* dst = gfib + f * J + Geo<J>::jbase(src.g);
+      if constexpr (Geo<J>::NG == 2) {
+        *reinterpret_cast<floatx2*>(dst) = floatx2{G[0], G[1]};
       } else {
-        shared_g<J, R>(Bw, w0[s], g);
-      }
-      float pr = 0.f;
 #pragma unroll
-      for (int e = 0; e < E; ++e) pr = fmaf((float)a[e], g[e], pr);
-      pr = group_sum<16>(pr);
-      const float es = bcast16<s>(xv0) - pr;
-      const double dec = (t0 + s) < it.len ? (double)c1 : 0.0;
-      const double le = (double)(lr * es);
-      if constexpr (RLX) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) gg = fmaf(g[e], g[e], gg);  // g = 0 past the end
-      }
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        a[e] = fma(dec, a[e], a[e]);
-        a[e] = fma(le, (double)g[e], a[e]);
-      }
-    });
-    if constexpr (PIPE) {
-#pragma unroll
-      for (int s = 0; s < 16; ++s)
-#pragma unroll
-        for (int e = 0; e < WD; ++e) w0[s][e] = wn[s][e];
-      xv0 = xv1;
-      xv1 = xv2;
-#pragma unroll
-      for (int k = 0; k < NI; ++k) ix1[k] = ix2[k];
-    }
-  }
-  if constexpr (RLX) {
-    gg = group_sum<16>(gg);
-    if (it.len > 0) {
-      const double own = pow(rho, (double)it.len);
-      const double after = pow(rho, (double)(row_ptr[it.row + 1] - (it.start + it.len)));
-      float* dst = incr + (int64_t)it.slot * (J + 1);
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const int j = l + 16 * e;
-        if (j < J) dst[j] = (float)(after * (a[e] - own * (double)Am[(int64_t)it.row * J + j]));
-      }
-      if (l == 0) dst[J] = gg;
-    }
-    return;
-  }
-  if (it.len > 0) {
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int j = l + 16 * e;
-      if (j < J) {
-        if (it.kind == ITEM_LIGHT || hvec == nullptr)
-          Am[(int64_t)it.row * J + j] = (float)a[e];
-        else
-          hvec[(int64_t)it.slot * J + j] = (float)a[e];
+        for (int k = 0; k < Geo<J>::NG; k += 4)
+          *reinterpret_cast<floatx4*>(dst + k) = floatx4{G[k], G[k + 1], G[k + 2], G[k + 3]};
       }
     }
   }
 }
 
-// One item per 16-lane group: the four groups of a wavefront take four
-// consecutive items (similar lengths, the lists are sorted).
-template <int N, int J, int R, class T, bool FIB, bool NC = false, bool RLX = false>
+// One block ready for its serial part, and (MAP) G by columns for the chunk map.
+template <int J, bool MAP>
+struct Block {
+  float Gu[Geo<J>::NG], Gr[Geo<J>::NS], L[16], xs;
+  float Gc[MAP ? Geo<J>::JT : 1][4];  // G[4 g + v][jmap(jt, i)]
+};
+
+// LDS is private to the wavefront, which executes its accesses in order; the
+// fence keeps the compiler from moving reads of other lanes' values up.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// G and K of a block, and both through LDS into the layouts of the serial
+// part.  G of the state product is read back as well (not taken from the MFMA
+// result), because inline assembly reads it.
+template <int J, bool MAP>
+__device__ __forceinline__ void prepare_block(const float (&G)[Geo<J>::NG], float x, float xscale, int nb, float gp,
+                                              int i, int g, WaveLds<J>& lds, Block<J, MAP>& blk) {
+  using Q = Geo<J>;
+  float* grow = lds.G + i * Q::GS + Q::jbase(g);
+  wave_lds_fence();
+  if constexpr (Q::NG == 2) {
+    *reinterpret_cast<floatx2*>(grow) = floatx2{G[0], G[1]};
+  } else {
+#pragma unroll
+    for (int k = 0; k < Q::NG; k += 4)
+      *reinterpret_cast<floatx4*>(grow + k) = floatx4{G[k], G[k + 1], G[k + 2], G[k + 3]};
+  }
+  floatx4 K = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < Q::NG; ++k) K = __builtin_amdgcn_mfma_f32_16x16x4f32(G[k], G[k], K, 0, 0, 0);
+  floatx4 Lw;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) Lw[v] = 4 * g + v < i ? -gp * K[v] : 0.f;
+  *reinterpret_cast<floatx4*>(lds.L + i * Q::LS + 4 * g) = Lw;
+  wave_lds_fence();
+  if constexpr (Q::NG == 2) {
+    const floatx2 u = *reinterpret_cast<const floatx2*>(grow);
+    blk.Gu[0] = u[0];
+    blk.Gu[1] = u[1];
+  } else {
+#pragma unroll
+    for (int k = 0; k < Q::NG; k += 4) {
+      const floatx4 u = *reinterpret_cast<const floatx4*>(grow + k);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) blk.Gu[k + v] = u[v];
+    }
+  }
+  const float* gcol = lds.G + Q::sbase(g) * Q::GS + Q::jlane(i, g);
+#pragma unroll
+  for (int k = 0; k < Q::NS; ++k) blk.Gr[k] = gcol[k * Q::GS];
+  const float* lrow = lds.L + i * Q::LS;
+#pragma unroll
+  for (int s = 0; s < 16; s += 4) {
+    const floatx4 u = *reinterpret_cast<const floatx4*>(lrow + s);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) blk.L[s + v] = u[v];
+  }
+  if constexpr (MAP) {
+#pragma unroll
+    for (int jt = 0; jt < Q::JT; ++jt) {
+      const int j = Q::jmap(jt, i);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float q = lds.G[(4 * g + v) * Q::GS + max(j, 0)];
+        blk.Gc[jt][v] = j >= 0 ? q : 0.f;
+      }
+    }
+  }
+  blk.xs = i < nb ? x * xscale : 0.f;
+}
+
+// The serial part of a block: a <- rho^nb (a + gp G^T e~).
+template <int J, bool MAP>
+__device__ __forceinline__ void step_block(const Block<J, MAP>& blk, double gp, double rho_nb, double& a) {
+  using Q = Geo<J>;
+  const float af = rotate_state<J>((float)a);
+  const float u = sum_rows(sum_halves(bsum<Q::NG>(af, blk.Gu)));
+  const float e = rotate_slots<J>(forward_substitute(blk.xs - u, blk.L));
+  float d = sum_halves(bsum<Q::NS>(e, blk.Gr));
+  if constexpr (J < 32) d = sum_rows(d);
+  a = rho_nb * fma(gp, (double)d, a);
+}
+
+// by value: a conditional of two array elements would put the array in memory
+__device__ __forceinline__ float pick(int c, float a, float b) { return c ? a : b; }
+
+// The chunk map's block, a -> rho^T (I + Nm) a + v with Nm = prod (I - gp g g^T) - I:
+//     Nm <- Nm - gp G^T (I + gp tril(K, -1))^-1 (G + G Nm).
+// Nm is kept as MFMA results, rows and columns in jmap order: row 4 g + v of
+// tile jt, column i of tile ct.  (Nm is M - I so that the small updates are
+// not absorbed.)
+template <int J>
+__device__ __forceinline__ void map_block(const Block<J, true>& blk, float gp, int i, int g,
+                                          floatx4 (&Nm)[Geo<J>::JT][Geo<J>::JT]) {
+  using Q = Geo<J>;
+  // row i of the inverse, every row of 16 lanes alike
+  float y[16];
+#pragma unroll
+  for (int s = 0; s < 16; ++s) y[s] = s == i ? 1.f : 0.f;
+  asm("s_nop 4" : "+v"(y[15]));
+  inverse_step<15>(y, blk.L);
+  inverse_step<14>(y, blk.L);
+  inverse_step<13>(y, blk.L);
+  inverse_step<12>(y, blk.L);
+  inverse_step<11>(y, blk.L);
+  inverse_step<10>(y, blk.L);
+  inverse_step<9>(y, blk.L);
+  inverse_step<8>(y, blk.L);
+  inverse_step<7>(y, blk.L);
+  inverse_step<6>(y, blk.L);
+  inverse_step<5>(y, blk.L);
+  inverse_step<4>(y, blk.L);
+  inverse_step<3>(y, blk.L);
+  inverse_step<2>(y, blk.L);
+  inverse_step<1>(y, blk.L);
+  // as the left operand: lane (i, g) supplies columns 4 g + v
+  float Ti[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const float lo = pick(g & 1, y[4 + v], y[v]), hi = pick(g & 1, y[12 + v], y[8 + v]);
+    Ti[v] = pick(g & 2, hi, lo);
+  }
+#pragma unroll
+  for (int ct = 0; ct < Q::JT; ++ct) {
+    floatx4 Y = {blk.Gc[ct][0], blk.Gc[ct][1], blk.Gc[ct][2], blk.Gc[ct][3]};
+#pragma unroll
+    for (int k = 0; k < Q::NG; ++k)
+      Y = __builtin_amdgcn_mfma_f32_16x16x4f32(blk.Gu[k], Nm[k / Q::VJ][ct][k % Q::VJ], Y, 0, 0, 0);
+    floatx4 Z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Z = __builtin_amdgcn_mfma_f32_16x16x4f32(Ti[v], Y[v], Z, 0, 0, 0);
+    float Zs[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Zs[v] = -gp * Z[v];
+#pragma unroll
+    for (int jt = 0; jt < Q::JT; ++jt)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        Nm[jt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(blk.Gc[jt][v], Zs[v], Nm[jt][ct], 0, 0, 0);
+  }
+}
+
+// What every item of a launch reads.
+template <int N, int J, int R, class T, bool FIB, bool NC>
+struct FactorArgs {
+  const int32_t* idx;
+  int64_t nnz;
+  const float* val;
+  CPtrs<N, T> cp;
+  const T* Bm;
+  float* Am;
+  float* hvec;
+  const int32_t* fid;
+  const float* gfib;
+  NoC<N> nc;
+  float* maps;         // chunk maps, or the relaxed chunks' increments
+  double* map_scale;
+  const int64_t* row_ptr;
+  double rho, gp;
+  RhoPow pw;
+  int block;           // elements per block (16; 1 where rho^-15 would leave the FP32 range)
+};
+
+enum { ITEM_CHAIN, ITEM_RELAXED, ITEM_MAP };
+
+// One work item on one wavefront.
+//  CHAIN: the row (or the head of a long row) is updated in place; a head
+//    writes the row's head vector, or A(m) itself when hvec is null (the
+//    relaxed passes).
+//  RELAXED: a chunk of a long row under FT_RELAXED runs from the row as its
+//    head left it, a_H (in A(m); the merge that follows is the only other
+//    writer) and stores its increment beyond the decay of a_H, weighted by the
+//    decay of the row's later elements,
+//        rho^T (a - rho^len a_H),   T = elements of the row after the chunk,
+//    and the sum of ||g||^2 over its steps, J + 1 floats per chunk slot.
+//  MAP: a chunk's affine map a -> rho^len (I + Nm) a + v; v is the state
+//    reached from a = 0.
+template <int KIND, int N, int J, int R, class T, bool FIB, bool NC>
+__device__ __forceinline__ void factor_item(const FItem& it, const FactorArgs<N, J, R, T, FIB, NC>& F,
+                                            WaveLds<J>& lds) {
+  using Q = Geo<J>;
+  constexpr bool MAP = KIND == ITEM_MAP;
+  const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+  if (it.len <= 0) return;
+  Source<N, J, R, T, FIB, NC> src;
+  src.idx = F.idx;
+  src.nnz = F.nnz;
+  src.val = F.val;
+  src.cp = F.cp;
+  src.fid = F.fid;
+  src.gfib = F.gfib;
+  src.nc = F.nc;
+  src.init(F.Bm, lane);
+  const int64_t pe = it.start + it.len;
+  const int bs = F.block;
+  const int jl = Q::jlane(i, g);
+  const float gpf = (float)F.gp;
+  const float xscale = F.pw.inv[i];
+  double a = 0.0;
+  if constexpr (!MAP) a = (double)F.Am[(int64_t)it.row * J + jl];
+  floatx4 Nm[Q::JT][Q::JT];
+  if constexpr (MAP)
+#pragma unroll
+    for (int jt = 0; jt < Q::JT; ++jt)
+#pragma unroll
+      for (int ct = 0; ct < Q::JT; ++ct) Nm[jt][ct] = floatx4{0.f, 0.f, 0.f, 0.f};
+  float gg = 0.f;  // sum of ||g||^2 (RELAXED), this lane's part
+  // Pipeline: the gathers of block b + 1 and the indices of block b + 2 are in
+  // flight while block b is formed, and block b is formed (MFMA, LDS) beside
+  // the serial part of block b - 1 (VALU).
+  typename Source<N, J, R, T, FIB, NC>::Idx ix0, ix1;
+  typename Source<N, J, R, T, FIB, NC>::Raw raw;
+  src.index(it.start, pe, ix0);
+  src.gather(ix0, raw);
+  src.index(min(it.start + bs, pe - 1), pe, ix1);
+  Block<J, MAP> cur;
+  auto form = [&](int64_t p, Block<J, MAP>& blk) {
+    const int nb = (int)min<int64_t>(bs, pe - p);
+    float G[Q::NG];
+    src.form(raw, nb, G);
+    const float x = ix0.x;
+    ix0 = ix1;
+    src.gather(ix0, raw);
+    src.index(min(p + 2 * bs, pe - 1), pe, ix1);
+    if constexpr (KIND == ITEM_RELAXED)
+#pragma unroll
+      for (int k = 0; k < Q::NG; ++k) gg = fmaf(G[k], G[k], gg);
+    prepare_block<J, MAP>(G, x, xscale, nb, gpf, i, g, lds, blk);
+  };
+  form(it.start, cur);
+  int64_t p = it.start;
+  if constexpr (MAP) {
+    // (a map's own products keep the matrix cores busy: its blocks are formed one after another, which
+    // leaves registers for three wavefronts per SIMD)
+    for (;;) {
+      step_block<J, MAP>(cur, F.gp, F.pw.p[min<int64_t>(bs, pe - p)], a);
+      map_block<J>(cur, gpf, i, g, Nm);
+      p += bs;
+      if (p >= pe) break;
+      form(p, cur);
+    }
+  } else {
+    for (; p + bs < pe; p += bs) {
+      Block<J, MAP> nxt;
+      form(p + bs, nxt);
+      step_block<J, MAP>(cur, F.gp, F.pw.p[bs], a);
+      cur = nxt;
+    }
+    step_block<J, MAP>(cur, F.gp, F.pw.p[pe - p], a);
+  }
+
+  // lanes that hold a copy of the state's element jl write it once
+  const bool writer = J >= 32 ? g < 2 : g == 0 && i < J;
+  if constexpr (KIND == ITEM_CHAIN) {
+    float* dst = it.kind == ITEM_LIGHT || F.hvec == nullptr ? F.Am + (int64_t)it.row * J : F.hvec + (int64_t)it.slot * J;
+    if (writer) dst[jl] = (float)a;
+  } else if constexpr (KIND == ITEM_RELAXED) {
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) gg += __shfl_xor(gg, off);
+    const double own = pow(F.rho, (double)it.len);
+    const double after = pow(F.rho, (double)(F.row_ptr[it.row + 1] - pe));
+    float* dst = F.maps + (int64_t)it.slot * (J + 1);
+    if (writer) dst[jl] = (float)(after * (a - own * (double)F.Am[(int64_t)it.row * J + jl]));
+    if (lane == 0) dst[J] = gg;
+  } else {
+    float* dst = F.maps + (int64_t)it.slot * (J * J + J);  // column-major
+#pragma unroll
+    for (int ct = 0; ct < Q::JT; ++ct) {
+      const int c = Q::jmap(ct, i);
+#pragma unroll
+      for (int jt = 0; jt < Q::JT; ++jt) {
+        const int r = Q::jmap(jt, 4 * g);
+        if constexpr (Q::VJ == 4)
+          *reinterpret_cast<floatx4*>(dst + c * J + r) = Nm[jt][ct];
+        else if (c >= 0)
+          *reinterpret_cast<floatx2*>(dst + c * J + r) = floatx2{Nm[jt][ct][0], Nm[jt][ct][1]};
+      }
+    }
+    if (writer) dst[J * J + jl] = (float)a;
+    if (lane == 0) F.map_scale[it.slot] = pow(F.rho, (double)it.len);
+  }
+}
+
+// One item per wavefront: the hardware dispatcher balances the items (the
+// lists are sorted by length, so that a workgroup's four end together).
+template <int KIND, int N, int J, int R, class T, bool FIB, bool NC = false>
 __global__ __launch_bounds__(256) void k_factor_apply(const FItem* __restrict__ items, int64_t n_items,
-                                                      const int32_t* __restrict__ idx, int64_t nnz,
-                                                      const float* __restrict__ val, CPtrs<N, T> cp,
-                                                      const T* __restrict__ Bm, float* __restrict__ Am,
-                                                      float* __restrict__ hvec, float lr, float c1,
-                                                      const int32_t* __restrict__ fid, const float* __restrict__ gfib,
-                                                      NoC<N> nc, float* __restrict__ incr,
-                                                      const int64_t* __restrict__ row_ptr, double rho) {
-  apply_item<N, J, R, T, FIB, NC, RLX>((int64_t)blockIdx.x * 16 + (threadIdx.x >> 4), items, n_items, idx, nnz, val,
-                                       cp, Bm, Am, hvec, lr, c1, fid, gfib, nc, incr, row_ptr, rho);
-}
-
-// Chunk maps.  With rho = 1 - lr lam and gp = lr / rho, one step is
-//     a <- rho (I - gp g g^T) a + lr x g.
-// A chunk of T steps is the affine map a -> rho^T (I + Nm) a + v with
-//     Nm <- Nm - gp g (g + Nm^T g)^T     (Nm = prod (I - gp g g^T) - I)
-//     v  <- v + (-lr lam) v + lr (x - v.g) g
-// (v is the state reached from a = 0).  Lane j keeps column j of Nm.
-template <int N, int J, int R, class T, bool FIB, bool NC = false>
-__device__ __forceinline__ void compose_item(int64_t gid, const FItem* __restrict__ items, int64_t n_items,
-                                             const int32_t* __restrict__ idx, int64_t nnz,
-                                             const float* __restrict__ val, const CPtrs<N, T>& cp,
-                                             const T* __restrict__ Bm, float* __restrict__ maps,
-                                             double* __restrict__ map_scale, float lr, float c1, float gp, double rho,
-                                             const int32_t* __restrict__ fid, const float* __restrict__ gfib,
-                                             const NoC<N>& nc) {
-  constexpr int E = J >= 16 ? J / 16 : 1;
-  constexpr int RE = R >= 16 ? R / 16 : 1;
-  constexpr int MS = J * J + J;
-  const int l = threadIdx.x & 15;
-  float Bw[E][R];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int j = l + 16 * e;
-#pragma unroll
-    for (int r = 0; r < R; ++r) Bw[e][r] = (!FIB && j < J) ? to_f(Bm[j * R + r]) : 0.f;
-  }
-  static_assert(!NC || (J == 16 && R == 16 && !FIB), "the no-C-cache variant is built for J = R = 16");
-  float Bc[N > 1 ? N - 1 : 1][16];
-  if constexpr (NC) load_nc_cols<N>(nc, l, Bc);
-  FItem it{0, 0, 0, 0, 0};
-  if (gid < n_items) it = items[gid];
-  float Nc[E][J];
-  float v[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    v[e] = 0.f;
-#pragma unroll
-    for (int i = 0; i < J; ++i) Nc[e][i] = 0.f;
-  }
-  int maxlen = it.len;
-  maxlen = max(maxlen, __shfl_xor(maxlen, 16));
-  maxlen = max(maxlen, __shfl_xor(maxlen, 32));
-  for (int t0 = 0; t0 < maxlen; t0 += 16) {
-    // past the end: clamp to the item's last element (valid address); those
-    // steps are neutralised below (w = 0, no decay)
-    const int64_t p = it.start + min(t0 + l, max(it.len - 1, 0));
-    const float xv = it.len > 0 ? val[p] : 0.f;
-    // phase 1: w of the 16 elements (or, with fibers, their precomputed g)
-    float w[16][FIB ? E : RE];
-    if constexpr (FIB) {
-      const int fv = it.len > 0 ? fid[p] : 0;
-      static_for<0, 16>([&](auto S) {
-        constexpr int s = decltype(S)::value;
-        const int64_t fb = (int64_t)bcast16i<s>(fv) * J;
-        const bool sv = (t0 + s) < it.len;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          // unconditional load (fv is a valid fiber, the column clamped) so
-          // that all 16 loads are in flight together; masked afterwards
-          const int j = l + 16 * e;
-          const float gv = gfib[fb + min(j, J - 1)];
-          w[s][e] = (sv && j < J) ? gv : 0.f;
-        }
-      });
-    } else {
-      int ix[N - 1];
-#pragma unroll
-      for (int k = 0; k < N - 1; ++k)
-        ix[k] = it.len > 0 ? (NC ? idx[(int64_t)k * nnz + p] : (int)row_bytes<R, T>(idx[(int64_t)k * nnz + p])) : 0;
-      if constexpr (NC)
-        gather_w_nc<N>(nc, Bc, ix, l, t0, it.len, w);
-      else
-        gather_w<N, R, T>(cp, ix, l, t0, it.len, w);
-    }
-    static_for<0, 16>([&](auto S) {
-      constexpr int s = decltype(S)::value;
-      float g[E];
-      if constexpr (FIB) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) g[e] = w[s][e];
-      } else {
-        shared_g<J, R>(Bw, w[s], g);
-      }
-      constexpr int JK = J >= 16 ? 16 : J;
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        // h = g_j + sum_i Nm[i][j] g_i ;  Nm[:, j] -= gp * h * g
-        float h = g[e];
-#pragma unroll
-        for (int q = 0; q < E; ++q) dot_bcast<JK>(h, g[q], &Nc[e][16 * q]);
-        const float t = -gp * h;
-#pragma unroll
-        for (int q = 0; q < E; ++q) axpy_bcast<JK>(&Nc[e][16 * q], g[q], t);
-      }
-      float pr = 0.f;
-#pragma unroll
-      for (int e = 0; e < E; ++e) pr = fmaf(v[e], g[e], pr);
-      pr = group_sum<16>(pr);
-      const float es = bcast16<s>(xv) - pr;
-      const float dec = (t0 + s) < it.len ? c1 : 0.f;
-      const float le = lr * es;
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        v[e] = fmaf(dec, v[e], v[e]);
-        v[e] = fmaf(le, g[e], v[e]);
-      }
-    });
-  }
-  if (it.len > 0) {
-    float* dst = maps + (int64_t)it.slot * MS;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int j = l + 16 * e;
-      if (j < J) {
-#pragma unroll
-        for (int i = 0; i < J; ++i) dst[j * J + i] = Nc[e][i];  // column-major
-        dst[J * J + j] = v[e];
-      }
-    }
-    if (l == 0) map_scale[it.slot] = pow(rho, (double)it.len);
-  }
+                                                      FactorArgs<N, J, R, T, FIB, NC> F) {
+  __shared__ WaveLds<J> lds[4];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t k = (int64_t)blockIdx.x * 4 + wave;
+  if (k < n_items) factor_item<KIND>(items[k], F, lds[wave]);
 }
 
 template <int N, int J, int R, class T, bool FIB, bool NC = false>
 __global__ __launch_bounds__(256) void k_factor_compose(const FItem* __restrict__ items, int64_t n_items,
-                                                        const int32_t* __restrict__ idx, int64_t nnz,
-                                                        const float* __restrict__ val, CPtrs<N, T> cp,
-                                                        const T* __restrict__ Bm, float* __restrict__ maps,
-                                                        double* __restrict__ map_scale, float lr, float c1, float gp,
-                                                        double rho, const int32_t* __restrict__ fid,
-                                                        const float* __restrict__ gfib, NoC<N> nc) {
-  compose_item<N, J, R, T, FIB, NC>((int64_t)blockIdx.x * 16 + (threadIdx.x >> 4), items, n_items, idx, nnz, val, cp,
-                                    Bm, maps, map_scale, lr, c1, gp, rho, fid, gfib, nc);
+                                                        FactorArgs<N, J, R, T, FIB, NC> F) {
+  __shared__ WaveLds<J> lds[4];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t k = (int64_t)blockIdx.x * 4 + wave;
+  if (k < n_items) factor_item<ITEM_MAP>(items[k], F, lds[wave]);
 }
 
 // The in-place items and the chunk maps of one exact factor pass in one
 // launch.  They are independent (a map starts from the identity, not from
 // its row's head), so the first apply_blocks workgroups take the in-place
 // items, heads of long rows first, and the rest the chunk maps: the long
-// serial heads start at once and run while the maps keep the SIMDs busy,
+// serial heads then start at once and run while the maps keep the SIMDs busy,
 // instead of running on an otherwise idle GPU after them.
 template <int N, int J, int R, class T, bool FIB, bool NC = false>
 __global__ __launch_bounds__(256) void k_factor_fused(int64_t apply_blocks, const FItem* __restrict__ apply_items,
                                                       int64_t n_apply, const FItem* __restrict__ compose_items,
-                                                      int64_t n_compose, const int32_t* __restrict__ idx, int64_t nnz,
-                                                      const float* __restrict__ val, CPtrs<N, T> cp,
-                                                      const T* __restrict__ Bm, float* __restrict__ Am,
-                                                      float* __restrict__ hvec, float* __restrict__ maps,
-                                                      double* __restrict__ map_scale, float lr, float c1, float gp,
-                                                      double rho, const int32_t* __restrict__ fid,
-                                                      const float* __restrict__ gfib, NoC<N> nc) {
-  const int64_t grp = threadIdx.x >> 4;
-  if ((int64_t)blockIdx.x < apply_blocks)
-    apply_item<N, J, R, T, FIB, NC, false>((int64_t)blockIdx.x * 16 + grp, apply_items, n_apply, idx, nnz, val, cp,
-                                           Bm, Am, hvec, lr, c1, fid, gfib, nc, nullptr, nullptr, rho);
-  else
-    compose_item<N, J, R, T, FIB, NC>(((int64_t)blockIdx.x - apply_blocks) * 16 + grp, compose_items, n_compose, idx,
-                                      nnz, val, cp, Bm, maps, map_scale, lr, c1, gp, rho, fid, gfib, nc);
+                                                      int64_t n_compose, FactorArgs<N, J, R, T, FIB, NC> F) {
+  __shared__ WaveLds<J> lds[4];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if ((int64_t)blockIdx.x < apply_blocks) {
+    const int64_t k = (int64_t)blockIdx.x * 4 + wave;
+    if (k < n_apply) factor_item<ITEM_CHAIN>(apply_items[k], F, lds[wave]);
+  } else {
+    const int64_t k = ((int64_t)blockIdx.x - apply_blocks) * 4 + wave;
+    if (k < n_compose) factor_item<ITEM_MAP>(compose_items[k], F, lds[wave]);
+  }
 }
 
 // Fold `count` consecutive maps (earliest first) into one, as a binary tree in
@@ -748,52 +1009,62 @@ __global__ __launch_bounds__(256) void k_relaxed_merge(const CItem* __restrict__
   }
 }
 
-// One item per 16-lane group: the hardware dispatcher balances the items
-// (measured faster than a grid-stride loop, which also costs registers).
-unsigned factor_blocks(const void* kernel, int64_t n_items) {
-  (void)kernel;
-  return (unsigned)std::max<int64_t>(1, (n_items + 15) / 16);
-}
+// workgroups of four items, one per wavefront
+unsigned factor_blocks(int64_t n_items) { return (unsigned)((n_items + 3) / 4); }
 
 template <int N, int J, int R, class T, bool FIB, bool NC = false>
 hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scratch& S, double lr, double lam,
                          hipStream_t s) {
   const ModeMeta& M = P->meta[m];
   const ModeDev& D = P->dev[m];
-  const CPtrs<N, T> cp = others<N, T>(p, m);
-  NoC<N> nc{};
+  FactorArgs<N, J, R, T, FIB, NC> F{};
+  F.idx = D.idx;
+  F.nnz = P->nnz;
+  F.val = D.val;
+  F.cp = others<N, T>(p, m);
+  F.Bm = Store<T>::B(p, m);
+  F.Am = p->A[m];
+  F.hvec = S.hvec;
+  F.fid = D.fid;
+  F.gfib = S.gfib;
   if (NC)
     for (int k = 0; k < N - 1; ++k) {
-      nc.A[k] = p->A[(m + 1 + k) % N];
-      nc.B[k] = p->B[(m + 1 + k) % N];
+      F.nc.A[k] = p->A[(m + 1 + k) % N];
+      F.nc.B[k] = p->B[(m + 1 + k) % N];
     }
-  const T* Bm = Store<T>::B(p, m);
-  const double rho = 1.0 - lr * lam;
-  const float flr = (float)lr, c1 = (float)(-lr * lam), gp = (float)(lr / rho);
+  F.maps = S.maps;
+  F.map_scale = S.map_scale;
+  F.row_ptr = D.row_ptr;
+  F.rho = 1.0 - lr * lam;
+  F.gp = lr / F.rho;
+  // rho^-15 scales the values of a block: with rho >= 1/2 it stays below 2^15;
+  // a decay above that (lr lam > 1/2) is stepped element by element
+  F.block = F.rho >= 0.5 ? 16 : 1;
+  F.pw.p[0] = 1.0;
+  for (int k = 1; k <= 16; ++k) F.pw.p[k] = F.pw.p[k - 1] * F.rho;
+  for (int k = 0; k < 16; ++k) F.pw.inv[k] = k < F.block ? (float)(1.0 / F.pw.p[k]) : 0.f;
   if (FIB) {
     KTimer tm(P, FT_K_FIBER_G, s);
-    // fiber_batches batches of 16 fibers per 16-lane group, 16 groups per workgroup
-    const int64_t per_block = 16 * 16 * fiber_batches<N, R>();
+    const int64_t per_block = 4 * 16 * kFiberBlocks;  // fibers of a workgroup
     hipLaunchKernelGGL((k_fiber_g<N, J, R, T>), dim3((unsigned)((M.n_fibers + per_block - 1) / per_block)), dim3(256),
-                       0, s, D.fib_idx, M.n_fibers, cp, Bm, S.gfib);
+                       0, s, D.fib_idx, M.n_fibers, F.cp, F.Bm, S.gfib);
   }
   if constexpr (!NC) {
     if (P->relaxed) {
       // short rows and heads (in place), then the chunks from the rows as their heads left them, then the
       // two merge levels; long rows are read in their dealt order
-      const int32_t* fidx = D.fidx ? D.fidx : D.idx;
-      const float* fval = D.fval ? D.fval : D.val;
+      if (D.fidx) F.idx = D.fidx;
+      if (D.fval) F.val = D.fval;
+      F.hvec = nullptr;
       if (M.n_apply > 0) {
         KTimer tm(P, FT_K_FACTOR_APPLY, s);
-        hipLaunchKernelGGL((k_factor_apply<N, J, R, T, FIB>), dim3(factor_blocks(nullptr, M.n_apply)), dim3(256), 0,
-                           s, D.apply, M.n_apply, fidx, P->nnz, fval, cp, Bm, p->A[m], nullptr, flr, c1, D.fid,
-                           S.gfib, nc, S.maps, D.row_ptr, rho);
+        hipLaunchKernelGGL((k_factor_apply<ITEM_CHAIN, N, J, R, T, FIB>), dim3(factor_blocks(M.n_apply)), dim3(256), 0,
+                           s, D.apply, M.n_apply, F);
       }
       if (M.n_compose > 0) {
         KTimer tm(P, FT_K_FACTOR_COMPOSE, s);
-        hipLaunchKernelGGL((k_factor_apply<N, J, R, T, FIB, false, true>), dim3(factor_blocks(nullptr, M.n_compose)),
-                           dim3(256), 0, s, D.compose, M.n_compose, fidx, P->nnz, fval, cp, Bm, p->A[m], S.hvec,
-                           flr, c1, D.fid, S.gfib, nc, S.maps, D.row_ptr, rho);
+        hipLaunchKernelGGL((k_factor_apply<ITEM_RELAXED, N, J, R, T, FIB>), dim3(factor_blocks(M.n_compose)),
+                           dim3(256), 0, s, D.compose, M.n_compose, F);
       }
       if (M.n_relax > 0) {
         KTimer tm(P, FT_K_COMBINE, s);
@@ -801,30 +1072,27 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
         hipLaunchKernelGGL((k_relaxed_group<J>), dim3((unsigned)M.n_relax_groups), dim3(256), 0, s, D.relax,
                            S.maps, part);
         hipLaunchKernelGGL((k_relaxed_merge<J>), dim3((unsigned)M.n_relax), dim3(256), 0, s,
-                           D.relax + M.n_relax_groups, part, p->A[m], lr, rho);
+                           D.relax + M.n_relax_groups, part, p->A[m], lr, F.rho);
       }
       return hipGetLastError();
     }
   }
   if (M.n_compose > 0 && M.n_apply > 0 && P->fused) {
     KTimer tm(P, FT_K_FACTOR_FUSED, s);
-    const int64_t ab = (M.n_apply + 15) / 16;
-    hipLaunchKernelGGL((k_factor_fused<N, J, R, T, FIB, NC>), dim3((unsigned)(ab + (M.n_compose + 15) / 16)),
-                       dim3(256), 0, s, ab, D.apply, M.n_apply, D.compose, M.n_compose, D.idx, P->nnz, D.val, cp, Bm,
-                       p->A[m], S.hvec, S.maps, S.map_scale, flr, c1, gp, rho, D.fid, S.gfib, nc);
-  } else if (M.n_compose > 0) {
-    KTimer tm(P, FT_K_FACTOR_COMPOSE, s);
-    hipLaunchKernelGGL((k_factor_compose<N, J, R, T, FIB, NC>),
-                       dim3(factor_blocks((const void*)k_factor_compose<N, J, R, T, FIB, NC>, M.n_compose)), dim3(256),
-                       0, s, D.compose, M.n_compose, D.idx, P->nnz, D.val, cp, Bm, S.maps, S.map_scale, flr, c1, gp,
-                       rho, D.fid, S.gfib, nc);
-  }
-  if (M.n_apply > 0 && !(M.n_compose > 0 && P->fused)) {
-    KTimer tm(P, FT_K_FACTOR_APPLY, s);
-    hipLaunchKernelGGL((k_factor_apply<N, J, R, T, FIB, NC>),
-                       dim3(factor_blocks((const void*)k_factor_apply<N, J, R, T, FIB, NC>, M.n_apply)), dim3(256), 0,
-                       s, D.apply, M.n_apply, D.idx, P->nnz, D.val, cp, Bm, p->A[m], S.hvec, flr, c1, D.fid, S.gfib,
-                       nc, S.maps, D.row_ptr, rho);
+    const unsigned ab = factor_blocks(M.n_apply);
+    hipLaunchKernelGGL((k_factor_fused<N, J, R, T, FIB, NC>), dim3(ab + factor_blocks(M.n_compose)), dim3(256), 0, s,
+                       (int64_t)ab, D.apply, M.n_apply, D.compose, M.n_compose, F);
+  } else {
+    if (M.n_compose > 0) {
+      KTimer tm(P, FT_K_FACTOR_COMPOSE, s);
+      hipLaunchKernelGGL((k_factor_compose<N, J, R, T, FIB, NC>), dim3(factor_blocks(M.n_compose)), dim3(256), 0, s,
+                         D.compose, M.n_compose, F);
+    }
+    if (M.n_apply > 0) {
+      KTimer tm(P, FT_K_FACTOR_APPLY, s);
+      hipLaunchKernelGGL((k_factor_apply<ITEM_CHAIN, N, J, R, T, FIB, NC>), dim3(factor_blocks(M.n_apply)), dim3(256),
+                         0, s, D.apply, M.n_apply, F);
+    }
   }
   for (size_t L = 0; L < M.level_len.size(); ++L) {
     KTimer tm(P, FT_K_COMBINE, s);
