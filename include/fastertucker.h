@@ -236,6 +236,16 @@ ft_status ft_predict(const ft_plan* plan, const ft_params* p, const int32_t* d_c
                      void* stream);
 
 /*
+ * ft_predict_checked -- ft_predict with the range of every query coordinate
+ * checked on the device: d_bad int32[N] receives 1 for each mode with an index
+ * outside its dimension and 0 otherwise (cleared by the call when q > 0).  An
+ * index out of range is read as 0, so nothing is read out of bounds; the
+ * output of such a query is meaningless.
+ */
+ft_status ft_predict_checked(const ft_plan* plan, const ft_params* p, const int32_t* d_coords, int64_t q,
+                             float* d_out, int32_t* d_bad, void* stream);
+
+/*
  * ft_factor_pass -- factor module of Algorithm 2 for one mode m: for every
  * element x of Omega, in the plan's per-row order, with
  *     w_x = prod_{n != m} C(n)[i_n, :]   (Eq. (12)),   g_x = B(m) w_x,

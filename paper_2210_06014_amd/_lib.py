@@ -38,6 +38,7 @@ SYMBOLS = [
     "ft_plan_host_csr",
     "ft_refresh",
     "ft_predict",
+    "ft_predict_checked",
     "ft_factor_pass",
     "ft_factor_epoch",
     "ft_core_grad",
@@ -141,6 +142,7 @@ def load():
         "ft_plan_host_csr": ([vp, i32, i32, vp, vp, vp, vp], i32),
         "ft_refresh": ([vp, P(FtParams), i32, vp], i32),
         "ft_predict": ([vp, P(FtParams), vp, i64, vp, vp], i32),
+        "ft_predict_checked": ([vp, P(FtParams), vp, i64, vp, vp, vp], i32),
         "ft_factor_pass": ([vp, P(FtParams), i32, dbl, dbl, vp], i32),
         "ft_factor_epoch": ([vp, P(FtParams), dbl, dbl, vp], i32),
         "ft_core_grad": ([vp, P(FtParams), i32, vp, vp], i32),

@@ -253,7 +253,7 @@ def refresh(plan: Plan, params: Params, mode: int = -1):
 def predict(plan: Plan, params: Params, coords):
     """coords: int32 CUDA tensor [order][q] -> float32 CUDA tensor [q].
 
-    The indices are checked against the dimensions here (the kernel gathers them unchecked)."""
+    The kernel checks the indices against the dimensions as it reads them; the flags come back with one copy."""
     import torch
 
     if not isinstance(coords, torch.Tensor) or not coords.is_cuda or coords.dtype != torch.int32 \
@@ -261,14 +261,14 @@ def predict(plan: Plan, params: Params, coords):
         raise ValueError(f"coords must be an int32 CUDA tensor of shape [{plan.order}][q]")
     coords = coords.contiguous()
     q = coords.shape[1]
-    if q > 0:
-        lo = coords.amin(dim=1).cpu().numpy()
-        hi = coords.amax(dim=1).cpu().numpy()
-        for n in range(plan.order):
-            if lo[n] < 0 or hi[n] >= plan.dims[n]:
-                raise ValueError(f"coordinate of mode {n} out of range [0, {plan.dims[n]})")
     out = torch.empty(q, dtype=torch.float32, device=coords.device)
-    check(plan._lib.ft_predict(plan.handle, _p(plan, params), coords.data_ptr(), q, out.data_ptr(), _stream()))
+    bad = torch.empty(plan.order, dtype=torch.int32, device=coords.device)
+    check(plan._lib.ft_predict_checked(plan.handle, _p(plan, params), coords.data_ptr(), q, out.data_ptr(),
+                                       bad.data_ptr(), _stream()))
+    if q > 0:
+        for n, off in enumerate(bad.tolist()):
+            if off:
+                raise ValueError(f"coordinate of mode {n} out of range [0, {plan.dims[n]})")
     return out
 
 

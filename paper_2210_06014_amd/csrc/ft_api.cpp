@@ -94,14 +94,25 @@ extern "C" ft_status ft_refresh(const ft_plan* P, const ft_params* p, int32_t mo
   return FT_OK;
 }
 
-extern "C" ft_status ft_predict(const ft_plan* P, const ft_params* p, const int32_t* d_coords, int64_t q,
-                                float* d_out, void* stream) {
+static ft_status predict(const ft_plan* P, const ft_params* p, const int32_t* d_coords, int64_t q, float* d_out,
+                         int32_t* d_bad, void* stream) {
   FT_TRY(check_plan(P));
   FT_TRY(check_params(P, p));
   if (q < 0) return fail(FT_ERR_ARG, "negative query count");
   if (q == 0) return FT_OK;
   if (!d_coords || !d_out) return fail(FT_ERR_ARG, "null coords or output");
-  return hip_status(launch_predict(P, p, d_coords, q, d_out, (hipStream_t)stream), "predict");
+  return hip_status(launch_predict(P, p, d_coords, q, d_out, d_bad, (hipStream_t)stream), "predict");
+}
+
+extern "C" ft_status ft_predict(const ft_plan* P, const ft_params* p, const int32_t* d_coords, int64_t q,
+                                float* d_out, void* stream) {
+  return predict(P, p, d_coords, q, d_out, nullptr, stream);
+}
+
+extern "C" ft_status ft_predict_checked(const ft_plan* P, const ft_params* p, const int32_t* d_coords, int64_t q,
+                                        float* d_out, int32_t* d_bad, void* stream) {
+  if (q > 0 && !d_bad) return fail(FT_ERR_ARG, "null range flags");
+  return predict(P, p, d_coords, q, d_out, d_bad, stream);
 }
 
 extern "C" ft_status ft_factor_pass(const ft_plan* P, const ft_params* p, int32_t mode, double lr, double lam,

@@ -241,8 +241,9 @@ hipError_t launch_core_update(const ft_plan* P, int m, const ft_params* p, const
                               hipStream_t s);
 hipError_t launch_loss(const ft_plan* P, const ft_params* p, const Scratch& S, double lam_a, double lam_b,
                        double* out4, hipStream_t s);
+// bad: null, or int32[N] that receives 1 for every mode with an index out of range
 hipError_t launch_predict(const ft_plan* P, const ft_params* p, const int32_t* coords, int64_t q, float* out,
-                          hipStream_t s);
+                          int32_t* bad, hipStream_t s);
 // ft_loss_noalloc: the loss with its partials in the library's static device
 // array (capacity and the bytes a plan needs, in bytes)
 size_t noalloc_loss_capacity();

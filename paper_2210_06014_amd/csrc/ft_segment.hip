@@ -760,27 +760,64 @@ __global__ __launch_bounds__(256) void k_loss_finish(const double* __restrict__ 
   }
 }
 
-// Predictions for query coordinates (structure of arrays [N][q]).
-template <int N, int R, class T>
-__global__ __launch_bounds__(256) void k_predict(const int32_t* __restrict__ coords, int64_t q,
-                                                 CPtrs<N + 1, T> cp, float* __restrict__ out) {
-  constexpr int QL = R / 4;
-  const int64_t tid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t x = tid / QL;
-  const int qq = (int)(tid % QL);
-  const bool vld = x < q;
-  floatx4 w = {1.f, 1.f, 1.f, 1.f};
+// Predictions for query coordinates (structure of arrays [N][q]).  A wavefront
+// takes 64 queries: lane l loads the coordinates of query l (64 distinct
+// addresses per load), then the R / V lanes of each slot gather 16-byte slices
+// of its rows, 64 V / R queries at a time, with the indices handed over by
+// cross-lane permutes.  What bounds it is the rate at which a CU's memory path
+// returns the gathered rows, and index loads that repeat an address over the
+// lanes of a row take half of its issue slots.  With `bad`, an index outside
+// its dimension is replaced by 0 before the gather and marks bad[n] (every
+// writer stores the same value).
+struct DimArgs {
+  int32_t d[FT_MAX_ORDER];
+};
+
+template <int N, int R, class T, bool CHECK>
+__global__ __launch_bounds__(256) void k_predict(const int32_t* __restrict__ coords, int64_t q, CPtrs<N + 1, T> cp,
+                                                 float* __restrict__ out, DimArgs dims, int32_t* __restrict__ bad) {
+  constexpr int V = vpl<T>();
+  constexpr int QL = R / V;
+  constexpr int P = 64 / QL;
+  const int lane = threadIdx.x & 63, slot = lane / QL, qq = lane % QL;
+  const int64_t x0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 64;
+  if (x0 >= q) return;
+  int32_t ik[N];
 #pragma unroll
   for (int n = 0; n < N; ++n) {
-    const int32_t i = vld ? coords[(int64_t)n * q + x] : 0;
-    const floatx4 c = load4(cp.p[n] + (int64_t)i * R + 4 * qq);
-    w *= c;
+    ik[n] = coords[(int64_t)n * q + min(x0 + lane, q - 1)];
+    if constexpr (CHECK) {
+      const bool off = (uint32_t)ik[n] >= (uint32_t)dims.d[n];
+      if (off) bad[n] = 1;
+      ik[n] = off ? 0 : ik[n];
+    }
   }
-  float s = ((w[0] + w[1]) + w[2]) + w[3];
-  s = group_sum<QL>(s);
-  if (vld && qq == 0) out[x] = s;
+  const uint32_t qb = (uint32_t)(16 * qq);
+  static_for<0, QL>([&](auto UU) {
+    constexpr int u = decltype(UU)::value;
+    float w[V];
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+      const int32_t i = QL > 1 ? __shfl(ik[n], u * P + slot) : ik[n];
+      float t[V];
+      load16(reinterpret_cast<const T*>(reinterpret_cast<const char*>(cp.p[n]) +
+                                        ((uint32_t)i * (uint32_t)(R * sizeof(T)) + qb)),
+             t);
+#pragma unroll
+      for (int c = 0; c < V; ++c) w[c] = n == 0 ? t[c] : w[c] * t[c];
+    }
+    float s = w[0];
+#pragma unroll
+    for (int c = 1; c < V; ++c) s += w[c];
+    s = group_sum<QL>(s);
+    const int64_t x = x0 + u * P + slot;
+    if (x < q && qq == 0) out[x] = s;
+  });
 }
 
+__global__ void k_clear(int32_t* __restrict__ p, int n) {
+  if ((int)threadIdx.x < n) p[threadIdx.x] = 0;
+}
 
 hipError_t reduce_partials(const ft_plan* P, const Scratch& S, int nparts, float* Bm, float* Gout, float lr,
                            float lam, float inv, int update, hipStream_t s) {
@@ -889,12 +926,21 @@ hipError_t loss_impl(const ft_plan* P, const ft_params* p, double* dpart, double
 }
 
 template <int N, int R, class T>
-hipError_t predict_impl(const ft_params* p, const int32_t* coords, int64_t q, float* out, hipStream_t s) {
+hipError_t predict_impl(const ft_plan* P, const ft_params* p, const int32_t* coords, int64_t q, float* out,
+                        int32_t* bad, hipStream_t s) {
   CPtrs<N + 1, T> cp{};
-  for (int n = 0; n < N; ++n) cp.p[n] = Store<T>::C(p, n);
-  const int64_t threads = q * (R / 4);
-  const unsigned nb = (unsigned)((threads + 255) / 256);
-  if (nb > 0) hipLaunchKernelGGL((k_predict<N, R, T>), dim3(nb), dim3(256), 0, s, coords, q, cp, out);
+  DimArgs dims{};
+  for (int n = 0; n < N; ++n) {
+    cp.p[n] = Store<T>::C(p, n);
+    dims.d[n] = (int32_t)P->desc.dims[n];
+  }
+  const unsigned nb = (unsigned)((q + 255) / 256);
+  if (bad) {
+    hipLaunchKernelGGL(k_clear, dim3(1), dim3(64), 0, s, bad, N);
+    hipLaunchKernelGGL((k_predict<N, R, T, true>), dim3(nb), dim3(256), 0, s, coords, q, cp, out, dims, bad);
+  } else {
+    hipLaunchKernelGGL((k_predict<N, R, T, false>), dim3(nb), dim3(256), 0, s, coords, q, cp, out, dims, bad);
+  }
   return hipGetLastError();
 }
 
@@ -979,11 +1025,11 @@ hipError_t launch_forward(const ft_plan* P, const ft_params* p, const Scratch&, 
 }
 
 hipError_t launch_predict(const ft_plan* P, const ft_params* p, const int32_t* coords, int64_t q, float* out,
-                          hipStream_t s) {
+                          int32_t* bad, hipStream_t s) {
 #define X(n, j, r)                                                                             \
   case key(n, j, r):                                                                           \
-    return bf16(p) ? predict_impl<n, r, uint16_t>(p, coords, q, out, s)                       \
-                   : predict_impl<n, r, float>(p, coords, q, out, s);
+    return bf16(p) ? predict_impl<n, r, uint16_t>(P, p, coords, q, out, bad, s)               \
+                   : predict_impl<n, r, float>(P, p, coords, q, out, bad, s);
   FT_DISPATCH()
 #undef X
 }
