@@ -580,29 +580,40 @@ __global__ __launch_bounds__(256) void k_core_nc(const Seg* __restrict__ segs, i
   }
 }
 
-// Sum of the workgroup partials in a fixed order, in two stages: first every
-// block of kFold consecutive partials (many workgroups), then the blocks.
-constexpr int kFold = 32;
+// Sum of the workgroup partials in a fixed order, in two stages.  First kFold
+// slices of the partials, each over all of J x R: a workgroup takes 64 entries
+// of one slice, its four wavefronts every fourth partial, so that a slice of
+// 2048 / kFold partials is four chains of independent loads instead of one
+// chain per entry of the whole list (1024 partials of 32 x 32: 31 us -> 5 us).
+// Then the kFold sums, in order.
+constexpr int kFold = 16;
 
 __global__ __launch_bounds__(256) void k_fold_partials(const float* __restrict__ partials, int nparts, int JR,
                                                        float* __restrict__ folded) {
-  const int b0 = blockIdx.x * kFold;
-  const int nb = min(kFold, nparts - b0);
-  for (int e = threadIdx.x; e < JR; e += blockDim.x) {
-    float s = 0.f;
-    for (int b = 0; b < nb; ++b) s += partials[(int64_t)(b0 + b) * JR + e];
-    folded[(int64_t)blockIdx.x * JR + e] = s;
-  }
+  __shared__ float red[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int e = blockIdx.x * 64 + lane;  // JR is a multiple of 64
+  const int per = (nparts + kFold - 1) / kFold;
+  const int b0 = blockIdx.y * per, b1 = min(nparts, b0 + per);
+  float s = 0.f;
+#pragma unroll 8
+  for (int b = b0 + wave; b < b1; b += 4) s += partials[(int64_t)b * JR + e];
+  red[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0) folded[(int64_t)blockIdx.y * JR + e] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
 }
 
 // Final sum; optionally the core step B <- B + lr (G / |Omega| - lam B) (Algorithm 5).
-__global__ __launch_bounds__(256) void k_reduce_update(const float* __restrict__ folded, int nfold, int JR,
-                                                       float* __restrict__ Bm, float* __restrict__ Gout, float lr,
-                                                       float lam, float inv_nnz, int update) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= JR) return;
+__global__ __launch_bounds__(64) void k_reduce_update(const float* __restrict__ folded, int JR,
+                                                      float* __restrict__ Bm, float* __restrict__ Gout, float lr,
+                                                      float lam, float inv_nnz, int update) {
+  const int e = blockIdx.x * 64 + threadIdx.x;
+  float f[kFold];
+#pragma unroll
+  for (int b = 0; b < kFold; ++b) f[b] = folded[(int64_t)b * JR + e];
   float s = 0.f;
-  for (int b = 0; b < nfold; ++b) s += folded[(int64_t)b * JR + e];
+#pragma unroll
+  for (int b = 0; b < kFold; ++b) s += f[b];
   if (Gout) Gout[e] = s;
   if (update) {
     const float b = Bm[e];
@@ -714,49 +725,73 @@ __global__ __launch_bounds__(256) void k_loss(const Seg* __restrict__ segs, int6
   if (threadIdx.x == 0 && dpart) dpart[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-// FP64 sum of squares of a matrix, one partial per workgroup.
-__global__ __launch_bounds__(256) void k_sumsq(const float* __restrict__ X, int64_t n, double* __restrict__ dpart) {
-  __shared__ double red[256];
-  double s = 0.0;
-  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (int64_t)gridDim.x * 256) {
-    const double x = X[k];
-    s += x * x;
+// FP64 sums of squares of every A(n), one launch: workgroup (x, n) adds its
+// share of A(n) in 16-byte loads (four bytes where A(n) starts off a 16-byte
+// boundary), four accumulators per thread.  One launch of 16-byte loads
+// instead of two per mode of four-byte ones: a 1e6 x 32 matrix 190 us -> 30 us.
+struct SumsqArgs {
+  const float* X[FT_MAX_ORDER];
+  int64_t n[FT_MAX_ORDER];
+};
+
+__global__ __launch_bounds__(256) void k_sumsq(SumsqArgs a, double* __restrict__ dpart) {
+  __shared__ double red[4];
+  const float* __restrict__ X = a.X[blockIdx.y];
+  const int64_t n = a.n[blockIdx.y];
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, nt = (int64_t)gridDim.x * 256;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  int64_t tail = 0;
+  if ((reinterpret_cast<uintptr_t>(X) & 15) == 0) {
+    const floatx4* X4 = reinterpret_cast<const floatx4*>(X);
+#pragma unroll 4
+    for (int64_t k = t; k < n / 4; k += nt) {
+      const floatx4 v = X4[k];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) s[c] = fma((double)v[c], (double)v[c], s[c]);
+    }
+    tail = n & ~(int64_t)3;
   }
-  red[threadIdx.x] = s;
+  for (int64_t k = tail + t; k < n; k += nt) s[0] = fma((double)X[k], (double)X[k], s[0]);
+  double v = (s[0] + s[1]) + (s[2] + s[3]);
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) v += __shfl_xor(v, off);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int h = 128; h > 0; h >>= 1) {
-    if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) dpart[blockIdx.x] = red[0];
+  if (threadIdx.x == 0) dpart[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-constexpr int kSumsqBlocks = 256;
+constexpr int kSumsqBlocks = 256;  // workgroups per matrix, at most
 
-// Fixed-order FP64 sums of the partials (strided per thread, then a tree).
+// Fixed-order FP64 sums of the partials and of the (small) B(n), strided per
+// thread, then a tree.
 __global__ __launch_bounds__(256) void k_loss_finish(const double* __restrict__ dpart, int n_sse,
-                                                     const double* __restrict__ rpart, int n_a, int n_b, double nnz,
-                                                     double lam_a, double lam_b, double* __restrict__ out4) {
-  __shared__ double red[3][256];
+                                                     const double* __restrict__ rpart, int n_a, SumsqArgs B, int N,
+                                                     double nnz, double lam_a, double lam_b,
+                                                     double* __restrict__ out4) {
+  __shared__ double red[3][4];
   const int t = threadIdx.x;
-  double sse = 0.0, ra = 0.0, rb = 0.0;
-  for (int k = t; k < n_sse; k += 256) sse += dpart[k];
-  for (int k = t; k < n_a; k += 256) ra += rpart[k];
-  for (int k = t; k < n_b; k += 256) rb += rpart[n_a + k];
-  red[0][t] = sse;
-  red[1][t] = ra;
-  red[2][t] = rb;
-  __syncthreads();
-  for (int h = 128; h > 0; h >>= 1) {
-    if (t < h)
-      for (int c = 0; c < 3; ++c) red[c][t] += red[c][t + h];
-    __syncthreads();
+  double v[3] = {0.0, 0.0, 0.0};
+#pragma unroll 8
+  for (int k = t; k < n_sse; k += 256) v[0] += dpart[k];
+#pragma unroll 4
+  for (int k = t; k < n_a; k += 256) v[1] += rpart[k];
+  for (int m = 0; m < N; ++m)
+#pragma unroll 4
+    for (int k = t; k < (int)B.n[m]; k += 256) v[2] = fma((double)B.X[m][k], (double)B.X[m][k], v[2]);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) v[c] += __shfl_xor(v[c], off);
+    if ((t & 63) == 0) red[c][t >> 6] = v[c];
   }
+  __syncthreads();
   if (t == 0) {
-    out4[0] = red[0][0];
-    out4[1] = nnz > 0 ? sqrt(red[0][0] / nnz) : 0.0;
-    out4[2] = lam_a * red[1][0];
-    out4[3] = lam_b * red[2][0];
+    double f[3];
+    for (int c = 0; c < 3; ++c) f[c] = ((red[c][0] + red[c][1]) + red[c][2]) + red[c][3];
+    out4[0] = f[0];
+    out4[1] = nnz > 0 ? sqrt(f[0] / nnz) : 0.0;
+    out4[2] = lam_a * f[1];
+    out4[3] = lam_b * f[2];
   }
 }
 
@@ -823,11 +858,10 @@ hipError_t reduce_partials(const ft_plan* P, const Scratch& S, int nparts, float
                            float lam, float inv, int update, hipStream_t s) {
   KTimer tm(P, FT_K_REDUCE, s);
   const int JR = P->J * P->R;
-  const int nfold = (nparts + kFold - 1) / kFold;
+  static_assert(kFold <= kPartials / 32 + 1, "the scratch layout holds kPartials / 32 + 1 folded sums");
   float* folded = S.partials + (int64_t)kPartials * JR;
-  if (nfold > 0) hipLaunchKernelGGL(k_fold_partials, dim3(nfold), dim3(256), 0, s, S.partials, nparts, JR, folded);
-  hipLaunchKernelGGL(k_reduce_update, dim3((JR + 255) / 256), dim3(256), 0, s, folded, nfold, JR, Bm, Gout, lr, lam,
-                     inv, update);
+  hipLaunchKernelGGL(k_fold_partials, dim3(JR / 64, kFold), dim3(256), 0, s, S.partials, nparts, JR, folded);
+  hipLaunchKernelGGL(k_reduce_update, dim3(JR / 64), dim3(64), 0, s, folded, JR, Bm, Gout, lr, lam, inv, update);
   return hipGetLastError();
 }
 
@@ -888,9 +922,8 @@ hipError_t segsum_impl(const ft_plan* P, int m, const ft_params* p, float* parti
 template <int N, int J, int R, class T>
 hipError_t loss_impl(const ft_plan* P, const ft_params* p, double* dpart, double lam_a, double lam_b, double* out4,
                      float* xout, hipStream_t s) {
-  // the loss is a sum over all elements: any mode's CSR serves; with run
-  // reuse the plan picks the mode with the longest runs
-  const int lm = P->run_reuse ? P->loss_mode : 0;
+  // the loss is a sum over all elements: any mode's CSR serves (P->loss_mode)
+  const int lm = P->loss_mode;
   const ModeMeta& M = P->meta[lm];
   const ModeDev& D = P->dev[lm];
   const CPtrs<N, T> cp = others<N, T>(p, lm);
@@ -914,14 +947,20 @@ hipError_t loss_impl(const ft_plan* P, const ft_params* p, double* dpart, double
   // the regularisers of Eq. (6) are taken on the FP32 masters
   KTimer tm(P, FT_K_REDUCE, s);
   double* rpart = dpart + kPartials;
-  for (int n = 0; n < N; ++n)
-    hipLaunchKernelGGL(k_sumsq, dim3(kSumsqBlocks), dim3(256), 0, s, p->A[n], P->desc.dims[n] * J,
-                       rpart + n * kSumsqBlocks);
-  for (int n = 0; n < N; ++n)
-    hipLaunchKernelGGL(k_sumsq, dim3(kSumsqBlocks), dim3(256), 0, s, p->B[n], (int64_t)J * R,
-                       rpart + (N + n) * kSumsqBlocks);
-  hipLaunchKernelGGL(k_loss_finish, dim3(1), dim3(256), 0, s, dpart, nb, rpart, N * kSumsqBlocks,
-                     N * kSumsqBlocks, (double)P->nnz, lam_a, lam_b, out4);
+  SumsqArgs a{}, bm{};
+  int64_t most = 0;
+  for (int n = 0; n < N; ++n) {
+    a.X[n] = p->A[n];
+    a.n[n] = P->desc.dims[n] * J;
+    most = std::max(most, a.n[n]);
+    bm.X[n] = p->B[n];
+    bm.n[n] = (int64_t)J * R;
+  }
+  // a thread adds at least 16 values; the grid is the largest matrix's for all
+  const int nx = (int)std::min<int64_t>(kSumsqBlocks, std::max<int64_t>(1, most / (256 * 16)));
+  hipLaunchKernelGGL(k_sumsq, dim3(nx, N), dim3(256), 0, s, a, rpart);
+  hipLaunchKernelGGL(k_loss_finish, dim3(1), dim3(256), 0, s, dpart, nb, rpart, nx * N, bm, N, (double)P->nnz, lam_a,
+                     lam_b, out4);
   return hipGetLastError();
 }
 
