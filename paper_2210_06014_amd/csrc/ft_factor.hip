@@ -715,21 +715,23 @@ __global__ __launch_bounds__(256) void k_factor_compose(const FItem* __restrict_
 
 // The in-place items and the chunk maps of one exact factor pass in one
 // launch.  They are independent (a map starts from the identity, not from
-// its row's head), so the first apply_blocks workgroups take the in-place
-// items, heads of long rows first, and the rest the chunk maps: the long
-// serial heads then start at once and run while the maps keep the SIMDs busy,
-// instead of running on an otherwise idle GPU after them.
+// its row's head).  The first head_blocks workgroups take the heads of the long
+// rows, the next map_blocks the chunk maps, the rest the short rows: the long
+// serial heads start at once and run while the maps keep the SIMDs busy, and
+// the short items fill in where the maps run out.
 template <int N, int J, int R, class T, bool FIB, bool NC = false>
-__global__ __launch_bounds__(256) void k_factor_fused(int64_t apply_blocks, const FItem* __restrict__ apply_items,
-                                                      int64_t n_apply, const FItem* __restrict__ compose_items,
-                                                      int64_t n_compose, FactorArgs<N, J, R, T, FIB, NC> F) {
+__global__ __launch_bounds__(256) void k_factor_fused(int64_t head_blocks, int64_t map_blocks,
+                                                      const FItem* __restrict__ apply_items, int64_t n_apply,
+                                                      const FItem* __restrict__ compose_items, int64_t n_compose,
+                                                      FactorArgs<N, J, R, T, FIB, NC> F) {
   __shared__ WaveLds<J> lds[4];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if ((int64_t)blockIdx.x < apply_blocks) {
-    const int64_t k = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t b = blockIdx.x;
+  if (b < head_blocks || b >= head_blocks + map_blocks) {
+    const int64_t k = (b < head_blocks ? b : b - map_blocks) * 4 + wave;
     if (k < n_apply) factor_item<ITEM_CHAIN>(apply_items[k], F, lds[wave]);
   } else {
-    const int64_t k = ((int64_t)blockIdx.x - apply_blocks) * 4 + wave;
+    const int64_t k = (b - head_blocks) * 4 + wave;
     if (k < n_compose) factor_item<ITEM_MAP>(compose_items[k], F, lds[wave]);
   }
 }
@@ -1079,9 +1081,10 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
   }
   if (M.n_compose > 0 && M.n_apply > 0 && P->fused) {
     KTimer tm(P, FT_K_FACTOR_FUSED, s);
-    const unsigned ab = factor_blocks(M.n_apply);
-    hipLaunchKernelGGL((k_factor_fused<N, J, R, T, FIB, NC>), dim3(ab + factor_blocks(M.n_compose)), dim3(256), 0, s,
-                       (int64_t)ab, D.apply, M.n_apply, D.compose, M.n_compose, F);
+    // the list of in-place items starts with the heads, padded to a multiple of four
+    const unsigned hb = factor_blocks(M.n_heavy), ab = factor_blocks(M.n_apply), mb = factor_blocks(M.n_compose);
+    hipLaunchKernelGGL((k_factor_fused<N, J, R, T, FIB, NC>), dim3(ab + mb), dim3(256), 0, s, (int64_t)hb, (int64_t)mb,
+                       D.apply, M.n_apply, D.compose, M.n_compose, F);
   } else {
     if (M.n_compose > 0) {
       KTimer tm(P, FT_K_FACTOR_COMPOSE, s);
