@@ -22,15 +22,19 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 // block ahead; what stays serial is one product G a_0, a 16 x 16 forward
 // substitution and one product G^T e~.
 //
-// What bounds it: at J = R = 32 the matrix cores (24 MFMA of 32 cycles per
-// block to form G and K, 64 where a chunk map is carried too), at J <= 16 the
-// VALU work of the serial part.  One item per wavefront, because a block's
+// What bounds it: issue.  An FP32 MFMA holds the VALU for its 32 cycles (16 of
+// them and 64 FMAs take the sum of their times, in one wavefront or in four),
+// so a block costs 24 MFMA (G and K at J = R = 32; 64 where a chunk map is
+// carried too) plus the VALU work of the serial part, which dominates at
+// J <= 16.  The bf16 MFMA would run beside the VALU, but it truncates the terms
+// of an instruction to the largest one's 24 bits: G from three bf16 parts per
+// value took a tenth off a launch and doubled the error of A.  One item per wavefront, because a block's
 // MFMA then serves one chain and the chain is 4 times shorter than with an
 // item per 16 lanes.  Against one step per element on 16 lanes (g by row
 // broadcasts), us per launch: Netflix-shaped 8M elements, J = R = 32, modes
-// 1 and 2: 1048 -> 652; order 4 (3M, J = R = 32) 934 -> 468; order 6 (1M, BF16)
-// 157 -> 55; order 8 (1M, J = 8, R = 16) 334 -> 101; Netflix-shaped 5M, J = R =
-// 16: 267 -> 259.
+// 1 and 2: 1048 -> 490; order 4 (3M, J = R = 32) 934 -> 300; order 6 (1M, BF16)
+// 157 -> 50; order 8 (1M, J = 8, R = 16) 334 -> 75; Netflix-shaped 5M, J = R =
+// 16: 267 -> 175.
 //
 // Lane l = 16 g + i of the wavefront holds:
 //   Gu[k]  G[i][jbase(g) + k], k < J / 4   (as the MFMA that forms G leaves it,
@@ -129,6 +133,8 @@ template <int J>
 struct __align__(16) WaveLds {
   float G[16 * Geo<J>::GS];
   float L[16 * Geo<J>::LS];
+  float T[16 * Geo<J>::LS];  // inverse of a map's block
+  float P[8 * 12];
 };
 
 // `v` with the lanes of row g of 16 rotated so that lane i holds the value of
@@ -200,10 +206,10 @@ __device__ __forceinline__ float forward_substitute(float z, const float (&L)[16
   return z;
 }
 
-// y[0..S-1] += (lane S's L[0..S-1]) * y[S]: one step of the rows of
-// (I + gp tril(K, -1))^-1, lane i holding row i
+// y[0..S-1] += (lane S's L[0..S-1]) * y[S]: one step of the rows of the inverse
+// of a unit lower triangular 8 x 8 matrix I - L, lane i holding row i % 8
 template <int S>
-__device__ __forceinline__ void inverse_step(float (&y)[16], const float (&L)[16]) {
+__device__ __forceinline__ void inverse_step(float (&y)[8], const float (&L)[8]) {
 #define FT_INV(n) asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:" #n " row_mask:0xf bank_mask:0xf" : "+v"(y[s]) : "v"(L[s]), "v"(y[S]))
 #pragma unroll
   for (int s = 0; s < S; ++s) {
@@ -214,51 +220,43 @@ __device__ __forceinline__ void inverse_step(float (&y)[16], const float (&L)[16
     if constexpr (S == 5) FT_INV(5);
     if constexpr (S == 6) FT_INV(6);
     if constexpr (S == 7) FT_INV(7);
-    if constexpr (S == 8) FT_INV(8);
-    if constexpr (S == 9) FT_INV(9);
-    if constexpr (S == 10) FT_INV(10);
-    if constexpr (S == 11) FT_INV(11);
-    if constexpr (S == 12) FT_INV(12);
-    if constexpr (S == 13) FT_INV(13);
-    if constexpr (S == 14) FT_INV(14);
-    if constexpr (S == 15) FT_INV(15);
   }
 #undef FT_INV
 }
 
-// This lane's part of B(m) as the left operand of G^T = B W^T: row r of tile
-// jt is factor index jmap(jt, r); the k values of lane (i, g) are the
-// contiguous rank indices KR g + s, so that W comes as contiguous slices.
+// B(m) as the left operand of G^T = B W^T: row r of tile jt is factor index
+// jmap(jt, r); the k values of lane (i, g) are the contiguous rank indices
+// KR g + s, so that W comes as contiguous slices.  form() is the one place
+// where g is formed, so that every caller gets the same bits: lane (i, g) gets
+// G[i][jbase(g) + k], k < J / 4, of the 16 slots whose w it is given.
 template <int J, int R, class T>
-__device__ __forceinline__ void load_b(const T* __restrict__ Bm, int i, int g, float (&b)[Geo<J>::JT][R / 4]) {
-  constexpr int KR = R / 4;
+struct GForm {
+  static constexpr int KR = R / 4;
+  float b[Geo<J>::JT][KR];
+  __device__ __forceinline__ void load(const T* __restrict__ Bm, int i, int g) {
 #pragma unroll
-  for (int jt = 0; jt < Geo<J>::JT; ++jt) {
-    const int j = Geo<J>::jmap(jt, i);
+    for (int jt = 0; jt < Geo<J>::JT; ++jt) {
+      const int j = Geo<J>::jmap(jt, i);
 #pragma unroll
-    for (int k = 0; k < KR; ++k) b[jt][k] = j >= 0 ? to_f(Bm[j * R + KR * g + k]) : 0.f;
+      for (int k = 0; k < KR; ++k) b[jt][k] = j >= 0 ? to_f(Bm[j * R + KR * g + k]) : 0.f;
+    }
   }
-}
-
-// G^T = B W^T of 16 slots: lane (i, g) gets G[i][jbase(g) + k], k < J / 4.
-// The one place where g is formed, so that every caller gets the same bits.
-template <int J, int R>
-__device__ __forceinline__ void form_g(const float (&b)[Geo<J>::JT][R / 4], const float (&w)[R / 4],
-                                       float (&G)[Geo<J>::NG]) {
-  constexpr int VJ = Geo<J>::VJ;
-  floatx4 acc[Geo<J>::JT];
+  __device__ __forceinline__ void form(const float (&w)[KR], float (&G)[Geo<J>::NG]) const {
+    constexpr int VJ = Geo<J>::VJ;
+    floatx4 acc[Geo<J>::JT];
 #pragma unroll
-  for (int jt = 0; jt < Geo<J>::JT; ++jt) acc[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int jt = 0; jt < Geo<J>::JT; ++jt) acc[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int k = 0; k < R / 4; ++k)
+    for (int k = 0; k < KR; ++k)
+#pragma unroll
+      for (int jt = 0; jt < Geo<J>::JT; ++jt)
+        acc[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[jt][k], w[k], acc[jt], 0, 0, 0);
 #pragma unroll
     for (int jt = 0; jt < Geo<J>::JT; ++jt)
-      acc[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[jt][k], w[k], acc[jt], 0, 0, 0);
 #pragma unroll
-  for (int jt = 0; jt < Geo<J>::JT; ++jt)
-#pragma unroll
-    for (int v = 0; v < VJ; ++v) G[VJ * jt + v] = acc[jt][v];
-}
+      for (int v = 0; v < VJ; ++v) G[VJ * jt + v] = acc[jt][v];
+  }
+};
 
 // Source of the blocks' G: the C rows of an element's other modes (w, then
 // B(m) w), its fiber's g, or (NC, order 3 and J = R = 16) C rows formed from
@@ -284,14 +282,14 @@ struct Source {
   const int32_t* fid;
   const float* gfib;
   NoC<N> nc;
-  float b[Geo<J>::JT][KR];
+  GForm<J, R, T> gf;
   float bn[NC ? N - 1 : 1][4];  // B(n) of the other modes as left operands (NC)
   int i, g;
 
   __device__ __forceinline__ void init(const T* Bm, int lane) {
     i = lane & 15;
     g = lane >> 4;
-    if constexpr (!FIB) load_b<J, R, T>(Bm, i, g, b);
+    if constexpr (!FIB) gf.load(Bm, i, g);
     if constexpr (NC)
 #pragma unroll
       for (int k = 0; k < N - 1; ++k)
@@ -355,7 +353,7 @@ struct Source {
       }
 #pragma unroll
       for (int s = 0; s < KR; ++s) w[s] = ok ? w[s] : 0.f;
-      form_g<J, R>(b, w, G);
+      gf.form(w, G);
     }
   }
 };
@@ -493,8 +491,57 @@ __device__ __forceinline__ void step_block(const Block<J, MAP>& blk, double gp, 
   a = rho_nb * fma(gp, (double)d, a);
 }
 
-// by value: a conditional of two array elements would put the array in memory
-__device__ __forceinline__ float pick(int c, float a, float b) { return c ? a : b; }
+// T = (I + gp tril(K, -1))^-1 of a block, as the left operand of T Y: lane
+// (i, g) gets T[i][4 g + v].  lds.L holds -gp tril(K, -1).  The two diagonal
+// 8 x 8 blocks are inverted by substitution, lanes 0-31 the first and lanes
+// 32-63 the second, so that one row broadcast serves both (28 FMAs; the whole
+// 16 x 16 matrix by substitution takes 120); then T21 = T22 (-L21) T11, an
+// entry per lane, through LDS.  T12 = 0 is stored once per item.
+template <int J>
+__device__ __forceinline__ void block_inverse(WaveLds<J>& lds, int lane, float (&Ti)[4]) {
+  constexpr int LS = Geo<J>::LS;
+  const int i = lane & 15, g = lane >> 4, h8 = 8 * (lane >> 5), r8 = i & 7;
+  auto row8 = [](const float* p, float (&o)[8]) {
+    const floatx4 u = *reinterpret_cast<const floatx4*>(p), v = *reinterpret_cast<const floatx4*>(p + 4);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      o[k] = u[k];
+      o[4 + k] = v[k];
+    }
+  };
+  float y[8], L[8];
+  row8(lds.L + (h8 + r8) * LS + h8, L);
+#pragma unroll
+  for (int s = 0; s < 8; ++s) y[s] = s == r8 ? 1.f : 0.f;
+  asm("s_nop 4" : "+v"(y[7]));
+  inverse_step<7>(y, L);
+  inverse_step<6>(y, L);
+  inverse_step<5>(y, L);
+  inverse_step<4>(y, L);
+  inverse_step<3>(y, L);
+  inverse_step<2>(y, L);
+  inverse_step<1>(y, L);
+  float* trow = lds.T + (h8 + r8) * LS + h8;
+  *reinterpret_cast<floatx4*>(trow) = floatx4{y[0], y[1], y[2], y[3]};
+  *reinterpret_cast<floatx4*>(trow + 4) = floatx4{y[4], y[5], y[6], y[7]};
+  wave_lds_fence();
+  const int k = lane >> 3, s = lane & 7;
+  float q[8], acc = 0.f;
+  row8(lds.L + (8 + k) * LS, q);
+#pragma unroll
+  for (int u = 0; u < 8; ++u) acc = fmaf(q[u], lds.T[u * LS + s], acc);
+  lds.P[k * 12 + s] = acc;
+  wave_lds_fence();
+  acc = 0.f;
+  row8(lds.T + (8 + k) * LS + 8, q);
+#pragma unroll
+  for (int u = 0; u < 8; ++u) acc = fmaf(q[u], lds.P[u * 12 + s], acc);
+  lds.T[(8 + k) * LS + s] = acc;
+  wave_lds_fence();
+  const floatx4 t = *reinterpret_cast<const floatx4*>(lds.T + i * LS + 4 * g);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) Ti[v] = t[v];
+}
 
 // The chunk map's block, a -> rho^T (I + Nm) a + v with Nm = prod (I - gp g g^T) - I:
 //     Nm <- Nm - gp G^T (I + gp tril(K, -1))^-1 (G + G Nm).
@@ -502,36 +549,11 @@ __device__ __forceinline__ float pick(int c, float a, float b) { return c ? a : 
 // tile jt, column i of tile ct.  (Nm is M - I so that the small updates are
 // not absorbed.)
 template <int J>
-__device__ __forceinline__ void map_block(const Block<J, true>& blk, float gp, int i, int g,
+__device__ __forceinline__ void map_block(const Block<J, true>& blk, WaveLds<J>& lds, float gp, int lane,
                                           floatx4 (&Nm)[Geo<J>::JT][Geo<J>::JT]) {
   using Q = Geo<J>;
-  // row i of the inverse, every row of 16 lanes alike
-  float y[16];
-#pragma unroll
-  for (int s = 0; s < 16; ++s) y[s] = s == i ? 1.f : 0.f;
-  asm("s_nop 4" : "+v"(y[15]));
-  inverse_step<15>(y, blk.L);
-  inverse_step<14>(y, blk.L);
-  inverse_step<13>(y, blk.L);
-  inverse_step<12>(y, blk.L);
-  inverse_step<11>(y, blk.L);
-  inverse_step<10>(y, blk.L);
-  inverse_step<9>(y, blk.L);
-  inverse_step<8>(y, blk.L);
-  inverse_step<7>(y, blk.L);
-  inverse_step<6>(y, blk.L);
-  inverse_step<5>(y, blk.L);
-  inverse_step<4>(y, blk.L);
-  inverse_step<3>(y, blk.L);
-  inverse_step<2>(y, blk.L);
-  inverse_step<1>(y, blk.L);
-  // as the left operand: lane (i, g) supplies columns 4 g + v
   float Ti[4];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const float lo = pick(g & 1, y[4 + v], y[v]), hi = pick(g & 1, y[12 + v], y[8 + v]);
-    Ti[v] = pick(g & 2, hi, lo);
-  }
+  block_inverse<J>(lds, lane, Ti);
 #pragma unroll
   for (int ct = 0; ct < Q::JT; ++ct) {
     floatx4 Y = {blk.Gc[ct][0], blk.Gc[ct][1], blk.Gc[ct][2], blk.Gc[ct][3]};
@@ -611,11 +633,13 @@ __device__ __forceinline__ void factor_item(const FItem& it, const FactorArgs<N,
   double a = 0.0;
   if constexpr (!MAP) a = (double)F.Am[(int64_t)it.row * J + jl];
   floatx4 Nm[Q::JT][Q::JT];
-  if constexpr (MAP)
+  if constexpr (MAP) {
 #pragma unroll
     for (int jt = 0; jt < Q::JT; ++jt)
 #pragma unroll
       for (int ct = 0; ct < Q::JT; ++ct) Nm[jt][ct] = floatx4{0.f, 0.f, 0.f, 0.f};
+    lds.T[(lane >> 3) * Q::LS + 8 + (lane & 7)] = 0.f;  // T12
+  }
   float gg = 0.f;  // sum of ||g||^2 (RELAXED), this lane's part
   // Pipeline: the gathers of block b + 1 and the indices of block b + 2 are in
   // flight while block b is formed, and block b is formed (MFMA, LDS) beside
@@ -646,17 +670,27 @@ __device__ __forceinline__ void factor_item(const FItem& it, const FactorArgs<N,
     // leaves registers for three wavefronts per SIMD)
     for (;;) {
       step_block<J, MAP>(cur, F.gp, F.pw.p[min<int64_t>(bs, pe - p)], a);
-      map_block<J>(cur, gpf, i, g, Nm);
+      map_block<J>(cur, lds, gpf, lane, Nm);
       p += bs;
       if (p >= pe) break;
       form(p, cur);
     }
   } else {
-    for (; p + bs < pe; p += bs) {
-      Block<J, MAP> nxt;
+    // (two blocks in turn: copying one to the other is 30 instructions)
+    const double rb = F.pw.p[bs];
+    Block<J, MAP> nxt;
+    while (p + 2 * bs < pe) {
       form(p + bs, nxt);
-      step_block<J, MAP>(cur, F.gp, F.pw.p[bs], a);
+      step_block<J, MAP>(cur, F.gp, rb, a);
+      form(p + 2 * bs, cur);
+      step_block<J, MAP>(nxt, F.gp, rb, a);
+      p += 2 * bs;
+    }
+    if (p + bs < pe) {
+      form(p + bs, nxt);
+      step_block<J, MAP>(cur, F.gp, rb, a);
       cur = nxt;
+      p += bs;
     }
     step_block<J, MAP>(cur, F.gp, F.pw.p[pe - p], a);
   }
@@ -705,7 +739,7 @@ __global__ __launch_bounds__(256) void k_factor_apply(const FItem* __restrict__ 
 }
 
 template <int N, int J, int R, class T, bool FIB, bool NC = false>
-__global__ __launch_bounds__(256) void k_factor_compose(const FItem* __restrict__ items, int64_t n_items,
+__global__ __launch_bounds__(256, 3) void k_factor_compose(const FItem* __restrict__ items, int64_t n_items,
                                                         FactorArgs<N, J, R, T, FIB, NC> F) {
   __shared__ WaveLds<J> lds[4];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -720,7 +754,7 @@ __global__ __launch_bounds__(256) void k_factor_compose(const FItem* __restrict_
 // serial heads start at once and run while the maps keep the SIMDs busy, and
 // the short items fill in where the maps run out.
 template <int N, int J, int R, class T, bool FIB, bool NC = false>
-__global__ __launch_bounds__(256) void k_factor_fused(int64_t head_blocks, int64_t map_blocks,
+__global__ __launch_bounds__(256, 3) void k_factor_fused(int64_t head_blocks, int64_t map_blocks,
                                                       const FItem* __restrict__ apply_items, int64_t n_apply,
                                                       const FItem* __restrict__ compose_items, int64_t n_compose,
                                                       FactorArgs<N, J, R, T, FIB, NC> F) {
