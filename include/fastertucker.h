@@ -112,9 +112,8 @@ typedef struct {
                                    launch (from the row lengths and whether g is shared per fiber)
                                    expects to end within the launch.  ft_plan_mode_info reports the
                                    value each mode uses */
-  int32_t fanin;                /* chunk maps folded per combine step (0 or above the maximum: 16 for
-                                   J <= 16, 8 above); a row with at most fanin maps has them applied in
-                                   sequence to its head's result */
+  int32_t fanin;                /* chunk maps folded per combine step (0 or above the maximum: 16); a row with
+                                   at most fanin maps has them applied in sequence to its head's result */
   int32_t flags;                /* FT_KEEP_HOST | FT_WITH_PERM | FT_NO_FIBER_SHARE | FT_NO_C_CACHE | FT_RELAXED |
                                    FT_SPLIT_FACTOR | FT_RUN_REUSE */
 } ft_desc;

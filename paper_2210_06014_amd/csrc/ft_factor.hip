@@ -770,137 +770,157 @@ __global__ __launch_bounds__(256, 3) void k_factor_fused(int64_t head_blocks, in
   }
 }
 
-// Fold `count` consecutive maps (earliest first) into one, as a binary tree in
-// LDS (fixed bracketing: pairs (0,1), (2,3), ... then (0,2), ... so that a
-// later map is always applied after an earlier one):
+// Fold `count` consecutive maps (earliest first) into one, in order:
 //   (s2, N2, v2) o (s1, N1, v1) = (s1 s2, N1 + N2 + N2 N1, s2 (v1 + N2 v1) + v2),
 // with s = rho^length kept in FP64.  Only rows with more maps than the last
 // fold takes in sequence (below) pass through here.
-template <int J>
-constexpr int combine_fanin() {
-  return J <= 16 ? 16 : 8;  // maps held in LDS by one workgroup
-}
+//
+// A wavefront per fold and 16 columns: the columns of the running map are
+// independent of each other, stay in MFMA results and are the right operand of
+// the next product as they are; each later map is read as the left operand and
+// once in the layout of the results, one map ahead.  What bounds it is the
+// latency of this chain (16 MFMA of 32 cycles per map at J = 32) and of the
+// launches, so a row has few levels: 16 maps per fold, and one launch for all
+// last folds.  Against a tree in LDS by a workgroup and a last fold per level,
+// us per pass: J = 32 (rows of up to 900 maps) 84 -> 31, J = 16 38 -> 20.
+constexpr int kMaxFanin = 16;
 
 template <int J>
-__global__ __launch_bounds__(256) void k_combine(const CItem* __restrict__ items, float* __restrict__ maps,
-                                                 double* __restrict__ map_scale) {
-  constexpr int MS = J * J + J;
-  constexpr int F = combine_fanin<J>();
-  // a thread forms a T x T tile of a product: 4 x 4 at J = 32, 2 x 2 at
-  // J = 16 (fan-in 16: 512 tiles for the 256 threads), one entry at J = 8
-  constexpr int T = J >= 32 ? 4 : J >= 16 ? 2 : 1;
-  constexpr int T4 = J / T;                            // output tiles per side of a product
-  constexpr int TMAX = (F / 2 * T4 * T4 + 255) / 256;  // output tiles per thread at the widest level
-  constexpr int VMAX = (F / 2 * J + 255) / 256;        // vector entries per thread at the widest level
-  static_assert(J % 4 == 0 && MS % 4 == 0, "16-byte LDS reads of map columns");
-  __shared__ __align__(16) float buf[F * MS];
-  __shared__ double sc[F];
-  const CItem it = items[blockIdx.x];
-  const int t = threadIdx.x;
-  const int count = it.count;
-  {
-    const float* src = maps + it.in_off * MS;
-    for (int k = t; k < count * MS; k += 256) buf[k] = src[k];
-    if (t < count) sc[t] = map_scale[it.in_off + t];
-  }
-  __syncthreads();
-  for (int stride = 1; stride < count; stride *= 2) {
-    const int pairs = (count - stride + 2 * stride - 1) / (2 * stride);  // a = 2 k stride, b = a + stride < count
-    // (N_b N_a)(i, j) = sum_q N_b(i, q) N_a(q, j), q in order, for a T x T
-    // tile of (i, j) per thread.  Columns are contiguous (entry (i, j) at
-    // j J + i), so each step of four q reads T columns of N_a (16 bytes
-    // each) and four column pieces of N_b (4 T bytes each) for 4 T^2 FMAs.
-    float res[TMAX][T][T];
+struct MapRegs {
+  static constexpr int JT = (J + 15) / 16;
+  floatx4 d[JT];       // rows 16 jt + 4 g + v, column 16 ct + i (result layout)
+  float a[JT][JT][4];  // row 16 it + i, columns 16 jt + 4 g + v (left operand)
+  float v[JT];         // vector, entry 16 it + i, every row of 16 lanes alike
+  double s;
+  __device__ __forceinline__ void load(const float* __restrict__ maps, const double* __restrict__ scale, int64_t slot,
+                                       int ct, int i, int g, bool left) {
+    const float* m = maps + slot * (J * J + J);
+    const bool ok = J >= 16 || (i < J && 4 * g < J);  // J = 8: a quarter of the tile
+    const int ic = J >= 16 ? i : i % J, gc = J >= 16 ? g : g % 2;
 #pragma unroll
-    for (int u = 0; u < TMAX; ++u) {
-      const int e = t + 256 * u;
-      if (e < pairs * T4 * T4) {
-        const int pr = e / (T4 * T4), rem = e % (T4 * T4);
-        const int i0 = T * (rem % T4), j0 = T * (rem / T4);
-        const float* Na = buf + (2 * pr * stride) * MS;
-        const float* Nb = Na + stride * MS;
-        if constexpr (T == 1) {
-          float acc = 0.f;
+    for (int jt = 0; jt < JT; ++jt) {
+      const floatx4 x = *reinterpret_cast<const floatx4*>(m + (16 * ct + ic) * J + 16 * jt + 4 * gc);
 #pragma unroll
-          for (int q = 0; q < J; ++q) acc = fmaf(Nb[q * J + i0], Na[j0 * J + q], acc);
-          const int ij = j0 * J + i0;
-          res[u][0][0] = (Na[ij] + Nb[ij]) + acc;
-        } else {
-          using Vec = typename std::conditional<T == 4, floatx4, floatx2>::type;
-          float acc[T][T];  // acc[c][r]: entry (i0 + r, j0 + c)
+      for (int u = 0; u < 4; ++u) d[jt][u] = ok ? x[u] : 0.f;
+    }
+    if (left)
 #pragma unroll
-          for (int c = 0; c < T; ++c)
+      for (int it = 0; it < JT; ++it)
 #pragma unroll
-            for (int r = 0; r < T; ++r) acc[c][r] = 0.f;
+        for (int jt = 0; jt < JT; ++jt)
 #pragma unroll
-          for (int q0 = 0; q0 < J; q0 += 4) {
-            floatx4 na[T];
-            Vec nb[4];
-#pragma unroll
-            for (int c = 0; c < T; ++c) na[c] = *reinterpret_cast<const floatx4*>(Na + (j0 + c) * J + q0);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) nb[k] = *reinterpret_cast<const Vec*>(Nb + (q0 + k) * J + i0);
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-#pragma unroll
-              for (int c = 0; c < T; ++c)
-#pragma unroll
-                for (int r = 0; r < T; ++r) acc[c][r] = fmaf(nb[k][r], na[c][k], acc[c][r]);
+          for (int u = 0; u < 4; ++u) {
+            const float x = m[(16 * jt + 4 * gc + u) * J + 16 * it + ic];
+            a[it][jt][u] = ok ? x : 0.f;
           }
 #pragma unroll
-          for (int c = 0; c < T; ++c)
-#pragma unroll
-            for (int r = 0; r < T; ++r) {
-              const int ij = (j0 + c) * J + i0 + r;
-              res[u][c][r] = (Na[ij] + Nb[ij]) + acc[c][r];
-            }
-        }
-      }
-    }
-    float vres[VMAX];
-    double sres[VMAX];
-#pragma unroll
-    for (int u = 0; u < VMAX; ++u) {
-      const int e = t + 256 * u;
-      if (e < pairs * J) {
-        const int pr = e / J, i = e % J;
-        const float* Na = buf + (2 * pr * stride) * MS;
-        const float* Nb = Na + stride * MS;
-        float acc = 0.f;
-#pragma unroll
-        for (int q = 0; q < J; ++q) acc = fmaf(Nb[q * J + i], Na[J * J + q], acc);
-        const double sb = sc[2 * pr * stride + stride];
-        vres[u] = (float)(sb * ((double)Na[J * J + i] + (double)acc)) + Nb[J * J + i];
-        sres[u] = sc[2 * pr * stride] * sb;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < TMAX; ++u) {
-      const int e = t + 256 * u;
-      if (e < pairs * T4 * T4) {
-        const int pr = e / (T4 * T4), rem = e % (T4 * T4);
-        const int i0 = T * (rem % T4), j0 = T * (rem / T4);
-#pragma unroll
-        for (int c = 0; c < T; ++c)
-#pragma unroll
-          for (int r = 0; r < T; ++r) buf[(2 * pr * stride) * MS + (j0 + c) * J + i0 + r] = res[u][c][r];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < VMAX; ++u) {
-      const int e = t + 256 * u;
-      if (e < pairs * J) {
-        const int pr = e / J, i = e % J;
-        buf[(2 * pr * stride) * MS + J * J + i] = vres[u];
-        if (i == 0) sc[2 * pr * stride] = sres[u];
-      }
-    }
-    __syncthreads();
+    for (int it = 0; it < JT; ++it) v[it] = m[J * J + 16 * it + ic];
+    s = scale[slot];
   }
-  float* dst = maps + it.out_off * MS;
-  for (int k = t; k < MS; k += 256) dst[k] = buf[k];
-  if (t == 0) map_scale[it.out_off] = sc[0];
+};
+
+template <int J>
+__global__ __launch_bounds__(256) void k_combine(const CItem* __restrict__ items, int64_t n_items,
+                                                 float* __restrict__ maps, double* __restrict__ map_scale) {
+  constexpr int JT = MapRegs<J>::JT;
+  const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+  const int64_t k = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (k >= n_items * JT) return;
+  const CItem it = items[k / JT];
+  const int ct = (int)(k % JT);
+  MapRegs<J> P, cur, nxt;
+  P.load(maps, map_scale, it.in_off, ct, i, g, false);
+  if (it.count > 1) nxt.load(maps, map_scale, it.in_off + 1, ct, i, g, true);
+  for (int c = 1; c < it.count; ++c) {
+    cur = nxt;
+    if (c + 1 < it.count) nxt.load(maps, map_scale, it.in_off + c + 1, ct, i, g, true);
+    floatx4 acc[JT];
+#pragma unroll
+    for (int rt = 0; rt < JT; ++rt) acc[rt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int rt = 0; rt < JT; ++rt)
+          acc[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.a[rt][jt][u], P.d[jt][u], acc[rt], 0, 0, 0);
+    if (ct == 0) {
+      // N2 v1: lane (i, g) adds its four columns per tile, then the four rows of lanes
+      float w[JT][4];
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) w[jt][u] = __shfl(P.v[jt], 4 * g + u);
+#pragma unroll
+      for (int rt = 0; rt < JT; ++rt) {
+        float z = 0.f;
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) z = fmaf(cur.a[rt][jt][u], w[jt][u], z);
+        z = sum_rows(sum_halves(z));
+        P.v[rt] = (float)(cur.s * ((double)P.v[rt] + (double)z)) + cur.v[rt];
+      }
+    }
+#pragma unroll
+    for (int rt = 0; rt < JT; ++rt) P.d[rt] = (P.d[rt] + cur.d[rt]) + acc[rt];
+    P.s *= cur.s;
+  }
+  float* dst = maps + it.out_off * (J * J + J);
+  if (J >= 16 || (i < J && 4 * g < J)) {
+#pragma unroll
+    for (int jt = 0; jt < JT; ++jt)
+      *reinterpret_cast<floatx4*>(dst + (16 * ct + i) * J + 16 * jt + 4 * g) = P.d[jt];
+    if (ct == 0 && g == 0)
+#pragma unroll
+      for (int rt = 0; rt < JT; ++rt) dst[J * J + 16 * rt + i] = P.v[rt];
+  }
+  if (ct == 0 && lane == 0) map_scale[it.out_off] = P.s;
+}
+
+// The last fold at J = 32, a wavefront per row: lane (i, g) takes row
+// 16 (g % 2) + i of a map and the 16 columns from 16 (g / 2) on, which the
+// state is kept spread for.  16 loads and FMAs per lane and map where a
+// 16-lane group per row takes 64 (16 maps: 16 us -> 8 us).
+__global__ __launch_bounds__(256) void k_combine_final32(const CItem* __restrict__ items, int64_t n_items,
+                                                         const float* __restrict__ maps,
+                                                         const double* __restrict__ map_scale,
+                                                         const float* __restrict__ hvec, float* __restrict__ Am) {
+  constexpr int J = 32, D = 4;  // maps in flight
+  const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+  const int64_t k = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (k >= n_items) return;
+  const CItem it = items[k];
+  const int row = 16 * (g & 1) + i;
+  double a = (double)hvec[(int64_t)it.heavy * J + row];
+  float N[D][16], v[D];
+  double s[D];
+  auto load = [&](int c, float (&n)[16], float& vv, double& sc) {
+    const int64_t slot = it.in_off + min(c, it.count - 1);
+    const float* m = maps + slot * (J * J + J);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) n[q] = m[(16 * (g >> 1) + q) * J + row];
+    vv = m[J * J + row];
+    sc = map_scale[slot];
+  };
+  static_for<0, D>([&](auto S) { load(decltype(S)::value, N[decltype(S)::value], v[decltype(S)::value], s[decltype(S)::value]); });
+  for (int c0 = 0; c0 < it.count; c0 += D) {
+    static_for<0, D>([&](auto S) {
+      constexpr int d = decltype(S)::value;
+      if (c0 + d < it.count) {
+        const uint32_t af = __float_as_uint((float)a);
+        const auto h = __builtin_amdgcn_permlane16_swap(af, af, false, false);  // every row: a_0..15, a_16..31
+        const float as = __uint_as_float(g < 2 ? h[0] : h[1]);
+        float z = bsum<8>(as, N[d]);
+        z += bsum<8>(__builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__float_as_int(as), 0x128, 0xf, 0xf, true)),
+                     N[d] + 8);
+        z = sum_halves(z);
+        a = s[d] * (a + (double)z) + (double)v[d];
+        load(c0 + d + D, N[d], v[d], s[d]);
+      }
+    });
+  }
+  if (g < 2) Am[(int64_t)it.row * J + row] = (float)a;
 }
 
 // Last fold of a heavy row: its remaining maps, earliest first, applied to
@@ -916,38 +936,29 @@ __global__ __launch_bounds__(256) void k_combine_final(const CItem* __restrict__
                                                        const float* __restrict__ maps,
                                                        const double* __restrict__ map_scale,
                                                        const float* __restrict__ hvec, float* __restrict__ Am) {
-  constexpr int E = J >= 16 ? J / 16 : 1;
-  constexpr int K = J >= 16 ? 16 : J;
+  static_assert(J <= 16, "J = 32 has a wavefront per row");
   constexpr int MS = J * J + J;
-  constexpr int D = J >= 32 ? 2 : 4;
+  constexpr int D = 4;
   const int l = threadIdx.x & 15;
   const int64_t gid = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
   CItem it{0, 0, 0, 0, 0, 0};
   if (gid < n_items) it = items[gid];
-  double a[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const int j = l + 16 * e;
-    a[e] = (it.count > 0 && j < J) ? (double)hvec[(int64_t)it.heavy * J + j] : 0.0;
-  }
+  double a = (it.count > 0 && l < J) ? (double)hvec[(int64_t)it.heavy * J + l] : 0.0;
   int maxc = it.count;
   maxc = max(maxc, __shfl_xor(maxc, 16));
   maxc = max(maxc, __shfl_xor(maxc, 32));
-  // row i = l + 16 e of map k (entry (i, q) at q J + i); lanes past J (J = 8)
-  // read row J - 1 and discard it.  Past the row's count: its last map.
-  auto load = [&](int k, float (&Nr)[E][J], float (&v)[E], double& sc) {
+  // row l of map k (entry (l, q) at q J + l); lanes past J (J = 8) read row
+  // J - 1 and discard it.  Past the row's count: its last map.
+  auto load = [&](int k, float (&Nr)[J], float& v, double& sc) {
     const int64_t slot = it.in_off + min(k, max(it.count - 1, 0));
     const float* mp = maps + slot * MS;
+    const int i = min(l, J - 1);
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int i = min(l + 16 * e, J - 1);
-#pragma unroll
-      for (int q = 0; q < J; ++q) Nr[e][q] = mp[q * J + i];
-      v[e] = mp[J * J + i];
-    }
+    for (int q = 0; q < J; ++q) Nr[q] = mp[q * J + i];
+    v = mp[J * J + i];
     sc = map_scale[slot];
   };
-  float Nq[D][E][J], vq[D][E];
+  float Nq[D][J], vq[D];
   double sq[D];
   static_for<0, D>([&](auto S) { load(decltype(S)::value, Nq[decltype(S)::value], vq[decltype(S)::value],
                                       sq[decltype(S)::value]); });
@@ -956,31 +967,14 @@ __global__ __launch_bounds__(256) void k_combine_final(const CItem* __restrict__
       constexpr int d = decltype(S)::value;
       const int k = k0 + d;
       if (k < maxc) {
-        float af[E];
-#pragma unroll
-        for (int e = 0; e < E; ++e) af[e] = (float)a[e];
-        float acc[E];
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          acc[e] = 0.f;
-#pragma unroll
-          for (int e2 = 0; e2 < E; ++e2) dot_bcast<K>(acc[e], af[e2], &Nq[d][e][16 * e2]);
-        }
-        if (k < it.count) {
-#pragma unroll
-          for (int e = 0; e < E; ++e) a[e] = sq[d] * (a[e] + (double)acc[e]) + (double)vq[d][e];
-        }
+        float acc = 0.f;
+        dot_bcast<J>(acc, (float)a, Nq[d]);
+        if (k < it.count) a = sq[d] * (a + (double)acc) + (double)vq[d];
         load(k + D, Nq[d], vq[d], sq[d]);
       }
     });
   }
-  if (it.count > 0) {
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int j = l + 16 * e;
-      if (j < J) Am[(int64_t)it.row * J + j] = (float)a[e];
-    }
-  }
+  if (it.count > 0 && l < J) Am[(int64_t)it.row * J + l] = (float)a;
 }
 
 // FT_RELAXED merge of a long row's chunk increments, in two fixed levels so
@@ -1135,11 +1129,17 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
     KTimer tm(P, FT_K_COMBINE, s);
     const int64_t nc = M.level_ncomp[L], nf = M.level_len[L] - nc;
     if (nc > 0)
-      hipLaunchKernelGGL((k_combine<J>), dim3((unsigned)nc), dim3(256), 0, s, D.levels + M.level_off[L], S.maps,
-                         S.map_scale);
-    if (nf > 0)
-      hipLaunchKernelGGL((k_combine_final<J>), dim3((unsigned)((nf + 15) / 16)), dim3(256), 0, s,
-                         D.levels + M.level_off[L] + nc, nf, S.maps, S.map_scale, S.hvec, p->A[m]);
+      hipLaunchKernelGGL((k_combine<J>), dim3((unsigned)((nc * MapRegs<J>::JT + 3) / 4)), dim3(256), 0, s,
+                         D.levels + M.level_off[L], nc, S.maps, S.map_scale);
+    if (nf > 0) {
+      const CItem* last = D.levels + M.level_off[L] + nc;
+      if constexpr (J == 32)
+        hipLaunchKernelGGL(k_combine_final32, dim3((unsigned)((nf + 3) / 4)), dim3(256), 0, s, last, nf, S.maps,
+                           S.map_scale, S.hvec, p->A[m]);
+      else
+        hipLaunchKernelGGL((k_combine_final<J>), dim3((unsigned)((nf + 15) / 16)), dim3(256), 0, s, last, nf, S.maps,
+                           S.map_scale, S.hvec, p->A[m]);
+    }
   }
   return hipGetLastError();
 }
@@ -1159,7 +1159,7 @@ hipError_t factor_impl(const ft_plan* P, int m, const ft_params* p, const Scratc
 
 }  // namespace
 
-int max_fanin(int J) { return J <= 8 ? combine_fanin<8>() : J <= 16 ? combine_fanin<16>() : combine_fanin<32>(); }
+int max_fanin() { return kMaxFanin; }
 
 hipError_t launch_factor(const ft_plan* P, int m, const ft_params* p, const Scratch& S, double lr, double lam,
                          hipStream_t s) {

@@ -135,8 +135,8 @@ struct ModeMeta {
   int64_t n_maps = 0;     // COMPOSE items (unpadded)
   std::vector<int64_t> level_off;  // offset of each level in the device array
   std::vector<int64_t> level_len;
-  std::vector<int64_t> level_ncomp;  // folds at the head of each level (final items follow)
-  int64_t n_level_out0 = 0;        // outputs of level 0 (ping-pong buffer size)
+  std::vector<int64_t> level_ncomp;  // folds of each level (0: the last level, whose items are final)
+  int64_t n_fold_out = 0;          // map slots that the folds write, after those of the chunks
   int64_t n_segs = 0;
   int64_t n_relax_groups = 0;  // FT_RELAXED level-1 items
   int64_t n_relax = 0;         // FT_RELAXED level-2 items (heavy rows)
@@ -254,5 +254,5 @@ hipError_t launch_forward(const ft_plan* P, const ft_params* p, const Scratch& S
 hipError_t launch_grad(const ft_plan* P, const ft_params* p, const Scratch& S, const float* upstream,
                        float* const* gA, float* const* gB, hipStream_t s);
 bool supported(int N, int J, int R);
-int max_fanin(int J);  // largest combine fan-in the kernels hold in LDS
+int max_fanin();  // default and largest number of maps per fold
 }  // namespace ft

@@ -313,44 +313,43 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
   // combine levels: a heavy row whose maps number at most fanin has them
   // applied in sequence to its head vector (a final item); a longer row first
   // has groups of `fanin` consecutive maps folded into one, level by level.
-  // Each level lists its folds first, then its final items by descending map
-  // count (similar counts share a wavefront).
-  const int64_t fan = P->fanin, fin = P->fanin;
-  std::vector<int64_t> cur_off(heavy_base), cur_n(heavy_nmaps);
-  int64_t region_base[2] = {0, n_maps};
-  int level = 0;
-  int64_t out0 = 0;
+  // Every fold writes a slot of its own, so the final items of all rows make
+  // one last level, by descending map count (similar counts share a wavefront).
+  const int64_t fan = P->fanin;
   std::vector<int64_t> active;
+  std::vector<CItem> finals;
+  int64_t n_out = 0;  // slots written by folds so far
   for (int64_t h = 0; h < n_heavy; ++h) active.push_back(h);
+  std::vector<int64_t> cur_off(heavy_base), cur_n(heavy_nmaps);
   while (!active.empty()) {
-    std::vector<CItem> items, finals;
+    std::vector<CItem> items;
     std::vector<int64_t> next;
-    int64_t out_next = 0;
-    int dst = (level + 1) & 1;
     for (int64_t h : active) {
-      int64_t n = cur_n[h], off = cur_off[h];
-      if (n <= fin) {
+      const int64_t n = cur_n[h], off = cur_off[h];
+      if (n <= fan) {
         finals.push_back(CItem{off, -1, (int32_t)n, (int32_t)heavy_rows[h], (int32_t)h, 0});
         continue;
       }
-      int64_t groups = (n + fan - 1) / fan;
-      int64_t base = region_base[dst] + out_next;
+      const int64_t groups = (n + fan - 1) / fan, base = n_maps + n_out;
       for (int64_t g = 0; g < groups; ++g)
         items.push_back(CItem{off + g * fan, base + g, (int32_t)std::min(fan, n - g * fan), (int32_t)heavy_rows[h],
                               (int32_t)h, 0});
-      out_next += groups;
+      n_out += groups;
       cur_off[h] = base;
       cur_n[h] = groups;
       next.push_back(h);
     }
-    if (level == 0) out0 = out_next;
-    if (out_next > (dst == 1 ? INT64_MAX : n_maps)) return fail(FT_ERR_STATE, "combine plan overflow");
-    std::stable_sort(finals.begin(), finals.end(), [](const CItem& x, const CItem& y) { return x.count > y.count; });
-    M.level_ncomp.push_back((int64_t)items.size());
-    items.insert(items.end(), finals.begin(), finals.end());
-    H.levels.push_back(std::move(items));
+    if (!items.empty()) {
+      M.level_ncomp.push_back((int64_t)items.size());
+      H.levels.push_back(std::move(items));
+    }
     active.swap(next);
-    ++level;
+  }
+  if (n_maps + n_out > 0x7FFFFFFF) return fail(FT_ERR_SHAPE, "too many chunks");
+  if (!finals.empty()) {
+    std::stable_sort(finals.begin(), finals.end(), [](const CItem& x, const CItem& y) { return x.count > y.count; });
+    M.level_ncomp.push_back(0);
+    H.levels.push_back(std::move(finals));
   }
 
   // relaxed merge items: a heavy row's chunk increments are slots
@@ -406,7 +405,7 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
   M.n_apply = (int64_t)H.apply.size();
   M.n_heavy = n_heavy;
   M.n_maps = n_maps;
-  M.n_level_out0 = out0;
+  M.n_fold_out = n_out;
   M.n_segs = (int64_t)H.segs.size();
   M.n_relax = (int64_t)H.relax.size() - M.n_relax_groups;
   int64_t off = 0;
@@ -461,7 +460,7 @@ static void layout(ft_plan* P) {
     o.fval = L.add(H.fval.size() * sizeof(float));
     o.fib_idx = L.add(M.use_fiber ? H.fib_idx.size() * sizeof(int32_t) : 0);
     if (M.use_fiber) max_fib = std::max(max_fib, M.n_fibers);
-    max_slots = std::max(max_slots, M.n_maps + M.n_level_out0);
+    max_slots = std::max(max_slots, M.n_maps + M.n_fold_out);
     max_heavy = std::max(max_heavy, M.n_heavy);
     max_segs = std::max(max_segs, M.n_segs);
     map_floats = std::max(map_floats, max_slots * (J * J + J));
@@ -581,7 +580,7 @@ extern "C" ft_status ft_plan_create(ft_plan** out, const ft_desc* d, const int32
   P->relaxed = (d->flags & FT_RELAXED) != 0;
   P->fused = !(d->flags & FT_SPLIT_FACTOR);
   P->run_reuse = (d->flags & FT_RUN_REUSE) && N >= 3;
-  P->fanin = std::min(d->fanin ? d->fanin : max_fanin(d->J[0]), max_fanin(d->J[0]));
+  P->fanin = std::min(d->fanin ? d->fanin : max_fanin(), max_fanin());
   try {
     P->meta.resize(N);
     P->host.resize(N);
