@@ -169,6 +169,55 @@ __device__ __forceinline__ void gather_w_nc(const NoC<N>& nc, const float (&Bc)[
 }
 
 
+// Layout of factor indices j over a wavefront where G^T = B W^T is formed by
+// MFMA (lane l = 16 g + i): lane (i, g) holds j = jbase(g) + k, k < J / 4, of
+// slot i, which are contiguous.
+template <int J>
+struct JLayout {
+  static constexpr int JT = (J + 15) / 16;      // 16-wide tiles of j
+  static constexpr int VJ = J >= 16 ? 4 : J / 4;  // j per lane and tile
+  static constexpr int NG = J / 4;              // j per lane
+  __device__ static int jbase(int g) { return J >= 32 ? 16 * (g & 1) + 8 * (g >> 1) : (J / 4) * g; }
+  // j of row (or column) r of tile jt of an MFMA result, -1 where J = 8 leaves it empty
+  __device__ static int jmap(int jt, int r) {
+    return (r & 3) < VJ ? jbase(r >> 2) + VJ * jt + (r & 3) : -1;
+  }
+};
+
+// B(m) as the left operand of G^T = B W^T: row r of tile jt is factor index
+// jmap(jt, r); the k values of lane (i, g) are the contiguous rank indices
+// KR g + s, so that W comes as contiguous slices.  form() is the one place
+// where g is formed, so that every caller gets the same bits: lane (i, g) gets
+// G[i][jbase(g) + k], k < J / 4, of the 16 slots whose w it is given.
+template <int J, int R, class T>
+struct GForm {
+  static constexpr int KR = R / 4;
+  float b[JLayout<J>::JT][KR];
+  __device__ __forceinline__ void load(const T* __restrict__ Bm, int i, int g) {
+#pragma unroll
+    for (int jt = 0; jt < JLayout<J>::JT; ++jt) {
+      const int j = JLayout<J>::jmap(jt, i);
+#pragma unroll
+      for (int k = 0; k < KR; ++k) b[jt][k] = j >= 0 ? to_f(Bm[j * R + KR * g + k]) : 0.f;
+    }
+  }
+  __device__ __forceinline__ void form(const float (&w)[KR], float (&G)[JLayout<J>::NG]) const {
+    constexpr int VJ = JLayout<J>::VJ;
+    floatx4 acc[JLayout<J>::JT];
+#pragma unroll
+    for (int jt = 0; jt < JLayout<J>::JT; ++jt) acc[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < KR; ++k)
+#pragma unroll
+      for (int jt = 0; jt < JLayout<J>::JT; ++jt)
+        acc[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[jt][k], w[k], acc[jt], 0, 0, 0);
+#pragma unroll
+    for (int jt = 0; jt < JLayout<J>::JT; ++jt)
+#pragma unroll
+      for (int v = 0; v < VJ; ++v) G[VJ * jt + v] = acc[jt][v];
+  }
+};
+
 #define FT_CONFIGS(X)                                                                                       \
   X(3, 8, 8) X(3, 16, 16) X(3, 32, 32) X(4, 8, 8) X(4, 32, 32) X(8, 8, 16) X(5, 32, 32) X(6, 32, 32) X(7, 32, 32) \
       X(8, 32, 32) X(9, 32, 32) X(10, 32, 32)

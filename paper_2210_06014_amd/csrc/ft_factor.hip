@@ -113,20 +113,12 @@ struct RhoPow {
 };
 
 template <int J>
-struct Geo {
-  static constexpr int JT = (J + 15) / 16;      // 16-wide tiles of j
-  static constexpr int VJ = J >= 16 ? 4 : J / 4;  // j per lane and tile
-  static constexpr int NG = J / 4;              // values of Gu
+struct Geo : JLayout<J> {
   static constexpr int NS = J >= 32 ? 8 : 4;    // values of Gr
   static constexpr int GS = J + 4;              // LDS row stride of G in floats
   static constexpr int LS = 20;                 // LDS row stride of L in floats
-  __device__ static int jbase(int g) { return J >= 32 ? 16 * (g & 1) + 8 * (g >> 1) : (J / 4) * g; }
   __device__ static int sbase(int g) { return J >= 32 ? 8 * (g >> 1) : 4 * g; }
   __device__ static int jlane(int i, int g) { return J >= 32 ? 16 * (g & 1) + i : i % J; }
-  // j of row (or column) r of tile jt of an MFMA result, -1 where J = 8 leaves it empty
-  __device__ static int jmap(int jt, int r) {
-    return (r & 3) < VJ ? jbase(r >> 2) + VJ * jt + (r & 3) : -1;
-  }
 };
 
 template <int J>
@@ -223,40 +215,6 @@ __device__ __forceinline__ void inverse_step(float (&y)[8], const float (&L)[8])
   }
 #undef FT_INV
 }
-
-// B(m) as the left operand of G^T = B W^T: row r of tile jt is factor index
-// jmap(jt, r); the k values of lane (i, g) are the contiguous rank indices
-// KR g + s, so that W comes as contiguous slices.  form() is the one place
-// where g is formed, so that every caller gets the same bits: lane (i, g) gets
-// G[i][jbase(g) + k], k < J / 4, of the 16 slots whose w it is given.
-template <int J, int R, class T>
-struct GForm {
-  static constexpr int KR = R / 4;
-  float b[Geo<J>::JT][KR];
-  __device__ __forceinline__ void load(const T* __restrict__ Bm, int i, int g) {
-#pragma unroll
-    for (int jt = 0; jt < Geo<J>::JT; ++jt) {
-      const int j = Geo<J>::jmap(jt, i);
-#pragma unroll
-      for (int k = 0; k < KR; ++k) b[jt][k] = j >= 0 ? to_f(Bm[j * R + KR * g + k]) : 0.f;
-    }
-  }
-  __device__ __forceinline__ void form(const float (&w)[KR], float (&G)[Geo<J>::NG]) const {
-    constexpr int VJ = Geo<J>::VJ;
-    floatx4 acc[Geo<J>::JT];
-#pragma unroll
-    for (int jt = 0; jt < Geo<J>::JT; ++jt) acc[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k = 0; k < KR; ++k)
-#pragma unroll
-      for (int jt = 0; jt < Geo<J>::JT; ++jt)
-        acc[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[jt][k], w[k], acc[jt], 0, 0, 0);
-#pragma unroll
-    for (int jt = 0; jt < Geo<J>::JT; ++jt)
-#pragma unroll
-      for (int v = 0; v < VJ; ++v) G[VJ * jt + v] = acc[jt][v];
-  }
-};
 
 // Source of the blocks' G: the C rows of an element's other modes (w, then
 // B(m) w), its fiber's g, or (NC, order 3 and J = R = 16) C rows formed from

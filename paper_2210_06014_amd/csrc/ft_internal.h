@@ -57,7 +57,7 @@ struct ModeHost {
   std::vector<CItem> relax;       // FT_RELAXED: group items (chunk slots -> group record), then one merge item per
                                   // heavy row (its group records; out_off = elements after the head)
   std::vector<Seg> segs;
-  std::vector<int64_t> seg_ptr;   // I+1: segments of row i are seg_ptr[i]..seg_ptr[i+1]-1
+  std::vector<int64_t> seg_first; // I: first segment of a row (its ceil(L / kSegLen) segments are consecutive)
   std::vector<int32_t> fid;       // nnz: fiber of the element at each CSR position
   std::vector<int32_t> fib_idx;   // (N-1) x fibers: fixed indices of each fiber (modes m+1, ..., m-1)
   // FT_RELAXED with rows longer than the head: idx, val and perm with those
@@ -77,7 +77,7 @@ struct ModeDev {
   CItem* levels = nullptr;  // all levels back to back
   CItem* relax = nullptr;
   Seg* segs = nullptr;
-  int64_t* seg_ptr = nullptr;
+  int64_t* seg_first = nullptr;
   int32_t* fid = nullptr;
   int32_t* fib_idx = nullptr;
   int32_t* fidx = nullptr;  // factor-order copies (FT_RELAXED), or null: the factor passes read idx, val
@@ -87,7 +87,7 @@ struct ModeDev {
 // Byte offsets of a mode's arrays in the caller's plan workspace (SIZE_MAX:
 // the array is empty and its device pointer stays null).
 struct ModeOff {
-  size_t row_ptr, idx, val, perm, compose, apply, levels, relax, segs, seg_ptr, fid, fib_idx, fidx, fval;
+  size_t row_ptr, idx, val, perm, compose, apply, levels, relax, segs, seg_first, fid, fib_idx, fidx, fval;
 };
 
 // Every array in a device workspace starts on this boundary.
@@ -138,6 +138,7 @@ struct ModeMeta {
   std::vector<int64_t> level_ncomp;  // folds of each level (0: the last level, whose items are final)
   int64_t n_fold_out = 0;          // map slots that the folds write, after those of the chunks
   int64_t n_segs = 0;
+  int64_t n_long_segs = 0;  // segments taken by a wavefront each; the short rows' follow, by descending length
   int64_t n_relax_groups = 0;  // FT_RELAXED level-1 items
   int64_t n_relax = 0;         // FT_RELAXED level-2 items (heavy rows)
   int64_t n_fibers = 0;
@@ -188,6 +189,8 @@ ft_status fail(ft_status s, const std::string& msg);
 // kernel launchers (ft_refresh.hip, ft_factor.hip, ft_segment.hip); return hipSuccess or the launch error
 constexpr int kPartials = 2048;  // max workgroups of the reduction kernels
 constexpr int kSegLen = 512;     // max elements per segment
+constexpr int kShortSeg = 32;    // rows of at most this many elements may be listed as short
+constexpr int kMinShort = 16384; // a mode with fewer of them lists none (one launch instead of two)
 constexpr int kRelaxGroup = 256; // chunks per level-1 group of the relaxed merge
 
 // FT_RELAXED scratch in the map region: J + 1 floats per chunk slot, then

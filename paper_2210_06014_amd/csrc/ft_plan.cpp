@@ -375,13 +375,32 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
     H.relax.insert(H.relax.end(), merges.begin(), merges.end());
   }
 
-  // segments for the core, loss and gradient passes
-  H.seg_ptr.assign((size_t)I + 1, 0);
+  // segments for the core, loss and gradient passes: a wavefront takes a
+  // segment, except that a mode with many short rows lists them last, longest
+  // first, for the kernel that takes one per slot of a wavefront
+  H.seg_first.assign((size_t)I, 0);
+  std::vector<Seg> shorts;
+  int64_t n_short = 0;
+  for (int64_t i = 0; i < I; ++i) {
+    const int64_t L = H.row_ptr[i + 1] - H.row_ptr[i];
+    n_short += L > 0 && L <= kShortSeg;
+  }
+  const bool split = n_short >= kMinShort;
   for (int64_t i = 0; i < I; ++i) {
     int64_t s = H.row_ptr[i], L = H.row_ptr[i + 1] - s;
+    H.seg_first[i] = (int64_t)H.segs.size();
+    if (split && L > 0 && L <= kShortSeg) {
+      shorts.push_back(Seg{s, (int32_t)L, (int32_t)i});
+      continue;
+    }
     for (int64_t o = 0; o < L; o += kSegLen)
       H.segs.push_back(Seg{s + o, (int32_t)std::min<int64_t>(kSegLen, L - o), (int32_t)i});
-    H.seg_ptr[i + 1] = (int64_t)H.segs.size();
+  }
+  M.n_long_segs = (int64_t)H.segs.size();
+  std::stable_sort(shorts.begin(), shorts.end(), [](const Seg& a, const Seg& b) { return a.len > b.len; });
+  for (const Seg& g : shorts) {
+    H.seg_first[g.row] = (int64_t)H.segs.size();
+    H.segs.push_back(g);
   }
 
   // runs of equal column-0 index (mode m + 1) within rows: the segment
@@ -454,7 +473,7 @@ static void layout(ft_plan* P) {
     o.levels = L.add(nlev * sizeof(CItem));
     o.relax = L.add(P->relaxed ? H.relax.size() * sizeof(CItem) : 0);
     o.segs = L.add(H.segs.size() * sizeof(Seg));
-    o.seg_ptr = L.add(H.seg_ptr.size() * sizeof(int64_t));
+    o.seg_first = L.add(H.seg_first.size() * sizeof(int64_t));
     o.fid = L.add(M.use_fiber ? H.fid.size() * sizeof(int32_t) : 0);
     o.fidx = L.add(H.fidx.size() * sizeof(int32_t));
     o.fval = L.add(H.fval.size() * sizeof(float));
@@ -653,7 +672,7 @@ extern "C" ft_status ft_plan_upload(ft_plan* P, void* ws, size_t ws_bytes, void*
     if (e == hipSuccess) e = copy_in(ws, o.levels, levels[m], s);
     if (e == hipSuccess) e = copy_in(ws, o.relax, H.relax, s);
     if (e == hipSuccess) e = copy_in(ws, o.segs, H.segs, s);
-    if (e == hipSuccess) e = copy_in(ws, o.seg_ptr, H.seg_ptr, s);
+    if (e == hipSuccess) e = copy_in(ws, o.seg_first, H.seg_first, s);
     if (e == hipSuccess) e = copy_in(ws, o.fid, H.fid, s);
     if (e == hipSuccess) e = copy_in(ws, o.fib_idx, H.fib_idx, s);
     if (e == hipSuccess) e = copy_in(ws, o.fidx, H.fidx, s);
@@ -674,7 +693,7 @@ extern "C" ft_status ft_plan_upload(ft_plan* P, void* ws, size_t ws_bytes, void*
     D.levels = at<CItem>(ws, o.levels);
     D.relax = at<CItem>(ws, o.relax);
     D.segs = at<Seg>(ws, o.segs);
-    D.seg_ptr = at<int64_t>(ws, o.seg_ptr);
+    D.seg_first = at<int64_t>(ws, o.seg_first);
     D.fid = at<int32_t>(ws, o.fid);
     D.fib_idx = at<int32_t>(ws, o.fib_idx);
     D.fidx = at<int32_t>(ws, o.fidx);

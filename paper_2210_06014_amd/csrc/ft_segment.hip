@@ -267,6 +267,155 @@ __global__ __launch_bounds__(256) void k_segsum(const Seg* __restrict__ segs, in
     partials[(int64_t)blockIdx.x * J * R + e] = ((red[0][e] + red[1][e]) + red[2][e]) + red[3][e];
 }
 
+// Short rows.  A row of ten elements leaves most of a wavefront idle in the
+// walk above (a trip is 64 elements at R = 16, 32 at R = 32), so where a mode
+// has many, the plan lists its rows of at most kShortSeg elements apart, by
+// descending length, and here the 64 / (R / V) slots of a wavefront take a row
+// each: a slot's lanes load the indices of 8 elements at a time and gather them
+// one after another, with no sum over the slots.  The rows' contribution to G,
+// sum_slot a_slot s_slot^T, is a product over the slots on the matrix cores.
+// Mode 0 of the Netflix-shaped tensors (400k rows, half the elements in rows of
+// ten): 8M elements, J = R = 32, 240 -> 134 us for both kernels; 5M, J = R = 16, 158 -> 59 us.
+template <int N, int J, int R, int MODE, class T>
+__global__ __launch_bounds__(256) void k_segshort(const Seg* __restrict__ segs, int64_t seg0, int64_t nseg,
+                                                  const int32_t* __restrict__ idx, int64_t nnz,
+                                                  const float* __restrict__ val, CPtrs<N, T> cp,
+                                                  const T* __restrict__ Cm, const T* __restrict__ Am,
+                                                  const float* __restrict__ up, const int32_t* __restrict__ perm,
+                                                  float* __restrict__ partials, float* __restrict__ tseg) {
+  constexpr int V = vpl<T>();
+  constexpr int QL = R / V;
+  constexpr int P = 64 / QL;
+  constexpr int EB = 8;                        // elements of a slot per batch of index loads
+  constexpr int NL = (EB + QL - 1) / QL;       // index loads per lane and batch
+  constexpr int U = trip_unroll<N>();          // elements of a slot gathered together
+  constexpr int JT = (J + 15) / 16, RT = (R + 15) / 16;
+  constexpr int SR = R + 4;
+  __shared__ float red[4][J * R];
+  __shared__ __align__(16) float sums[4][P * SR];
+  const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int slot = lane / QL, q = lane % QL;
+  const float* xs = MODE == 2 ? up : val;
+  floatx4 G[JT][RT];
+#pragma unroll
+  for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) G[jt][rt] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const int64_t ngrp = (nseg + P - 1) / P, nw = (int64_t)gridDim.x * 4;
+  for (int64_t grp = (int64_t)blockIdx.x * 4 + wave; grp < ngrp; grp += nw) {
+    const int64_t k = grp * P + slot;
+    Seg S = segs[seg0 + min(k, nseg - 1)];
+    if (k >= nseg) S.len = 0;
+    const int maxlen = __builtin_amdgcn_readfirstlane(S.len);  // slot 0's: the list is sorted
+    float crow[V];
+#pragma unroll
+    for (int c = 0; c < V; ++c) crow[c] = 0.f;
+    if (MODE != 2) load16(Cm + (int64_t)S.row * R + V * q, crow);
+    // A(m) of the slots 4 t + g as the left operand of G
+    float av[P / 4][JT];
+#pragma unroll
+    for (int t = 0; t < P / 4; ++t) {
+      const int64_t row = __shfl(S.row, (4 * t + g) * QL);
+#pragma unroll
+      for (int jt = 0; jt < JT; ++jt) {
+        const float a = to_f(Am[row * J + 16 * jt + (J >= 16 ? i : i % J)]);
+        av[t][jt] = (J >= 16 || i < J) ? a : 0.f;
+      }
+    }
+    float acc[V];
+#pragma unroll
+    for (int c = 0; c < V; ++c) acc[c] = 0.f;
+    struct Batch {
+      int32_t ik[NL][N > 1 ? N - 1 : 1];
+      float xv[NL];
+    };
+    const int last = max(S.len - 1, 0);
+    auto load = [&](int t0, Batch& b) {
+#pragma unroll
+      for (int h = 0; h < NL; ++h) {
+        const uint32_t o = (uint32_t)min(t0 + q + QL * h, last);
+#pragma unroll
+        for (int n = 0; n < N - 1; ++n) b.ik[h][n] = (idx + (int64_t)n * nnz + S.start)[o];
+        b.xv[h] = MODE == 2 ? xs[(perm + S.start)[o]] : (xs + S.start)[o];
+      }
+    };
+    Batch cur;
+    load(0, cur);
+    for (int t0 = 0; t0 < maxlen; t0 += EB) {
+      Batch nxt;
+      load(t0 + EB, nxt);
+      static_for<0, EB / U>([&](auto HH) {
+        constexpr int u0 = decltype(HH)::value * U;
+        if (t0 + u0 < maxlen) {
+          float w[U][V], xv[U];
+          bool vl[U];
+          static_for<0, U>([&](auto UU) {
+            constexpr int u = decltype(UU)::value, e = u0 + u, h = e / QL;
+            const int from = slot * QL + e % QL;
+            int32_t ik[N > 1 ? N - 1 : 1];
+#pragma unroll
+            for (int n = 0; n < N - 1; ++n) ik[n] = QL > 1 ? __shfl(cur.ik[h][n], from) : cur.ik[h][n];
+            xv[u] = QL > 1 ? __shfl(cur.xv[h], from) : cur.xv[h];
+            vl[u] = t0 + e < S.len;
+            gather_slices<N, R, T>(cp, ik, vl[u], q, w[u]);
+          });
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            float d;
+            if (MODE == 2) {
+              d = vl[u] ? xv[u] : 0.f;
+            } else {
+              float xh = crow[0] * w[u][0];
+#pragma unroll
+              for (int c = 1; c < V; ++c) xh = fmaf(crow[c], w[u][c], xh);
+              xh = group_sum<QL>(xh);
+              d = vl[u] ? (MODE == 0 ? xv[u] - xh : xh - xv[u]) : 0.f;
+            }
+#pragma unroll
+            for (int c = 0; c < V; ++c) acc[c] = fmaf(d, w[u][c], acc[c]);
+          }
+        }
+      });
+      cur = nxt;
+    }
+    if (tseg && k < nseg)
+#pragma unroll
+      for (int c = 0; c < V; ++c) tseg[(seg0 + k) * R + V * q + c] = acc[c];
+    // (the wavefront's own LDS, in order)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int c = 0; c < V; c += 4)
+      *reinterpret_cast<floatx4*>(&sums[wave][slot * SR + V * q + c]) =
+          floatx4{acc[c], acc[c + 1], acc[c + 2], acc[c + 3]};
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int t = 0; t < P / 4; ++t)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const float sv = sums[wave][(4 * t + g) * SR + 16 * rt + (R >= 16 ? i : i % R)];
+        const float sr = (R >= 16 || i < R) ? sv : 0.f;
+#pragma unroll
+        for (int jt = 0; jt < JT; ++jt)
+          G[jt][rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[t][jt], sr, G[jt][rt], 0, 0, 0);
+      }
+  }
+#pragma unroll
+  for (int jt = 0; jt < JT; ++jt)
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int j = 16 * jt + 4 * g + v, r = 16 * rt + i;
+        if (j < J && r < R) red[wave][j * R + r] = G[jt][rt][v];
+      }
+  __syncthreads();
+  for (int e = threadIdx.x; e < J * R; e += 256)
+    partials[(int64_t)blockIdx.x * J * R + e] = ((red[0][e] + red[1][e]) + red[2][e]) + red[3][e];
+}
+
 // ---------------------------------------------------------------------------
 // Segment passes with the C row of the first index column reused along runs.
 // Within a row of mode m the elements are sorted by the index of mode m + 1
@@ -621,24 +770,37 @@ __global__ __launch_bounds__(64) void k_reduce_update(const float* __restrict__ 
   }
 }
 
-// dA(m)[i, j] = sum_r B(m)[j, r] t_i[r], t_i = sum of the row's segment sums.
+// dA(m)[i, j] = sum_r B(m)[j, r] t_i[r], t_i = sum of the row's segment sums:
+// 16 rows per wavefront, a lane summing a slice of one row's segments, eight
+// loads in flight, and B t on the matrix cores.  (A thread per entry read the
+// row's sums J times and a long row's one load after another: 100k rows, J = R
+// = 16, 49 -> 13 us.)
 template <int J, int R, class T>
-__global__ __launch_bounds__(256) void k_grad_rows(const int64_t* __restrict__ seg_ptr, const float* __restrict__ tseg,
-                                                   const T* __restrict__ Bm, float* __restrict__ gA, int64_t I) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= I * J) return;
-  const int64_t i = e / J;
-  const int j = (int)(e % J);
-  float t[R];
+__global__ __launch_bounds__(256) void k_grad_rows(const int64_t* __restrict__ seg_first,
+                                                   const int64_t* __restrict__ row_ptr,
+                                                   const float* __restrict__ tseg, const T* __restrict__ Bm,
+                                                   float* __restrict__ gA, int64_t I) {
+  constexpr int KR = R / 4;
+  const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+  const int64_t row = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 16 + i;
+  if (row - i >= I) return;
+  GForm<J, R, T> gf;
+  gf.load(Bm, i, g);
+  const int64_t rc = min(row, I - 1);
+  const int64_t n = row < I ? (row_ptr[rc + 1] - row_ptr[rc] + kSegLen - 1) / kSegLen : 0;
+  const float* src = tseg + seg_first[rc] * R + KR * g;
+  float t[KR];
 #pragma unroll
-  for (int r = 0; r < R; ++r) t[r] = 0.f;
-  for (int64_t sg = seg_ptr[i]; sg < seg_ptr[i + 1]; ++sg)
+  for (int c = 0; c < KR; ++c) t[c] = 0.f;
+#pragma unroll 8
+  for (int64_t k = 0; k < n; ++k)
 #pragma unroll
-    for (int r = 0; r < R; ++r) t[r] += tseg[sg * R + r];
-  float s = 0.f;
+    for (int c = 0; c < KR; ++c) t[c] += src[k * R + c];
+  float G[JLayout<J>::NG];
+  gf.form(t, G);
+  if (row < I)
 #pragma unroll
-  for (int r = 0; r < R; ++r) s = fmaf(to_f(Bm[j * R + r]), t[r], s);
-  gA[e] = s;
+    for (int k = 0; k < JLayout<J>::NG; ++k) gA[row * J + JLayout<J>::jbase(g) + k] = G[k];
 }
 
 // Loss: per-element e^2 summed in FP64 (and, with out != nullptr, xhat stored
@@ -902,18 +1064,31 @@ hipError_t segsum_impl(const ft_plan* P, int m, const ft_params* p, float* parti
     }
   }
   const void* kern = mode == 2 ? (const void*)k_segsum<N, J, R, 2, T> : (const void*)k_segsum<N, J, R, 0, T>;
-  const int nb = seg_blocks(kern, M.n_segs);
-  *nblocks = nb;
+  const void* kshort = mode == 2 ? (const void*)k_segshort<N, J, R, 2, T> : (const void*)k_segshort<N, J, R, 0, T>;
+  const int64_t n_short = M.n_segs - M.n_long_segs;
+  // the two kernels' partials share the scratch: at most half of it each where both run
+  const int most = n_short > 0 ? kPartials / 2 : kPartials;
+  const int nb = M.n_long_segs > 0 || n_short == 0 ? std::min(most, seg_blocks(kern, M.n_long_segs)) : 0;
+  const int nbs = n_short > 0 ? std::min(most, seg_blocks(kshort, n_short)) : 0;
+  *nblocks = nb + nbs;
+  float* pshort = partials + (int64_t)nb * J * R;
   KTimer tm(P, FT_K_SEGSUM, s);
+#define FT_SEGSUM(MODE, UP, PERM)                                                                                     \
+  do {                                                                                                                \
+    if (nb > 0)                                                                                                       \
+      hipLaunchKernelGGL((k_segsum<N, J, R, MODE, T>), dim3(nb), dim3(256), 0, s, D.segs, M.n_long_segs, D.idx,       \
+                         P->nnz, D.val, cp, Cm, Am, UP, PERM, partials, tseg);                                        \
+    if (nbs > 0)                                                                                                      \
+      hipLaunchKernelGGL((k_segshort<N, J, R, MODE, T>), dim3(nbs), dim3(256), 0, s, D.segs, M.n_long_segs, n_short,  \
+                         D.idx, P->nnz, D.val, cp, Cm, Am, UP, PERM, pshort, tseg);                                   \
+  } while (0)
   if (mode == 0)
-    hipLaunchKernelGGL((k_segsum<N, J, R, 0, T>), dim3(nb), dim3(256), 0, s, D.segs, M.n_segs, D.idx, P->nnz, D.val,
-                       cp, Cm, Am, nullptr, nullptr, partials, tseg);
+    FT_SEGSUM(0, nullptr, nullptr);
   else if (mode == 1)
-    hipLaunchKernelGGL((k_segsum<N, J, R, 1, T>), dim3(nb), dim3(256), 0, s, D.segs, M.n_segs, D.idx, P->nnz, D.val,
-                       cp, Cm, Am, nullptr, nullptr, partials, tseg);
+    FT_SEGSUM(1, nullptr, nullptr);
   else
-    hipLaunchKernelGGL((k_segsum<N, J, R, 2, T>), dim3(nb), dim3(256), 0, s, D.segs, M.n_segs, D.idx, P->nnz, D.val,
-                       cp, Cm, Am, up, D.perm, partials, tseg);
+    FT_SEGSUM(2, up, D.perm);
+#undef FT_SEGSUM
   return hipGetLastError();
 }
 
@@ -986,9 +1161,9 @@ hipError_t predict_impl(const ft_plan* P, const ft_params* p, const int32_t* coo
 template <int J, int R, class T>
 hipError_t grad_rows_impl(const ft_plan* P, int m, const ft_params* p, const float* tseg, float* gA, hipStream_t s) {
   const int64_t I = P->desc.dims[m];
-  const unsigned gb = (unsigned)((I * J + 255) / 256);
+  const unsigned gb = (unsigned)((I + 63) / 64);
   if (gb > 0)
-    hipLaunchKernelGGL((k_grad_rows<J, R, T>), dim3(gb), dim3(256), 0, s, P->dev[m].seg_ptr, tseg,
+    hipLaunchKernelGGL((k_grad_rows<J, R, T>), dim3(gb), dim3(256), 0, s, P->dev[m].seg_first, P->dev[m].row_ptr, tseg,
                        Store<T>::B(p, m), gA, I);
   return hipGetLastError();
 }
