@@ -87,11 +87,7 @@ extern "C" ft_status ft_refresh(const ft_plan* P, const ft_params* p, int32_t mo
   FT_TRY(check_params(P, p));
   if (mode >= P->N) return fail(FT_ERR_ARG, "mode out of range");
   hipStream_t s = (hipStream_t)stream;
-  for (int n = 0; n < P->N; ++n) {
-    if (mode >= 0 && n != mode) continue;
-    FT_TRY(hip_status(launch_refresh(P, n, p, s), "refresh"));
-  }
-  return FT_OK;
+  return hip_status(mode >= 0 ? launch_refresh(P, mode, mode + 1, p, s) : launch_refresh(P, 0, P->N, p, s), "refresh");
 }
 
 static ft_status predict(const ft_plan* P, const ft_params* p, const int32_t* d_coords, int64_t q, float* d_out,
@@ -134,7 +130,7 @@ extern "C" ft_status ft_factor_epoch(const ft_plan* P, const ft_params* p, doubl
   const Scratch S = scratch_of(P, p);
   for (int m = 0; m < P->N; ++m) {
     FT_TRY(hip_status(launch_factor(P, m, p, S, lr, lam, s), "factor pass"));
-    FT_TRY(hip_status(launch_refresh(P, m, p, s), "refresh"));
+    FT_TRY(hip_status(launch_refresh(P, m, m + 1, p, s), "refresh"));
   }
   return FT_OK;
 }
@@ -167,7 +163,7 @@ extern "C" ft_status ft_core_epoch(const ft_plan* P, const ft_params* p, double 
   const Scratch S = scratch_of(P, p);
   for (int m = 0; m < P->N; ++m) {
     FT_TRY(hip_status(launch_core_update(P, m, p, S, lr, lam, s), "core pass"));
-    FT_TRY(hip_status(launch_refresh(P, m, p, s), "refresh"));
+    FT_TRY(hip_status(launch_refresh(P, m, m + 1, p, s), "refresh"));
   }
   return FT_OK;
 }

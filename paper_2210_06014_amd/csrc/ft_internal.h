@@ -235,7 +235,7 @@ inline double* relax_partials(const ft_plan* P, const Scratch& S, int m) {
 // Scratch pointers of a parameter set (its buffer checked by the caller).
 Scratch scratch_of(const ft_plan* P, const ft_params* p);
 
-hipError_t launch_refresh(const ft_plan* P, int n, const ft_params* p, hipStream_t s);
+hipError_t launch_refresh(const ft_plan* P, int n0, int n1, const ft_params* p, hipStream_t s);  // modes n0..n1-1
 hipError_t launch_factor(const ft_plan* P, int m, const ft_params* p, const Scratch& S, double lr, double lam,
                          hipStream_t s);
 hipError_t launch_core_grad(const ft_plan* P, int m, const ft_params* p, const Scratch& S, float* G_out,

@@ -27,9 +27,23 @@ __device__ __forceinline__ int refresh_k(int g, int kb) {
     return (J / 4) * g + kb;
 }
 
+// The modes of one launch (blockIdx.y): one, or all of them when every C is
+// refreshed, so that a model's first refresh is one launch.
+struct RefreshArgs {
+  const float* A[FT_MAX_ORDER];
+  const float* B[FT_MAX_ORDER];
+  void* A16[FT_MAX_ORDER];
+  void* B16[FT_MAX_ORDER];
+  void* C[FT_MAX_ORDER];  // FP32, or BF16
+  int64_t I[FT_MAX_ORDER];
+};
+
 template <int J, int R>
-__global__ __launch_bounds__(256) void k_refresh(const float* __restrict__ A, const float* __restrict__ B,
-                                                 float* __restrict__ C, int64_t I) {
+__global__ __launch_bounds__(256) void k_refresh(RefreshArgs args) {
+  const float* __restrict__ A = args.A[blockIdx.y];
+  const float* __restrict__ B = args.B[blockIdx.y];
+  float* __restrict__ C = static_cast<float*>(args.C[blockIdx.y]);
+  const int64_t I = args.I[blockIdx.y];
   static_assert(J % 4 == 0, "J is a multiple of 4");
   constexpr int KPL = J / 4;  // k values per lane
   constexpr int CT = (R + 15) / 16;
@@ -80,18 +94,21 @@ __global__ __launch_bounds__(256) void k_refresh(const float* __restrict__ A, co
   }
 }
 
-// BF16 storage: C16 = bf16(A16 B16) with v_mfma_f32_16x16x16_bf16 (FP32
-// accumulation).  Lane (i, g) supplies four k values per instruction: with
-// J a multiple of 32 they are 8 g + 4 kb + u (one 16-byte load of 8 BF16
-// values per row covers both instructions), otherwise 16 kb + 4 g + u; k
-// beyond J supplies zeros.  The result layout is that of the FP32 tile.
+// BF16 storage: A16 = bf16(A), B16 = bf16(B), C16 = bf16(A16 B16) in one launch,
+// with v_mfma_f32_16x16x16_bf16 (FP32 accumulation): a lane rounds the master
+// values that it supplies to the product and stores them (three launches,
+// casts first, took 12 us on a 10,000-row mode, this one 5).  Lane (i, g)
+// supplies four k values per instruction: with J a multiple of 32 they are
+// 8 g + 4 kb + u (8 consecutive values of a row cover both instructions),
+// otherwise 16 kb + 4 g + u; k beyond J supplies zeros.  The result layout is
+// that of the FP32 tile.
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint16_t f2bf(float f) {
   // round to nearest even on the upper 16 bits (IEEE-754 binary32 -> bfloat16); NaN stays NaN
   const uint32_t u = __float_as_uint(f);
-  if ((u & 0x7FFFFFFFu) > 0x7F800000u) return (uint16_t)((u >> 16) | 0x40);
-  return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+  const uint32_t nan = (u >> 16) | 0x40u, num = (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+  return (uint16_t)((u & 0x7FFFFFFFu) > 0x7F800000u ? nan : num);
 }
 
 template <int J>
@@ -103,51 +120,75 @@ __device__ __forceinline__ int refresh_k16(int g, int kb, int u) {
 }
 
 template <int J, int R>
-__global__ __launch_bounds__(256) void k_refresh_bf16(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
-                                                      uint16_t* __restrict__ C, int64_t I) {
+__global__ __launch_bounds__(256) void k_refresh_bf16(RefreshArgs args) {
   constexpr int CT = (R + 15) / 16;
   constexpr int KB = (J + 15) / 16;
   constexpr int TPW = kRefreshTiles;
+  const float* __restrict__ A = args.A[blockIdx.y];
+  const float* __restrict__ B = args.B[blockIdx.y];
+  uint16_t* __restrict__ A16 = static_cast<uint16_t*>(args.A16[blockIdx.y]);
+  uint16_t* __restrict__ B16 = static_cast<uint16_t*>(args.B16[blockIdx.y]);
+  uint16_t* __restrict__ C = static_cast<uint16_t*>(args.C[blockIdx.y]);
+  const int64_t I = args.I[blockIdx.y];
   const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
   const int64_t tile0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * TPW;
   if (tile0 * 16 >= I) return;
-  shortx4 b[CT][KB];
+  // loads from clamped addresses, masked afterwards, so that all are in flight together
+  float bv[CT][KB][4], av[TPW][KB][4];
 #pragma unroll
-  for (int ct = 0; ct < CT; ++ct) {
-    const int col = ct * 16 + li;
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        bv[ct][kb][u] = B[min(refresh_k16<J>(lg, kb, u), J - 1) * R + min(ct * 16 + li, R - 1)];
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    const float* ar = A + min((tile0 + t) * 16 + li, I - 1) * J;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      const int k = min(refresh_k16<J>(lg, kb, 0), J - 4);  // four consecutive values
+#pragma unroll
+      for (int u = 0; u < 4; ++u) av[t][kb][u] = ar[k + u];
+    }
+  }
+  shortx4 b[CT][KB], a[TPW][KB];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int k = refresh_k16<J>(lg, kb, u);
-        b[ct][kb][u] = (col < R && k < J) ? (short)B[k * R + col] : (short)0;
+        const bool ok = ct * 16 + li < R && refresh_k16<J>(lg, kb, u) < J;
+        b[ct][kb][u] = ok ? (short)f2bf(bv[ct][kb][u]) : (short)0;
       }
-  }
-  shortx4 a[TPW][KB];
 #pragma unroll
-  for (int t = 0; t < TPW; ++t) {
-    const int64_t row = (tile0 + t) * 16 + li;
-    const bool ok = row < I;
-    const uint16_t* ar = A + (ok ? row : 0) * J;
-    if constexpr (J % 32 == 0) {
+  for (int t = 0; t < TPW; ++t)
 #pragma unroll
-      for (int h = 0; h < J / 32; ++h) {
-        const uint4 v = *reinterpret_cast<const uint4*>(ar + 32 * h + 8 * lg);
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          a[t][2 * h + q / 2][2 * (q % 2)] = ok ? (short)(w[q] & 0xFFFFu) : (short)0;
-          a[t][2 * h + q / 2][2 * (q % 2) + 1] = ok ? (short)(w[q] >> 16) : (short)0;
-        }
+      for (int u = 0; u < 4; ++u) {
+        const bool ok = (tile0 + t) * 16 + li < I && refresh_k16<J>(lg, kb, u) < J;
+        a[t][kb][u] = ok ? (short)f2bf(av[t][kb][u]) : (short)0;
       }
-    } else {
+  if (tile0 == 0) {  // the first wavefront stores B16: its lanes hold every entry once
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const int k = refresh_k16<J>(lg, kb, u);
-          a[t][kb][u] = (ok && k < J) ? (short)ar[k] : (short)0;
+          const int col = ct * 16 + li, k = refresh_k16<J>(lg, kb, u);
+          if (col < R && k < J) B16[k * R + col] = (uint16_t)b[ct][kb][u];
         }
+  }
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    const int64_t row = (tile0 + t) * 16 + li;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      const int k = refresh_k16<J>(lg, kb, 0);
+      if (row < I && k < J) __builtin_memcpy(A16 + row * J + k, &a[t][kb], 8);
     }
   }
 #pragma unroll
@@ -168,12 +209,6 @@ __global__ __launch_bounds__(256) void k_refresh_bf16(const uint16_t* __restrict
   }
 }
 
-__global__ __launch_bounds__(256) void k_cast_bf16(const float* __restrict__ src, uint16_t* __restrict__ dst,
-                                                   int64_t n) {
-  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += (int64_t)gridDim.x * 256)
-    dst[k] = f2bf(src[k]);
-}
-
 }  // namespace
 
 bool supported(int N, int J, int R) {
@@ -186,37 +221,32 @@ bool supported(int N, int J, int R) {
   }
 }
 
-hipError_t launch_refresh(const ft_plan* P, int n, const ft_params* p, hipStream_t s) {
-  const int64_t I = P->desc.dims[n];
-  const int64_t waves = ((I + 15) / 16 + kRefreshTiles - 1) / kRefreshTiles;
-  const unsigned nb = (unsigned)((waves + 3) / 4);
-  KTimer tm(P, FT_K_REFRESH, s);
-  if (bf16(p)) {
-    // BF16 copies of the masters (round to nearest even), then C16 = bf16(A16 B16)
-    const int64_t na = I * P->J, nbm = (int64_t)P->J * P->R;
-    hipLaunchKernelGGL(k_cast_bf16, dim3((unsigned)std::min<int64_t>((na + 255) / 256, 4096) + (na == 0)), dim3(256),
-                       0, s, p->A[n], (uint16_t*)p->A16[n], na);
-    hipLaunchKernelGGL(k_cast_bf16, dim3((unsigned)((nbm + 255) / 256)), dim3(256), 0, s, p->B[n],
-                       (uint16_t*)p->B16[n], nbm);
-    if (nb == 0) return hipGetLastError();
-    switch (P->J * 64 + P->R) {
-#define X(n_, j, r)                                                                                       \
-  case j * 64 + r:                                                                                        \
-    hipLaunchKernelGGL((k_refresh_bf16<j, r>), dim3(nb), dim3(256), 0, s, (const uint16_t*)p->A16[n],    \
-                       (const uint16_t*)p->B16[n], (uint16_t*)p->C16[n], I);                              \
-    return hipGetLastError();
-      X(0, 8, 8) X(0, 16, 16) X(0, 32, 32) X(0, 8, 16)
-#undef X
-      default: return hipErrorInvalidValue;
-    }
+// modes n0 .. n1 - 1
+hipError_t launch_refresh(const ft_plan* P, int n0, int n1, const ft_params* p, hipStream_t s) {
+  RefreshArgs a{};
+  int64_t most = 0;
+  for (int n = n0; n < n1; ++n) {
+    a.A[n - n0] = p->A[n];
+    a.B[n - n0] = p->B[n];
+    a.A16[n - n0] = p->A16[n];
+    a.B16[n - n0] = p->B16[n];
+    a.C[n - n0] = bf16(p) ? p->C16[n] : p->C[n];
+    a.I[n - n0] = P->desc.dims[n];
+    most = std::max(most, P->desc.dims[n]);
   }
-  if (nb == 0) return hipSuccess;
+  if (n1 <= n0) return hipSuccess;
+  const int64_t waves = ((most + 15) / 16 + kRefreshTiles - 1) / kRefreshTiles;
+  const dim3 grid((unsigned)((waves + 3) / 4), (unsigned)(n1 - n0));
+  KTimer tm(P, FT_K_REFRESH, s);
   switch (P->J * 64 + P->R) {
-#define X(n_, j, r)                                                                                           \
-  case j * 64 + r:                                                                                            \
-    hipLaunchKernelGGL((k_refresh<j, r>), dim3(nb), dim3(256), 0, s, p->A[n], p->B[n], p->C[n], I);          \
+#define X(j, r)                                                                          \
+  case j * 64 + r:                                                                       \
+    if (bf16(p))                                                                         \
+      hipLaunchKernelGGL((k_refresh_bf16<j, r>), grid, dim3(256), 0, s, a);              \
+    else                                                                                 \
+      hipLaunchKernelGGL((k_refresh<j, r>), grid, dim3(256), 0, s, a);                   \
     return hipGetLastError();
-    X(0, 8, 8) X(0, 16, 16) X(0, 32, 32) X(0, 8, 16)
+    X(8, 8) X(16, 16) X(32, 32) X(8, 16)
 #undef X
     default: return hipErrorInvalidValue;
   }
