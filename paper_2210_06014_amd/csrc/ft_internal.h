@@ -57,7 +57,7 @@ struct ModeHost {
   std::vector<CItem> relax;       // FT_RELAXED: group items (chunk slots -> group record), then one merge item per
                                   // heavy row (its group records; out_off = elements after the head)
   std::vector<Seg> segs;
-  std::vector<int64_t> seg_first; // I: first segment of a row (its ceil(L / kSegLen) segments are consecutive)
+  std::vector<int64_t> seg_first; // I+1: first segment of a row (its ceil(L / seg_len) segments are consecutive)
   std::vector<int32_t> fid;       // nnz: fiber of the element at each CSR position
   std::vector<int32_t> fib_idx;   // (N-1) x fibers: fixed indices of each fiber (modes m+1, ..., m-1)
   // FT_RELAXED with rows longer than the head: idx, val and perm with those
@@ -161,6 +161,7 @@ struct ft_plan {
   int64_t nnz = 0;
   int chunk = 512, head = 1024, fanin = 16;  // head 0: chosen per mode (ModeMeta::head), at most head_cap
   int64_t head_cap = 0;
+  int seg_len = 512;  // longest segment of the core, loss and gradient passes
   bool no_c_cache = false;  // FT_NO_C_CACHE
   bool relaxed = false;     // FT_RELAXED
   bool fused = true;        // exact factor passes launch in-place items and chunk maps together (not FT_SPLIT_FACTOR)
@@ -188,7 +189,7 @@ ft_status fail(ft_status s, const std::string& msg);
 
 // kernel launchers (ft_refresh.hip, ft_factor.hip, ft_segment.hip); return hipSuccess or the launch error
 constexpr int kPartials = 2048;  // max workgroups of the reduction kernels
-constexpr int kSegLen = 512;     // max elements per segment
+constexpr int kSegLen = 512;     // max elements per segment (ft_plan::seg_len)
 constexpr int kShortSeg = 32;    // rows of at most this many elements may be listed as short
 constexpr int kMinShort = 16384; // a mode with fewer of them lists none (one launch instead of two)
 constexpr int kRelaxGroup = 256; // chunks per level-1 group of the relaxed merge

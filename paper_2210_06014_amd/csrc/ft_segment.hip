@@ -779,7 +779,7 @@ template <int J, int R, class T>
 __global__ __launch_bounds__(256) void k_grad_rows(const int64_t* __restrict__ seg_first,
                                                    const int64_t* __restrict__ row_ptr,
                                                    const float* __restrict__ tseg, const T* __restrict__ Bm,
-                                                   float* __restrict__ gA, int64_t I) {
+                                                   float* __restrict__ gA, int64_t I, int seg_len) {
   constexpr int KR = R / 4;
   const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
   const int64_t row = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 16 + i;
@@ -787,7 +787,7 @@ __global__ __launch_bounds__(256) void k_grad_rows(const int64_t* __restrict__ s
   GForm<J, R, T> gf;
   gf.load(Bm, i, g);
   const int64_t rc = min(row, I - 1);
-  const int64_t n = row < I ? (row_ptr[rc + 1] - row_ptr[rc] + kSegLen - 1) / kSegLen : 0;
+  const int64_t n = row < I ? (row_ptr[rc + 1] - row_ptr[rc] + seg_len - 1) / seg_len : 0;
   const float* src = tseg + seg_first[rc] * R + KR * g;
   float t[KR];
 #pragma unroll
@@ -1164,7 +1164,7 @@ hipError_t grad_rows_impl(const ft_plan* P, int m, const ft_params* p, const flo
   const unsigned gb = (unsigned)((I + 63) / 64);
   if (gb > 0)
     hipLaunchKernelGGL((k_grad_rows<J, R, T>), dim3(gb), dim3(256), 0, s, P->dev[m].seg_first, P->dev[m].row_ptr, tseg,
-                       Store<T>::B(p, m), gA, I);
+                       Store<T>::B(p, m), gA, I, P->seg_len);
   return hipGetLastError();
 }
 
