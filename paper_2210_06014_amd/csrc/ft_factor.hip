@@ -28,13 +28,14 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 // carried too) plus the VALU work of the serial part, which dominates at
 // J <= 16.  The bf16 MFMA would run beside the VALU, but it truncates the terms
 // of an instruction to the largest one's 24 bits: G from three bf16 parts per
-// value took a tenth off a launch and doubled the error of A.  One item per wavefront, because a block's
-// MFMA then serves one chain and the chain is 4 times shorter than with an
-// item per 16 lanes.  Against one step per element on 16 lanes (g by row
-// broadcasts), us per launch: Netflix-shaped 8M elements, J = R = 32, modes
-// 1 and 2: 1048 -> 490; order 4 (3M, J = R = 32) 934 -> 300; order 6 (1M, BF16)
-// 157 -> 50; order 8 (1M, J = 8, R = 16) 334 -> 75; Netflix-shaped 5M, J = R =
-// 16: 267 -> 175.
+// value took a tenth off a launch and doubled the error of A.  One item per
+// wavefront, because a block's MFMA then serves one chain and the chain is 4
+// times shorter than with an item per 16 lanes.  Against one step per element
+// on 16 lanes (g by row broadcasts), us per launch with the forms below:
+// Netflix-shaped 8M elements, J = R = 32, modes 0 to 2: 828, 1048, 1048 -> 370,
+// 505, 580; order 4 (3M, J = R = 32) 934 -> 253; order 6 (1M, BF16) 157 -> 56;
+// order 8 (1M, J = 8, R = 16) 334 -> 62; Netflix-shaped 5M, J = R = 16: 267 ->
+// 171.
 //
 // Lane l = 16 g + i of the wavefront holds:
 //   Gu[k]  G[i][jbase(g) + k], k < J / 4   (as the MFMA that forms G leaves it,
@@ -377,15 +378,12 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// G and K of a block, and both through LDS into the layouts of the serial
-// part.  G of the state product is read back as well (not taken from the MFMA
-// result), because inline assembly reads it.
-template <int J, bool MAP>
-__device__ __forceinline__ void prepare_block(const float (&G)[Geo<J>::NG], float x, float xscale, int nb, float gp,
-                                              int i, int g, WaveLds<J>& lds, Block<J, MAP>& blk) {
+// G and K of a block into LDS: G by slots, and -gp tril(K, -1) by rows.
+template <int J>
+__device__ __forceinline__ void store_block(const float (&G)[Geo<J>::NG], float gp, int i, int g, float* lds_g,
+                                            float* lds_l) {
   using Q = Geo<J>;
-  float* grow = lds.G + i * Q::GS + Q::jbase(g);
-  wave_lds_fence();
+  float* grow = lds_g + i * Q::GS + Q::jbase(g);
   if constexpr (Q::NG == 2) {
     *reinterpret_cast<floatx2*>(grow) = floatx2{G[0], G[1]};
   } else {
@@ -399,8 +397,16 @@ __device__ __forceinline__ void prepare_block(const float (&G)[Geo<J>::NG], floa
   floatx4 Lw;
 #pragma unroll
   for (int v = 0; v < 4; ++v) Lw[v] = 4 * g + v < i ? -gp * K[v] : 0.f;
-  *reinterpret_cast<floatx4*>(lds.L + i * Q::LS + 4 * g) = Lw;
-  wave_lds_fence();
+  *reinterpret_cast<floatx4*>(lds_l + i * Q::LS + 4 * g) = Lw;
+}
+
+// The same out of LDS in the layouts of the serial part.  G of the state
+// product is read back as well (not taken from the MFMA result), because
+// inline assembly reads it.
+template <int J, bool MAP>
+__device__ __forceinline__ void load_block(const float* lds_g, const float* lds_l, int i, int g, Block<J, MAP>& blk) {
+  using Q = Geo<J>;
+  const float* grow = lds_g + i * Q::GS + Q::jbase(g);
   if constexpr (Q::NG == 2) {
     const floatx2 u = *reinterpret_cast<const floatx2*>(grow);
     blk.Gu[0] = u[0];
@@ -413,10 +419,10 @@ __device__ __forceinline__ void prepare_block(const float (&G)[Geo<J>::NG], floa
       for (int v = 0; v < 4; ++v) blk.Gu[k + v] = u[v];
     }
   }
-  const float* gcol = lds.G + Q::sbase(g) * Q::GS + Q::jlane(i, g);
+  const float* gcol = lds_g + Q::sbase(g) * Q::GS + Q::jlane(i, g);
 #pragma unroll
   for (int k = 0; k < Q::NS; ++k) blk.Gr[k] = gcol[k * Q::GS];
-  const float* lrow = lds.L + i * Q::LS;
+  const float* lrow = lds_l + i * Q::LS;
 #pragma unroll
   for (int s = 0; s < 16; s += 4) {
     const floatx4 u = *reinterpret_cast<const floatx4*>(lrow + s);
@@ -429,11 +435,20 @@ __device__ __forceinline__ void prepare_block(const float (&G)[Geo<J>::NG], floa
       const int j = Q::jmap(jt, i);
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const float q = lds.G[(4 * g + v) * Q::GS + max(j, 0)];
+        const float q = lds_g[(4 * g + v) * Q::GS + max(j, 0)];
         blk.Gc[jt][v] = j >= 0 ? q : 0.f;
       }
     }
   }
+}
+
+template <int J, bool MAP>
+__device__ __forceinline__ void prepare_block(const float (&G)[Geo<J>::NG], float x, float xscale, int nb, float gp,
+                                              int i, int g, WaveLds<J>& lds, Block<J, MAP>& blk) {
+  wave_lds_fence();
+  store_block<J>(G, gp, i, g, lds.G, lds.L);
+  wave_lds_fence();
+  load_block<J, MAP>(lds.G, lds.L, i, g, blk);
   blk.xs = i < nb ? x * xscale : 0.f;
 }
 
@@ -685,46 +700,148 @@ __device__ __forceinline__ void factor_item(const FItem& it, const FactorArgs<N,
   }
 }
 
-// One item per wavefront: the hardware dispatcher balances the items (the
-// lists are sorted by length, so that a workgroup's four end together).
-template <int KIND, int N, int J, int R, class T, bool FIB, bool NC = false>
-__global__ __launch_bounds__(256) void k_factor_apply(const FItem* __restrict__ items, int64_t n_items,
-                                                      FactorArgs<N, J, R, T, FIB, NC> F) {
-  __shared__ WaveLds<J> lds[4];
+// The head of a long row, by a workgroup: wavefronts 1 to 3 form its blocks in
+// turn (gathers, MFMA) and leave them in LDS, a round of three ahead of
+// wavefront 0, which only takes the serial parts.  A lone wavefront issues an
+// instruction about every five cycles, so a chain that also forms its blocks
+// takes 1900 cycles per block (J = 8) to 2400 (J = 32); the serial part alone
+// is a quarter of that, and the head of a long row is what a launch waits for.
+template <int J>
+struct __align__(16) TeamLds {
+  float G[2][3][16 * Geo<J>::GS];
+  float L[2][3][16 * Geo<J>::LS];
+  float x[2][3][16];
+};
+
+template <int N, int J, int R, class T, bool FIB, bool NC>
+__device__ __forceinline__ void team_item(const FItem& it, const FactorArgs<N, J, R, T, FIB, NC>& F, TeamLds<J>& lds) {
+  using Q = Geo<J>;
+  using Src = Source<N, J, R, T, FIB, NC>;
+  const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t k = (int64_t)blockIdx.x * 4 + wave;
-  if (k < n_items) factor_item<KIND>(items[k], F, lds[wave]);
+  if (it.len <= 0) return;
+  const int64_t pe = it.start + it.len;
+  const int bs = F.block;
+  const int nblk = (it.len + bs - 1) / bs, rounds = (nblk + 2) / 3;
+  const int jl = Q::jlane(i, g);
+  if (wave == 0) {
+    __builtin_amdgcn_s_setprio(3);
+    double a = (double)F.Am[(int64_t)it.row * J + jl];
+    const double rb = F.pw.p[bs];
+    for (int r = 0; r <= rounds; ++r) {
+      if (r > 0) {
+        const int h = (r - 1) & 1, b0 = 3 * (r - 1);
+        Block<J, false> blk[2];
+        load_block<J, false>(lds.G[h][0], lds.L[h][0], i, g, blk[0]);
+        blk[0].xs = lds.x[h][0][i];
+        static_for<0, 3>([&](auto S) {
+          constexpr int q = decltype(S)::value;
+          if (b0 + q < nblk) {
+            if constexpr (q < 2) {  // (a slot past the last block holds an old one, which is not used)
+              load_block<J, false>(lds.G[h][q + 1], lds.L[h][q + 1], i, g, blk[(q + 1) & 1]);
+              blk[(q + 1) & 1].xs = lds.x[h][q + 1][i];
+            }
+            const int64_t left = pe - it.start - (int64_t)(b0 + q) * bs;
+            step_block<J, false>(blk[q & 1], F.gp, left >= bs ? rb : F.pw.p[left], a);
+          }
+        });
+      }
+      __syncthreads();
+    }
+    __builtin_amdgcn_s_setprio(0);
+    float* dst = it.kind == ITEM_LIGHT || F.hvec == nullptr ? F.Am + (int64_t)it.row * J : F.hvec + (int64_t)it.slot * J;
+    if (J >= 32 ? g < 2 : g == 0 && i < J) dst[jl] = (float)a;
+    return;
+  }
+  Src src;
+  src.idx = F.idx;
+  src.nnz = F.nnz;
+  src.val = F.val;
+  src.cp = F.cp;
+  src.fid = F.fid;
+  src.gfib = F.gfib;
+  src.nc = F.nc;
+  src.init(F.Bm, lane);
+  const float gpf = (float)F.gp, xscale = F.pw.inv[i];
+  const int step = 3 * bs;
+  int64_t p = it.start + (int64_t)(wave - 1) * bs;
+  typename Src::Idx ix0, ix1;
+  typename Src::Raw raw;
+  src.index(min(p, pe - 1), pe, ix0);
+  src.gather(ix0, raw);
+  src.index(min(p + step, pe - 1), pe, ix1);
+  for (int r = 0; r <= rounds; ++r) {
+    if (p < pe) {
+      const int nb = (int)min<int64_t>(bs, pe - p);
+      float G[Q::NG];
+      src.form(raw, nb, G);
+      const float x = ix0.x;
+      ix0 = ix1;
+      src.gather(ix0, raw);
+      src.index(min(p + 2 * step, pe - 1), pe, ix1);
+      store_block<J>(G, gpf, i, g, lds.G[r & 1][wave - 1], lds.L[r & 1][wave - 1]);
+      if (g == 0) lds.x[r & 1][wave - 1][i] = i < nb ? x * xscale : 0.f;
+      p += step;
+    }
+    __syncthreads();
+  }
+}
+
+template <int J>
+union FactorLds {
+  WaveLds<J> wave[4];
+  TeamLds<J> team;
+};
+
+// Short rows and relaxed chunks: one item per wavefront; the hardware
+// dispatcher balances the items (the lists are sorted by length, so that a
+// workgroup's four end together).  The first `teams` workgroups take a head
+// each, the items after the padded list of heads follow.
+template <int KIND, int N, int J, int R, class T, bool FIB, bool NC = false>
+__global__ __launch_bounds__(256) void k_factor_apply(const FItem* __restrict__ items, int64_t n_items, int64_t teams,
+                                                      FactorArgs<N, J, R, T, FIB, NC> F) {
+  __shared__ FactorLds<J> lds;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t b = blockIdx.x;
+  if (KIND == ITEM_CHAIN && b < teams) {
+    team_item(items[b], F, lds.team);
+    return;
+  }
+  const int64_t k = (teams + 3) / 4 * 4 + (b - teams) * 4 + wave;
+  if (k < n_items) factor_item<KIND>(items[k], F, lds.wave[wave]);
 }
 
 template <int N, int J, int R, class T, bool FIB, bool NC = false>
 __global__ __launch_bounds__(256, 3) void k_factor_compose(const FItem* __restrict__ items, int64_t n_items,
                                                         FactorArgs<N, J, R, T, FIB, NC> F) {
-  __shared__ WaveLds<J> lds[4];
+  __shared__ FactorLds<J> lds;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t k = (int64_t)blockIdx.x * 4 + wave;
-  if (k < n_items) factor_item<ITEM_MAP>(items[k], F, lds[wave]);
+  if (k < n_items) factor_item<ITEM_MAP>(items[k], F, lds.wave[wave]);
 }
 
 // The in-place items and the chunk maps of one exact factor pass in one
 // launch.  They are independent (a map starts from the identity, not from
-// its row's head).  The first head_blocks workgroups take the heads of the long
+// its row's head).  The first `teams` workgroups take the heads of the long
 // rows, the next map_blocks the chunk maps, the rest the short rows: the long
 // serial heads start at once and run while the maps keep the SIMDs busy, and
 // the short items fill in where the maps run out.
 template <int N, int J, int R, class T, bool FIB, bool NC = false>
-__global__ __launch_bounds__(256, 3) void k_factor_fused(int64_t head_blocks, int64_t map_blocks,
+__global__ __launch_bounds__(256, 3) void k_factor_fused(int64_t teams, int64_t map_blocks,
                                                       const FItem* __restrict__ apply_items, int64_t n_apply,
                                                       const FItem* __restrict__ compose_items, int64_t n_compose,
                                                       FactorArgs<N, J, R, T, FIB, NC> F) {
-  __shared__ WaveLds<J> lds[4];
+  __shared__ FactorLds<J> lds;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t b = blockIdx.x;
-  if (b < head_blocks || b >= head_blocks + map_blocks) {
-    const int64_t k = (b < head_blocks ? b : b - map_blocks) * 4 + wave;
-    if (k < n_apply) factor_item<ITEM_CHAIN>(apply_items[k], F, lds[wave]);
+  if (b < teams) {
+    team_item(apply_items[b], F, lds.team);
+  } else if (b < teams + map_blocks) {
+    const int64_t k = (b - teams) * 4 + wave;
+    if (k < n_compose) factor_item<ITEM_MAP>(compose_items[k], F, lds.wave[wave]);
   } else {
-    const int64_t k = (b - head_blocks) * 4 + wave;
-    if (k < n_compose) factor_item<ITEM_MAP>(compose_items[k], F, lds[wave]);
+    const int64_t k = (teams + 3) / 4 * 4 + (b - teams - map_blocks) * 4 + wave;
+    if (k < n_apply) factor_item<ITEM_CHAIN>(apply_items[k], F, lds.wave[wave]);
   }
 }
 
@@ -1031,6 +1148,8 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
   F.pw.p[0] = 1.0;
   for (int k = 1; k <= 16; ++k) F.pw.p[k] = F.pw.p[k - 1] * F.rho;
   for (int k = 0; k < 16; ++k) F.pw.inv[k] = k < F.block ? (float)(1.0 / F.pw.p[k]) : 0.f;
+  // the list of in-place items: n_team for a workgroup each (padded to a multiple of four), then one per wavefront
+  const unsigned apply_blocks = (unsigned)(M.n_team + (M.n_apply - (M.n_team + 3) / 4 * 4) / 4);
   if (FIB) {
     KTimer tm(P, FT_K_FIBER_G, s);
     const int64_t per_block = 4 * 16 * kFiberBlocks;  // fibers of a workgroup
@@ -1046,13 +1165,13 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
       F.hvec = nullptr;
       if (M.n_apply > 0) {
         KTimer tm(P, FT_K_FACTOR_APPLY, s);
-        hipLaunchKernelGGL((k_factor_apply<ITEM_CHAIN, N, J, R, T, FIB>), dim3(factor_blocks(M.n_apply)), dim3(256), 0,
-                           s, D.apply, M.n_apply, F);
+        hipLaunchKernelGGL((k_factor_apply<ITEM_CHAIN, N, J, R, T, FIB>), dim3(apply_blocks), dim3(256), 0, s,
+                           D.apply, M.n_apply, M.n_team, F);
       }
       if (M.n_compose > 0) {
         KTimer tm(P, FT_K_FACTOR_COMPOSE, s);
         hipLaunchKernelGGL((k_factor_apply<ITEM_RELAXED, N, J, R, T, FIB>), dim3(factor_blocks(M.n_compose)),
-                           dim3(256), 0, s, D.compose, M.n_compose, F);
+                           dim3(256), 0, s, D.compose, M.n_compose, 0, F);
       }
       if (M.n_relax > 0) {
         KTimer tm(P, FT_K_COMBINE, s);
@@ -1067,10 +1186,9 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
   }
   if (M.n_compose > 0 && M.n_apply > 0 && P->fused) {
     KTimer tm(P, FT_K_FACTOR_FUSED, s);
-    // the list of in-place items starts with the heads, padded to a multiple of four
-    const unsigned hb = factor_blocks(M.n_heavy), ab = factor_blocks(M.n_apply), mb = factor_blocks(M.n_compose);
-    hipLaunchKernelGGL((k_factor_fused<N, J, R, T, FIB, NC>), dim3(ab + mb), dim3(256), 0, s, (int64_t)hb, (int64_t)mb,
-                       D.apply, M.n_apply, D.compose, M.n_compose, F);
+    const unsigned mb = factor_blocks(M.n_compose);
+    hipLaunchKernelGGL((k_factor_fused<N, J, R, T, FIB, NC>), dim3(apply_blocks + mb), dim3(256), 0, s, M.n_team,
+                       (int64_t)mb, D.apply, M.n_apply, D.compose, M.n_compose, F);
   } else {
     if (M.n_compose > 0) {
       KTimer tm(P, FT_K_FACTOR_COMPOSE, s);
@@ -1079,8 +1197,8 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
     }
     if (M.n_apply > 0) {
       KTimer tm(P, FT_K_FACTOR_APPLY, s);
-      hipLaunchKernelGGL((k_factor_apply<ITEM_CHAIN, N, J, R, T, FIB, NC>), dim3(factor_blocks(M.n_apply)), dim3(256),
-                         0, s, D.apply, M.n_apply, F);
+      hipLaunchKernelGGL((k_factor_apply<ITEM_CHAIN, N, J, R, T, FIB, NC>), dim3(apply_blocks), dim3(256), 0, s,
+                         D.apply, M.n_apply, M.n_team, F);
     }
   }
   for (size_t L = 0; L < M.level_len.size(); ++L) {

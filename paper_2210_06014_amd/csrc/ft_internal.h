@@ -52,7 +52,7 @@ struct ModeHost {
   std::vector<float> val;         // nnz
   std::vector<int64_t> perm;      // nnz: CSR position -> input position
   std::vector<FItem> compose;     // COMPOSE items, padded to multiples of 4
-  std::vector<FItem> apply;       // HEAD then LIGHT items, padded to multiples of 4
+  std::vector<FItem> apply;       // HEAD items and longer LIGHT items, padded to a multiple of 4, then the others, padded
   std::vector<std::vector<CItem>> levels;
   std::vector<CItem> relax;       // FT_RELAXED: group items (chunk slots -> group record), then one merge item per
                                   // heavy row (its group records; out_off = elements after the head)
@@ -131,6 +131,7 @@ struct ModeMeta {
   int64_t I = 0;
   int64_t n_compose = 0;  // padded counts
   int64_t n_apply = 0;
+  int64_t n_team = 0;     // in-place items (heads, then longer rows) that a workgroup takes each
   int64_t n_heavy = 0;
   int64_t n_maps = 0;     // COMPOSE items (unpadded)
   std::vector<int64_t> level_off;  // offset of each level in the device array
@@ -192,6 +193,7 @@ constexpr int kPartials = 2048;  // max workgroups of the reduction kernels
 constexpr int kSegLen = 512;     // max elements per segment (ft_plan::seg_len)
 constexpr int kShortSeg = 32;    // rows of at most this many elements may be listed as short
 constexpr int kMinShort = 16384; // a mode with fewer of them lists none (one launch instead of two)
+constexpr int kTeamRow = 1024;   // rows longer than this are updated by a workgroup, shorter ones by a wavefront
 constexpr int kRelaxGroup = 256; // chunks per level-1 group of the relaxed merge
 
 // FT_RELAXED scratch in the map region: J + 1 floats per chunk slot, then

@@ -305,9 +305,13 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
   std::stable_sort(H.compose.begin(), H.compose.end(), [](const FItem& a, const FItem& b) { return a.len > b.len; });
   std::stable_sort(light.begin(), light.end(), [](const FItem& a, const FItem& b) { return a.len > b.len; });
   pad4(H.compose, ITEM_COMPOSE);
+  // heads, then short rows by descending length; a workgroup takes each item of the first part
   H.apply = head;
-  pad4(H.apply, ITEM_HEAD);
-  H.apply.insert(H.apply.end(), light.begin(), light.end());
+  auto rest = std::find_if(light.begin(), light.end(), [](const FItem& a) { return a.len <= kTeamRow; });
+  H.apply.insert(H.apply.end(), light.begin(), rest);
+  M.n_team = (int64_t)H.apply.size();
+  pad4(H.apply, ITEM_LIGHT);
+  H.apply.insert(H.apply.end(), rest, light.end());
   pad4(H.apply, ITEM_LIGHT);
 
   // combine levels: a heavy row whose maps number at most fanin has them
