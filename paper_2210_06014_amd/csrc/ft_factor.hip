@@ -787,6 +787,122 @@ __device__ __forceinline__ void team_item(const FItem& it, const FactorArgs<N, J
   }
 }
 
+// A pack: a block of 16 slots shared by whole short rows.  The rows' steps are
+// independent, so K is masked to pairs of one row; each slot reads its own
+// row's state, and the rows' sums of e~_t g_t are one product over the slots,
+// Delta^T = G^T (e~_s [row s = row t]).  (A row of five elements in a block of
+// its own costs as much as one of 16: order 4, 300k such rows, J = R = 32,
+// 554 -> 253 us per pass; Netflix-shaped 5M mode 0, J = R = 16: 279 -> 171.)  Rows share sums in
+// which another row's terms carry a factor 0, so a pack with a value that is
+// not finite is left alone (false): its rows are then taken one by one.
+template <int N, int J, int R, class T, bool FIB, bool NC>
+__device__ __forceinline__ bool pack_item(const Pack* __restrict__ pk, const FactorArgs<N, J, R, T, FIB, NC>& F,
+                                          WaveLds<J>& lds) {
+  using Q = Geo<J>;
+  using Src = Source<N, J, R, T, FIB, NC>;
+  const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+  Src src;
+  src.idx = F.idx;
+  src.nnz = F.nnz;
+  src.val = F.val;
+  src.cp = F.cp;
+  src.fid = F.fid;
+  src.gfib = F.gfib;
+  src.nc = F.nc;
+  src.init(F.Bm, lane);
+  const int n = pk->n;
+  typename Src::Idx ix;
+  typename Src::Raw raw;
+  src.index(pk->start, pk->start + n, ix);
+  src.gather(ix, raw);
+  const int row = pk->row[i], at = pk->at[i];
+  const int4 row4 = *reinterpret_cast<const int4*>(&pk->row[4 * g]);
+  const int rows[4] = {row4.x, row4.y, row4.z, row4.w};  // of slots 4 g + v
+  float* arow = F.Am + (int64_t)row * J + Q::jbase(g);
+  float as[Q::NG];
+#pragma unroll
+  for (int k = 0; k < Q::NG; ++k) as[k] = arow[k];
+  float G[Q::NG];
+  src.form(raw, n, G);
+  float u = G[0] * as[0];
+#pragma unroll
+  for (int k = 1; k < Q::NG; ++k) u = fmaf(G[k], as[k], u);
+  u = sum_rows(sum_halves(u));
+  wave_lds_fence();
+  float* grow = lds.G + i * Q::GS + Q::jbase(g);
+#pragma unroll
+  for (int k = 0; k < Q::NG; k += 2) *reinterpret_cast<floatx2*>(grow + k) = floatx2{G[k], G[k + 1]};
+  floatx4 K = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < Q::NG; ++k) K = __builtin_amdgcn_mfma_f32_16x16x4f32(G[k], G[k], K, 0, 0, 0);
+  const float gpf = (float)F.gp;
+  floatx4 Lw;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) Lw[v] = 4 * g + v < i && rows[v] == row ? -gpf * K[v] : 0.f;
+  *reinterpret_cast<floatx4*>(lds.L + i * Q::LS + 4 * g) = Lw;
+  wave_lds_fence();
+  float L[16];
+#pragma unroll
+  for (int s = 0; s < 16; s += 4) {
+    const floatx4 x = *reinterpret_cast<const floatx4*>(lds.L + i * Q::LS + s);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) L[s + v] = x[v];
+  }
+  // rho^-t and rho^count by the slot's place in its row: lane t holds the t-th power
+  const float xs = i < n ? ix.x * __shfl(F.pw.inv[i], at & 15) : 0.f;
+  const double rc = __shfl(F.pw.p[i < 15 ? i + 1 : 16], max((at >> 8) - 1, 0));
+  const float e = forward_substitute(xs - u, L);
+  if (__any(!(fabsf(e) <= 3.402823466e38f))) return false;
+  const float er = rotate_rows<12, 8, 4>(e);  // broadcast v gives lane row g slot 4 g + v
+  floatx4 d[Q::JT];
+#pragma unroll
+  for (int jt = 0; jt < Q::JT; ++jt) d[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
+  static_for<0, 4>([&](auto VV) {
+    constexpr int v = decltype(VV)::value;
+    const float ev = bcast16<v>(er);
+    const float em = rows[v] == row ? ev : 0.f;
+#pragma unroll
+    for (int jt = 0; jt < Q::JT; ++jt) {
+      const int j = Q::jmap(jt, i);
+      const float q = lds.G[(4 * g + v) * Q::GS + max(j, 0)];
+      d[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(j >= 0 ? q : 0.f, em, d[jt], 0, 0, 0);
+    }
+  });
+  if ((at & 255) == 0 && i < n) {
+#pragma unroll
+    for (int k = 0; k < Q::NG; ++k)
+      arow[k] = (float)(rc * fma(F.gp, (double)d[k / Q::VJ][k % Q::VJ], (double)as[k]));
+  }
+  return true;
+}
+
+// Entry k of the in-place items that a wavefront takes: a row, or past them a pack.
+template <int N, int J, int R, class T, bool FIB, bool NC>
+__device__ __forceinline__ void wave_items(int64_t k, const FItem* __restrict__ items, int64_t n_items,
+                                           const Pack* __restrict__ packs, int64_t n_packs,
+                                           const FactorArgs<N, J, R, T, FIB, NC>& F, WaveLds<J>& lds) {
+  FItem it{0, 0, 0, 0, ITEM_LIGHT};
+  const Pack* pk = nullptr;
+  int t = 0;
+  if (k < n_items) {
+    it = items[k];
+  } else {
+    if (k - n_items >= n_packs) return;
+    pk = packs + (k - n_items);
+    if (pack_item(pk, F, lds)) return;
+  }
+  for (;;) {
+    if (pk) {
+      it.start = pk->start + t;
+      it.len = pk->at[t] >> 8;
+      it.row = pk->row[t];
+      t += it.len;
+    }
+    factor_item<ITEM_CHAIN>(it, F, lds);
+    if (!pk || t >= pk->n) return;
+  }
+}
+
 template <int J>
 union FactorLds {
   WaveLds<J> wave[4];
@@ -799,6 +915,7 @@ union FactorLds {
 // each, the items after the padded list of heads follow.
 template <int KIND, int N, int J, int R, class T, bool FIB, bool NC = false>
 __global__ __launch_bounds__(256) void k_factor_apply(const FItem* __restrict__ items, int64_t n_items, int64_t teams,
+                                                      const Pack* __restrict__ packs, int64_t n_packs,
                                                       FactorArgs<N, J, R, T, FIB, NC> F) {
   __shared__ FactorLds<J> lds;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -808,7 +925,10 @@ __global__ __launch_bounds__(256) void k_factor_apply(const FItem* __restrict__ 
     return;
   }
   const int64_t k = (teams + 3) / 4 * 4 + (b - teams) * 4 + wave;
-  if (k < n_items) factor_item<KIND>(items[k], F, lds.wave[wave]);
+  if constexpr (KIND == ITEM_CHAIN)
+    wave_items(k, items, n_items, packs, n_packs, F, lds.wave[wave]);
+  else if (k < n_items)
+    factor_item<KIND>(items[k], F, lds.wave[wave]);
 }
 
 template <int N, int J, int R, class T, bool FIB, bool NC = false>
@@ -830,6 +950,7 @@ template <int N, int J, int R, class T, bool FIB, bool NC = false>
 __global__ __launch_bounds__(256, 3) void k_factor_fused(int64_t teams, int64_t map_blocks,
                                                       const FItem* __restrict__ apply_items, int64_t n_apply,
                                                       const FItem* __restrict__ compose_items, int64_t n_compose,
+                                                      const Pack* __restrict__ packs, int64_t n_packs,
                                                       FactorArgs<N, J, R, T, FIB, NC> F) {
   __shared__ FactorLds<J> lds;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -841,7 +962,7 @@ __global__ __launch_bounds__(256, 3) void k_factor_fused(int64_t teams, int64_t 
     if (k < n_compose) factor_item<ITEM_MAP>(compose_items[k], F, lds.wave[wave]);
   } else {
     const int64_t k = (teams + 3) / 4 * 4 + (b - teams - map_blocks) * 4 + wave;
-    if (k < n_apply) factor_item<ITEM_CHAIN>(apply_items[k], F, lds.wave[wave]);
+    wave_items(k, apply_items, n_apply, packs, n_packs, F, lds.wave[wave]);
   }
 }
 
@@ -1148,8 +1269,10 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
   F.pw.p[0] = 1.0;
   for (int k = 1; k <= 16; ++k) F.pw.p[k] = F.pw.p[k - 1] * F.rho;
   for (int k = 0; k < 16; ++k) F.pw.inv[k] = k < F.block ? (float)(1.0 / F.pw.p[k]) : 0.f;
-  // the list of in-place items: n_team for a workgroup each (padded to a multiple of four), then one per wavefront
-  const unsigned apply_blocks = (unsigned)(M.n_team + (M.n_apply - (M.n_team + 3) / 4 * 4) / 4);
+  // the list of in-place items: n_team for a workgroup each (padded to a multiple of four), then one per wavefront,
+  // the shortest rows as packs (or, where blocks are single elements, on their own)
+  const int64_t n_packs = F.block == 16 ? M.n_packs : 0, n_apply = n_packs > 0 ? M.n_wave : M.n_apply;
+  const unsigned apply_blocks = (unsigned)(M.n_team + (n_apply - (M.n_team + 3) / 4 * 4) / 4 + (n_packs + 3) / 4);
   if (FIB) {
     KTimer tm(P, FT_K_FIBER_G, s);
     const int64_t per_block = 4 * 16 * kFiberBlocks;  // fibers of a workgroup
@@ -1166,12 +1289,12 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
       if (M.n_apply > 0) {
         KTimer tm(P, FT_K_FACTOR_APPLY, s);
         hipLaunchKernelGGL((k_factor_apply<ITEM_CHAIN, N, J, R, T, FIB>), dim3(apply_blocks), dim3(256), 0, s,
-                           D.apply, M.n_apply, M.n_team, F);
+                           D.apply, n_apply, M.n_team, D.packs, n_packs, F);
       }
       if (M.n_compose > 0) {
         KTimer tm(P, FT_K_FACTOR_COMPOSE, s);
         hipLaunchKernelGGL((k_factor_apply<ITEM_RELAXED, N, J, R, T, FIB>), dim3(factor_blocks(M.n_compose)),
-                           dim3(256), 0, s, D.compose, M.n_compose, 0, F);
+                           dim3(256), 0, s, D.compose, M.n_compose, 0, nullptr, 0, F);
       }
       if (M.n_relax > 0) {
         KTimer tm(P, FT_K_COMBINE, s);
@@ -1188,7 +1311,7 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
     KTimer tm(P, FT_K_FACTOR_FUSED, s);
     const unsigned mb = factor_blocks(M.n_compose);
     hipLaunchKernelGGL((k_factor_fused<N, J, R, T, FIB, NC>), dim3(apply_blocks + mb), dim3(256), 0, s, M.n_team,
-                       (int64_t)mb, D.apply, M.n_apply, D.compose, M.n_compose, F);
+                       (int64_t)mb, D.apply, n_apply, D.compose, M.n_compose, D.packs, n_packs, F);
   } else {
     if (M.n_compose > 0) {
       KTimer tm(P, FT_K_FACTOR_COMPOSE, s);
@@ -1198,7 +1321,7 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
     if (M.n_apply > 0) {
       KTimer tm(P, FT_K_FACTOR_APPLY, s);
       hipLaunchKernelGGL((k_factor_apply<ITEM_CHAIN, N, J, R, T, FIB, NC>), dim3(apply_blocks), dim3(256), 0, s,
-                         D.apply, M.n_apply, M.n_team, F);
+                         D.apply, n_apply, M.n_team, D.packs, n_packs, F);
     }
   }
   for (size_t L = 0; L < M.level_len.size(); ++L) {

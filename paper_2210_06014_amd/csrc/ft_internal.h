@@ -25,6 +25,17 @@ struct FItem {
 };
 static_assert(sizeof(FItem) == 24, "FItem layout");
 
+// A block of whole short rows, consecutive in the CSR: slot t holds element
+// start + t of row[t], the at[t] & 255-th of its row's at[t] >> 8 elements.
+struct Pack {
+  int64_t start;
+  int32_t n;      // elements (at most 16)
+  int32_t pad;
+  int32_t row[16];
+  int32_t at[16];
+};
+static_assert(sizeof(Pack) == 144, "Pack layout");
+
 // One step of the combine reduction: fold `count` consecutive maps starting
 // at in_off (in order) into one; write it to out_off, or if out_off < 0
 // apply it to the head vector `heavy` and write row `row` of A(m).
@@ -53,6 +64,7 @@ struct ModeHost {
   std::vector<int64_t> perm;      // nnz: CSR position -> input position
   std::vector<FItem> compose;     // COMPOSE items, padded to multiples of 4
   std::vector<FItem> apply;       // HEAD items and longer LIGHT items, padded to a multiple of 4, then the others, padded
+  std::vector<Pack> packs;        // the rows of at most kPackRow elements, which are also the last of `apply`
   std::vector<std::vector<CItem>> levels;
   std::vector<CItem> relax;       // FT_RELAXED: group items (chunk slots -> group record), then one merge item per
                                   // heavy row (its group records; out_off = elements after the head)
@@ -74,6 +86,7 @@ struct ModeDev {
   int32_t* perm = nullptr;  // device permutation (int32: nnz < 2^31 required with FT_WITH_PERM)
   FItem* compose = nullptr;
   FItem* apply = nullptr;
+  Pack* packs = nullptr;
   CItem* levels = nullptr;  // all levels back to back
   CItem* relax = nullptr;
   Seg* segs = nullptr;
@@ -87,7 +100,7 @@ struct ModeDev {
 // Byte offsets of a mode's arrays in the caller's plan workspace (SIZE_MAX:
 // the array is empty and its device pointer stays null).
 struct ModeOff {
-  size_t row_ptr, idx, val, perm, compose, apply, levels, relax, segs, seg_first, fid, fib_idx, fidx, fval;
+  size_t row_ptr, idx, val, perm, compose, apply, packs, levels, relax, segs, seg_first, fid, fib_idx, fidx, fval;
 };
 
 // Every array in a device workspace starts on this boundary.
@@ -131,6 +144,8 @@ struct ModeMeta {
   int64_t I = 0;
   int64_t n_compose = 0;  // padded counts
   int64_t n_apply = 0;
+  int64_t n_packs = 0;
+  int64_t n_wave = 0;     // entries of the apply list before the rows that packs cover (a multiple of 4)
   int64_t n_team = 0;     // in-place items (heads, then longer rows) that a workgroup takes each
   int64_t n_heavy = 0;
   int64_t n_maps = 0;     // COMPOSE items (unpadded)
@@ -194,6 +209,7 @@ constexpr int kSegLen = 512;     // max elements per segment (ft_plan::seg_len)
 constexpr int kShortSeg = 32;    // rows of at most this many elements may be listed as short
 constexpr int kMinShort = 16384; // a mode with fewer of them lists none (one launch instead of two)
 constexpr int kTeamRow = 1024;   // rows longer than this are updated by a workgroup, shorter ones by a wavefront
+constexpr int kPackRow = 16;      // rows of at most this many elements share blocks of 16
 constexpr int kRelaxGroup = 256; // chunks per level-1 group of the relaxed merge
 
 // FT_RELAXED scratch in the map region: J + 1 floats per chunk slot, then

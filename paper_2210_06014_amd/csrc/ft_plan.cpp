@@ -311,8 +311,33 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
   H.apply.insert(H.apply.end(), light.begin(), rest);
   M.n_team = (int64_t)H.apply.size();
   pad4(H.apply, ITEM_LIGHT);
-  H.apply.insert(H.apply.end(), rest, light.end());
+  auto packed = std::find_if(rest, light.end(), [](const FItem& a) { return a.len <= kPackRow; });
+  H.apply.insert(H.apply.end(), rest, packed);
   pad4(H.apply, ITEM_LIGHT);
+  M.n_wave = (int64_t)H.apply.size();
+  H.apply.insert(H.apply.end(), packed, light.end());
+  pad4(H.apply, ITEM_LIGHT);
+  // packs of the rows of at most kPackRow elements: neighbours in the CSR
+  // while they fit into 16 slots
+  for (int64_t i = 0; i < I; ++i) {
+    const int64_t s = H.row_ptr[i], L = H.row_ptr[i + 1] - s;
+    if (L == 0 || L > kPackRow || L > hl) continue;
+    if (H.packs.empty() || H.packs.back().start + H.packs.back().n != s || H.packs.back().n + L > 16) {
+      H.packs.push_back(Pack{});
+      H.packs.back().start = s;
+      for (int t = 0; t < 16; ++t) H.packs.back().row[t] = (int32_t)i;
+    }
+    Pack& q = H.packs.back();
+    for (int64_t t = 0; t < L; ++t) {
+      q.row[q.n] = (int32_t)i;
+      q.at[q.n++] = (int32_t)(t | L << 8);
+    }
+    for (int t = q.n; t < 16; ++t) {  // unused slots: no row's (at most the last row's number, count 0)
+      q.row[t] = (int32_t)i;
+      q.at[t] = 0xFF;
+    }
+  }
+  M.n_packs = (int64_t)H.packs.size();
 
   // combine levels: a heavy row whose maps number at most fanin has them
   // applied in sequence to its head vector (a final item); a longer row first
@@ -476,6 +501,7 @@ static void layout(ft_plan* P) {
     o.perm = L.add(perm ? H.perm.size() * sizeof(int32_t) : 0);
     o.compose = L.add(H.compose.size() * sizeof(FItem));
     o.apply = L.add(H.apply.size() * sizeof(FItem));
+    o.packs = L.add(H.packs.size() * sizeof(Pack));
     o.levels = L.add(nlev * sizeof(CItem));
     o.relax = L.add(P->relaxed ? H.relax.size() * sizeof(CItem) : 0);
     o.segs = L.add(H.segs.size() * sizeof(Seg));
@@ -680,6 +706,7 @@ extern "C" ft_status ft_plan_upload(ft_plan* P, void* ws, size_t ws_bytes, void*
     if (e == hipSuccess) e = copy_in(ws, o.perm, perm32[m], s);
     if (e == hipSuccess) e = copy_in(ws, o.compose, H.compose, s);
     if (e == hipSuccess) e = copy_in(ws, o.apply, H.apply, s);
+    if (e == hipSuccess) e = copy_in(ws, o.packs, H.packs, s);
     if (e == hipSuccess) e = copy_in(ws, o.levels, levels[m], s);
     if (e == hipSuccess) e = copy_in(ws, o.relax, H.relax, s);
     if (e == hipSuccess) e = copy_in(ws, o.segs, H.segs, s);
@@ -701,6 +728,7 @@ extern "C" ft_status ft_plan_upload(ft_plan* P, void* ws, size_t ws_bytes, void*
     D.perm = at<int32_t>(ws, o.perm);
     D.compose = at<FItem>(ws, o.compose);
     D.apply = at<FItem>(ws, o.apply);
+    D.packs = at<Pack>(ws, o.packs);
     D.levels = at<CItem>(ws, o.levels);
     D.relax = at<CItem>(ws, o.relax);
     D.segs = at<Seg>(ws, o.segs);
