@@ -111,7 +111,11 @@ typedef struct {
                                    quarter of its elements and whose serial chain a cost model of the
                                    launch (from the row lengths and whether g is shared per fiber)
                                    expects to end within the launch.  ft_plan_mode_info reports the
-                                   value each mode uses */
+                                   value each mode uses.  Where chunk and head are both 0, J >= 32 and the
+                                   plan is not FT_RELAXED, the in-place part of a long row may reach
+                                   further, by whole chunks, where a second estimate (of the launch with
+                                   a workgroup per long row) has its chain end in time; ft_mode_info
+                                   counts the pieces that result */
   int32_t fanin;                /* chunk maps folded per combine step (0 or above the maximum: 16); a row with
                                    at most fanin maps has them applied in sequence to its head's result */
   int32_t flags;                /* FT_KEEP_HOST | FT_WITH_PERM | FT_NO_FIBER_SHARE | FT_NO_C_CACHE | FT_RELAXED |
@@ -150,7 +154,7 @@ typedef struct {
   int64_t rows;          /* I_m */
   int64_t nonempty_rows; /* rows with at least one element */
   int64_t max_row;       /* largest row length */
-  int64_t light_rows;    /* rows of at most `head` elements, updated in one piece */
+  int64_t light_rows;    /* rows updated in one piece (of at most `head` elements; see ft_desc.head) */
   int64_t heavy_rows;    /* longer rows: a head plus chunks */
   int64_t chunks;        /* pieces of heavy rows, heads included */
   int64_t segments;      /* pieces of rows used by the core, loss and gradient passes */

@@ -272,10 +272,51 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
     }
   }
 
-  // factor work lists: a row of at most `head` elements is one serial item;
-  // a longer row is a head item (its first `head` elements, updated in
+  // In-place length of a plan that leaves chunk and head to the library, J = 32:
+  // a workgroup updates the in-place part of a long row, and a chunk map's
+  // element costs two and a half times of a chain's, so that part reaches past
+  // `head`, by whole chunks, to where the launch is estimated shortest: the
+  // longer of its longest chain (about 35 ns per element beside other work, 21
+  // alone) and of its work, 31 (45 with g formed per element) ps per chain
+  // element and 76 (90) per map element.  A chunk's map is itself about 200 us
+  // of one wavefront's time; it starts beside the chains where these leave room
+  // (512 workgroups of the 768 to 1024 that are resident), after them otherwise.
+  // 1000 rows of 8000 elements, g shared: 471 -> 252 us per pass (no maps);
+  // Netflix-shaped 8M, modes 0-2: 411 -> 370, 518 -> 505, 603 -> 580.  At
+  // J <= 16 a map element costs little more than a chain element, and a longer
+  // head gained nothing.
+  int64_t reach = M.head;
+  if (P->desc.chunk == 0 && P->desc.head == 0 && !P->relaxed && P->J >= 32) {
+    const bool shares_g = fiber_share(P->desc.flags, M.n_fibers, nnz);
+    const double cc = shares_g ? 31e-6 : 45e-6, cm = shares_g ? 76e-6 : 90e-6, step = 35e-3;  // us
+    int64_t maxL = 0, n_team = 0;
+    for (int64_t i = 0; i < I; ++i) {
+      maxL = std::max(maxL, H.row_ptr[i + 1] - H.row_ptr[i]);
+      n_team += H.row_ptr[i + 1] - H.row_ptr[i] > kTeamRow;
+    }
+    double best = 0.0;
+    for (int64_t r = M.head;; r += std::max<int64_t>(P->chunk, r / 8 / P->chunk * P->chunk)) {
+      const double chain = step * (double)std::min(r, maxL);
+      if (r > M.head && chain >= best) break;  // the chain only grows
+      double work = 0.0;
+      for (int64_t i = 0; i < I; ++i) {
+        const int64_t L = H.row_ptr[i + 1] - H.row_ptr[i];
+        work += cc * (double)std::min(L, r) + cm * (double)std::max<int64_t>(L - r, 0);
+      }
+      const double after = r < maxL && n_team > 512 ? 200.0 * (double)P->chunk / 1024 : 0.0;
+      const double t = std::max(chain + after, work);
+      if (r == M.head || t < best) {
+        best = t;
+        reach = r;
+      }
+      if (r >= maxL) break;
+    }
+  }
+
+  // factor work lists: a row of at most `reach` elements is one serial item;
+  // a longer row is a head item (its first `reach` elements, updated in
   // place) followed by chunk items whose maps the combine applies in order
-  const int64_t chunk = P->chunk, hl = M.head;
+  const int64_t chunk = P->chunk, hl = reach;
   std::vector<FItem> light, head;
   int64_t n_heavy = 0, n_maps = 0, max_row = 0, nonempty = 0;
   std::vector<int64_t> heavy_rows, heavy_base, heavy_nmaps;
