@@ -565,7 +565,7 @@ static void layout(ft_plan* P) {
   so.maps = S.add((size_t)std::max<int64_t>(map_floats, 1) * sizeof(float));
   so.map_scale = S.add((size_t)max_slots * sizeof(double));
   so.hvec = S.add((size_t)max_heavy * J * sizeof(float));
-  so.partials = S.add((size_t)(kPartials + kPartials / 32 + 1) * J * R * sizeof(float));
+  so.partials = S.add((size_t)kPartials * J * R * sizeof(float));
   so.dpartials = S.add(((size_t)kPartials + 2 * FT_MAX_ORDER * 256) * sizeof(double));
   so.tseg = S.add((size_t)max_segs * R * sizeof(float));
   so.gfib = S.add((size_t)max_fib * J * sizeof(float));

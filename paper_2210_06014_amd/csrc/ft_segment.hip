@@ -729,40 +729,35 @@ __global__ __launch_bounds__(256) void k_core_nc(const Seg* __restrict__ segs, i
   }
 }
 
-// Sum of the workgroup partials in a fixed order, in two stages.  First kFold
-// slices of the partials, each over all of J x R: a workgroup takes 64 entries
-// of one slice, its four wavefronts every fourth partial, so that a slice of
-// 2048 / kFold partials is four chains of independent loads instead of one
-// chain per entry of the whole list (1024 partials of 32 x 32: 31 us -> 5 us).
-// Then the kFold sums, in order.
+// Sum of the workgroup partials in a fixed order, then optionally the core
+// step B <- B + lr (G / |Omega| - lam B) (Algorithm 5).  A workgroup takes 16
+// entries of J x R and sums the partials in 64 chains of 16 lanes: kFold
+// slices, four chains per slice, each over every fourth partial of its slice,
+// so that 2048 partials are 32 independent loads per lane.  Bound by the
+// latency of these loads and by the launch itself: as two launches, slices
+// over all entries first, 5 + 5 us at any size; as one launch of 16 entries per
+// workgroup 5 us (the same sums in the same order).
 constexpr int kFold = 16;
 
-__global__ __launch_bounds__(256) void k_fold_partials(const float* __restrict__ partials, int nparts, int JR,
-                                                       float* __restrict__ folded) {
-  __shared__ float red[4][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int e = blockIdx.x * 64 + lane;  // JR is a multiple of 64
-  const int per = (nparts + kFold - 1) / kFold;
-  const int b0 = blockIdx.y * per, b1 = min(nparts, b0 + per);
-  float s = 0.f;
-#pragma unroll 8
-  for (int b = b0 + wave; b < b1; b += 4) s += partials[(int64_t)b * JR + e];
-  red[wave][lane] = s;
-  __syncthreads();
-  if (wave == 0) folded[(int64_t)blockIdx.y * JR + e] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
-}
-
-// Final sum; optionally the core step B <- B + lr (G / |Omega| - lam B) (Algorithm 5).
-__global__ __launch_bounds__(64) void k_reduce_update(const float* __restrict__ folded, int JR,
+__global__ __launch_bounds__(1024) void k_fold_update(const float* __restrict__ partials, int nparts, int JR,
                                                       float* __restrict__ Bm, float* __restrict__ Gout, float lr,
                                                       float lam, float inv_nnz, int update) {
-  const int e = blockIdx.x * 64 + threadIdx.x;
-  float f[kFold];
-#pragma unroll
-  for (int b = 0; b < kFold; ++b) f[b] = folded[(int64_t)b * JR + e];
+  __shared__ float red[4 * kFold][16], fold[kFold][16];
+  const int c = threadIdx.x & 15, q = threadIdx.x >> 4;
+  const int e = blockIdx.x * 16 + c;  // JR is a multiple of 64
+  const int per = (nparts + kFold - 1) / kFold;
+  const int b0 = (q >> 2) * per, b1 = min(nparts, b0 + per);
   float s = 0.f;
+#pragma unroll 16
+  for (int b = b0 + (q & 3); b < b1; b += 4) s += partials[(int64_t)b * JR + e];
+  red[q][c] = s;
+  __syncthreads();
+  if (q < kFold) fold[q][c] = ((red[4 * q][c] + red[4 * q + 1][c]) + red[4 * q + 2][c]) + red[4 * q + 3][c];
+  __syncthreads();
+  if (q > 0) return;
+  s = 0.f;
 #pragma unroll
-  for (int b = 0; b < kFold; ++b) s += f[b];
+  for (int b = 0; b < kFold; ++b) s += fold[b][c];
   if (Gout) Gout[e] = s;
   if (update) {
     const float b = Bm[e];
@@ -1020,10 +1015,8 @@ hipError_t reduce_partials(const ft_plan* P, const Scratch& S, int nparts, float
                            float lam, float inv, int update, hipStream_t s) {
   KTimer tm(P, FT_K_REDUCE, s);
   const int JR = P->J * P->R;
-  static_assert(kFold <= kPartials / 32 + 1, "the scratch layout holds kPartials / 32 + 1 folded sums");
-  float* folded = S.partials + (int64_t)kPartials * JR;
-  hipLaunchKernelGGL(k_fold_partials, dim3(JR / 64, kFold), dim3(256), 0, s, S.partials, nparts, JR, folded);
-  hipLaunchKernelGGL(k_reduce_update, dim3(JR / 64), dim3(64), 0, s, folded, JR, Bm, Gout, lr, lam, inv, update);
+  hipLaunchKernelGGL(k_fold_update, dim3(JR / 16), dim3(64 * kFold), 0, s, S.partials, nparts, JR, Bm, Gout, lr, lam,
+                     inv, update);
   return hipGetLastError();
 }
 
