@@ -111,7 +111,7 @@ typedef struct {
                                    quarter of its elements and whose serial chain a cost model of the
                                    launch (from the row lengths and whether g is shared per fiber)
                                    expects to end within the launch.  ft_plan_mode_info reports the
-                                   value each mode uses.  Where chunk and head are both 0, J >= 32 and the
+                                   value each mode uses.  Where chunk and head are both 0, J >= 16 and the
                                    plan is not FT_RELAXED, the in-place part of a long row may reach
                                    further, by whole chunks, where a second estimate (of the launch with
                                    a workgroup per long row) has its chain end in time; ft_mode_info

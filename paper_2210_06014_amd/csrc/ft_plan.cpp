@@ -272,23 +272,30 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
     }
   }
 
-  // In-place length of a plan that leaves chunk and head to the library, J = 32:
+  // In-place length of a plan that leaves chunk and head to the library, J >= 16:
   // a workgroup updates the in-place part of a long row, and a chunk map's
-  // element costs two and a half times of a chain's, so that part reaches past
-  // `head`, by whole chunks, to where the launch is estimated shortest: the
-  // longer of its longest chain (about 35 ns per element beside other work, 21
-  // alone) and of its work, 31 (45 with g formed per element) ps per chain
-  // element and 76 (90) per map element.  A chunk's map is itself about 200 us
-  // of one wavefront's time; it starts beside the chains where these leave room
-  // (512 workgroups of the 768 to 1024 that are resident), after them otherwise.
-  // 1000 rows of 8000 elements, g shared: 471 -> 252 us per pass (no maps);
-  // Netflix-shaped 8M, modes 0-2: 411 -> 370, 518 -> 505, 603 -> 580.  At
-  // J <= 16 a map element costs little more than a chain element, and a longer
-  // head gained nothing.
+  // element costs up to two and a half times of a chain's, so that part reaches
+  // past `head`, by whole chunks, to where the launch is estimated shortest: the
+  // longer of its longest chain (per element 35 ns beside other work, 20 alone;
+  // a quarter more at 100,000 elements) and of its work, in ps per chain and per
+  // map element 31 and 76 (45 and 90 with g formed per element) at J = 32, 19
+  // and 32 (23 and 36) at J = 16, there with 20 us for its ends.  A chunk's map
+  // is itself about 200 us of one wavefront's time; it starts beside the chains
+  // where these leave room (512 workgroups of the 768 to 1024 that are
+  // resident), after them otherwise.  Fitted to launches of Netflix-shaped
+  // tensors: the best length at J = 32 is 8192 to 12288 for 8M elements (500,
+  // 500, 560 us for modes 0 to 2, combine included, against 544, 542, 615 at
+  // 2048) and 32768 for 30M (1817 us, 2162 at 2048, 2239 at 65536), at J = 16
+  // 4096 for 5M and 24576 for 30M (893 us; 988 and 1599).  1000 rows of 8000
+  // elements, J = 32, g shared: 471 -> 252 us per pass (no maps).  At J = 8 a
+  // map element costs little more than a chain element.
   int64_t reach = M.head;
-  if (P->desc.chunk == 0 && P->desc.head == 0 && !P->relaxed && P->J >= 32) {
+  if (P->desc.chunk == 0 && P->desc.head == 0 && !P->relaxed && P->J >= 16) {
     const bool shares_g = fiber_share(P->desc.flags, M.n_fibers, nnz);
-    const double cc = shares_g ? 31e-6 : 45e-6, cm = shares_g ? 76e-6 : 90e-6, step = 35e-3;  // us
+    const bool wide = P->J >= 32;
+    const double step = 35e-3, ends = wide ? 0.0 : 20.0;  // us
+    const double cc = wide ? (shares_g ? 31e-6 : 45e-6) : (shares_g ? 19e-6 : 23e-6);
+    const double cm = wide ? (shares_g ? 76e-6 : 90e-6) : (shares_g ? 32e-6 : 36e-6);
     int64_t maxL = 0, n_team = 0;
     for (int64_t i = 0; i < I; ++i) {
       maxL = std::max(maxL, H.row_ptr[i + 1] - H.row_ptr[i]);
@@ -296,9 +303,9 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
     }
     double best = 0.0;
     for (int64_t r = M.head;; r += std::max<int64_t>(P->chunk, r / 8 / P->chunk * P->chunk)) {
-      const double chain = step * (double)std::min(r, maxL);
+      const double rc = (double)std::min(r, maxL), chain = step * rc * (1.0 + rc / 400e3);
       if (r > M.head && chain >= best) break;  // the chain only grows
-      double work = 0.0;
+      double work = ends;
       for (int64_t i = 0; i < I; ++i) {
         const int64_t L = H.row_ptr[i + 1] - H.row_ptr[i];
         work += cc * (double)std::min(L, r) + cm * (double)std::max<int64_t>(L - r, 0);
