@@ -80,7 +80,8 @@ def algorithmic(w, nnz, row_counts, heads, fibers, relaxed=False, sp=4):
             c_share = 0.0
         out["factor_compose"][0] += comp * f_elem
         # executed on top: the chunk map's matrix part, a J x J matrix-vector
-        # product and a rank-1 update per element (4 J^2 flops)
+        # product and a rank-1 update per element (4 J^2 flops).  An upper bound:
+        # the in-place part of a long row may reach past the head reported here
         out["compose_executed"][0] += comp * (f_elem + (2 * J if relaxed else 4 * J * J))
         out["factor_compose"][1] += comp * e_bytes + c_share * comp / max(nnz, 1)
         out["factor_apply"][0] += app * f_elem
