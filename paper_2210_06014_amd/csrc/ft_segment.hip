@@ -766,10 +766,18 @@ __global__ __launch_bounds__(1024) void k_fold_update(const float* __restrict__ 
 }
 
 // dA(m)[i, j] = sum_r B(m)[j, r] t_i[r], t_i = sum of the row's segment sums:
-// 16 rows per wavefront, a lane summing a slice of one row's segments, eight
-// loads in flight, and B t on the matrix cores.  (A thread per entry read the
-// row's sums J times and a long row's one load after another: 100k rows, J = R
-// = 16, 49 -> 13 us.)
+// 16 rows per wavefront, lane (i, g) summing a slice of row i's segments, and
+// B t on the matrix cores.  The segment sums are added in FP64, so that a
+// row's error is that of its segments (FP32, at most 512 elements each)
+// however many it has: added in FP32, 678 segments of 192 elements had twice
+// the error of the same row in 254 of 512.  What bounds the launch is the
+// latency of the longest row's loads: eight are in flight, and a row of more
+// than kSerialSegs segments is summed by the whole wavefront, 16 segments at a
+// time and then over 16 lanes in a fixed tree (about 2 us a row, which fewer
+// segments do not repay: with 16 in place of 128, 40 us).  Planted shape, 1M
+// elements, J = R = 16, us per mode: 26 in one chain per row, 19 so.
+constexpr int kSerialSegs = 128;
+
 template <int J, int R, class T>
 __global__ __launch_bounds__(256) void k_grad_rows(const int64_t* __restrict__ seg_first,
                                                    const int64_t* __restrict__ row_ptr,
@@ -782,17 +790,47 @@ __global__ __launch_bounds__(256) void k_grad_rows(const int64_t* __restrict__ s
   GForm<J, R, T> gf;
   gf.load(Bm, i, g);
   const int64_t rc = min(row, I - 1);
-  const int64_t n = row < I ? (row_ptr[rc + 1] - row_ptr[rc] + seg_len - 1) / seg_len : 0;
-  const float* src = tseg + seg_first[rc] * R + KR * g;
-  float t[KR];
+  const int n = row < I ? (int)((row_ptr[rc + 1] - row_ptr[rc] + seg_len - 1) / seg_len) : 0;
+  const int64_t first = seg_first[rc];
+  double t[KR];
 #pragma unroll
-  for (int c = 0; c < KR; ++c) t[c] = 0.f;
-#pragma unroll 8
-  for (int64_t k = 0; k < n; ++k)
+  for (int c = 0; c < KR; ++c) t[c] = 0.0;
+  // segment sums k0, k0 + step, ... below count, eight loads in flight
+  auto add = [&](const float* src, int k0, int step, int count, double (&s)[KR]) {
+    for (int k = k0; k < count; k += 8 * step) {
+      float x[8][KR];
 #pragma unroll
-    for (int c = 0; c < KR; ++c) t[c] += src[k * R + c];
-  float G[JLayout<J>::NG];
-  gf.form(t, G);
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int c = 0; c < KR; ++c) x[u][c] = src[(int64_t)min(k + u * step, count - 1) * R + c];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int c = 0; c < KR; ++c) s[c] += k + u * step < count ? (double)x[u][c] : 0.0;
+    }
+  };
+  add(tseg + first * R + KR * g, 0, 1, n <= kSerialSegs ? n : 0, t);
+  // (the four lanes of a row agree on n; the low 16 bits are those of the lanes of g = 0)
+  for (uint32_t todo = (uint32_t)__ballot(n > kSerialSegs) & 0xFFFFu; todo; todo &= todo - 1) {
+    const int r = __builtin_ctz(todo);
+    const int nr = __shfl(n, r);
+    const float* src = tseg + (int64_t)__shfl(first, r) * R + KR * g;
+    double s[KR];
+#pragma unroll
+    for (int c = 0; c < KR; ++c) s[c] = 0.0;
+    add(src, i, 16, nr, s);
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1)
+#pragma unroll
+      for (int c = 0; c < KR; ++c) s[c] += __shfl_xor(s[c], off);
+    if (i == r)
+#pragma unroll
+      for (int c = 0; c < KR; ++c) t[c] = s[c];
+  }
+  float tf[KR], G[JLayout<J>::NG];
+#pragma unroll
+  for (int c = 0; c < KR; ++c) tf[c] = (float)t[c];
+  gf.form(tf, G);
   if (row < I)
 #pragma unroll
     for (int k = 0; k < JLayout<J>::NG; ++k) gA[row * J + JLayout<J>::jbase(g) + k] = G[k];
