@@ -269,6 +269,17 @@ int resident_blocks(const void* kernel) {
   return r;
 }
 
+// A launch holds fewer than 2^32 threads along x: more than 2^24 - 1 workgroups
+// of 256 threads (a wavefront per item: 67 million items) take a second grid
+// dimension.  Kernels read their workgroup with block_id(); numbers from
+// `blocks` on, which fill up the last y, lie past every list.
+dim3 block_grid(int64_t blocks) {
+  constexpr int64_t most = (int64_t)1 << 23;
+  if (blocks < ((int64_t)1 << 24)) return dim3((unsigned)blocks);
+  return dim3((unsigned)most, (unsigned)((blocks + most - 1) / most));
+}
+__device__ __forceinline__ int64_t block_id() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 bool bf16(const ft_params* p) { return p->storage == FT_STORE_BF16; }
 
 #define FT_DISPATCH(CALL)                                            \

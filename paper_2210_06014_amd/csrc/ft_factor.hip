@@ -919,7 +919,7 @@ __global__ __launch_bounds__(256) void k_factor_apply(const FItem* __restrict__ 
                                                       FactorArgs<N, J, R, T, FIB, NC> F) {
   __shared__ FactorLds<J> lds;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t b = blockIdx.x;
+  const int64_t b = block_id();
   if (KIND == ITEM_CHAIN && b < teams) {
     team_item(items[b], F, lds.team);
     return;
@@ -936,7 +936,7 @@ __global__ __launch_bounds__(256, 3) void k_factor_compose(const FItem* __restri
                                                         FactorArgs<N, J, R, T, FIB, NC> F) {
   __shared__ FactorLds<J> lds;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t k = (int64_t)blockIdx.x * 4 + wave;
+  const int64_t k = block_id() * 4 + wave;
   if (k < n_items) factor_item<ITEM_MAP>(items[k], F, lds.wave[wave]);
 }
 
@@ -954,7 +954,7 @@ __global__ __launch_bounds__(256, 3) void k_factor_fused(int64_t teams, int64_t 
                                                       FactorArgs<N, J, R, T, FIB, NC> F) {
   __shared__ FactorLds<J> lds;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t b = blockIdx.x;
+  const int64_t b = block_id();
   if (b < teams) {
     team_item(apply_items[b], F, lds.team);
   } else if (b < teams + map_blocks) {
@@ -1236,7 +1236,7 @@ __global__ __launch_bounds__(256) void k_relaxed_merge(const CItem* __restrict__
 }
 
 // workgroups of four items, one per wavefront
-unsigned factor_blocks(int64_t n_items) { return (unsigned)((n_items + 3) / 4); }
+int64_t factor_blocks(int64_t n_items) { return (n_items + 3) / 4; }
 
 template <int N, int J, int R, class T, bool FIB, bool NC = false>
 hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scratch& S, double lr, double lam,
@@ -1272,7 +1272,7 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
   // the list of in-place items: n_team for a workgroup each (padded to a multiple of four), then one per wavefront,
   // the shortest rows as packs (or, where blocks are single elements, on their own)
   const int64_t n_packs = F.block == 16 ? M.n_packs : 0, n_apply = n_packs > 0 ? M.n_wave : M.n_apply;
-  const unsigned apply_blocks = (unsigned)(M.n_team + (n_apply - (M.n_team + 3) / 4 * 4) / 4 + (n_packs + 3) / 4);
+  const int64_t apply_blocks = M.n_team + (n_apply - (M.n_team + 3) / 4 * 4) / 4 + (n_packs + 3) / 4;
   if (FIB) {
     KTimer tm(P, FT_K_FIBER_G, s);
     const int64_t per_block = 4 * 16 * kFiberBlocks;  // fibers of a workgroup
@@ -1288,12 +1288,12 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
       F.hvec = nullptr;
       if (M.n_apply > 0) {
         KTimer tm(P, FT_K_FACTOR_APPLY, s);
-        hipLaunchKernelGGL((k_factor_apply<ITEM_CHAIN, N, J, R, T, FIB>), dim3(apply_blocks), dim3(256), 0, s,
+        hipLaunchKernelGGL((k_factor_apply<ITEM_CHAIN, N, J, R, T, FIB>), block_grid(apply_blocks), dim3(256), 0, s,
                            D.apply, n_apply, M.n_team, D.packs, n_packs, F);
       }
       if (M.n_compose > 0) {
         KTimer tm(P, FT_K_FACTOR_COMPOSE, s);
-        hipLaunchKernelGGL((k_factor_apply<ITEM_RELAXED, N, J, R, T, FIB>), dim3(factor_blocks(M.n_compose)),
+        hipLaunchKernelGGL((k_factor_apply<ITEM_RELAXED, N, J, R, T, FIB>), block_grid(factor_blocks(M.n_compose)),
                            dim3(256), 0, s, D.compose, M.n_compose, 0, nullptr, 0, F);
       }
       if (M.n_relax > 0) {
@@ -1309,18 +1309,18 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
   }
   if (M.n_compose > 0 && M.n_apply > 0 && P->fused) {
     KTimer tm(P, FT_K_FACTOR_FUSED, s);
-    const unsigned mb = factor_blocks(M.n_compose);
-    hipLaunchKernelGGL((k_factor_fused<N, J, R, T, FIB, NC>), dim3(apply_blocks + mb), dim3(256), 0, s, M.n_team,
-                       (int64_t)mb, D.apply, n_apply, D.compose, M.n_compose, D.packs, n_packs, F);
+    const int64_t mb = factor_blocks(M.n_compose);
+    hipLaunchKernelGGL((k_factor_fused<N, J, R, T, FIB, NC>), block_grid(apply_blocks + mb), dim3(256), 0, s, M.n_team,
+                       mb, D.apply, n_apply, D.compose, M.n_compose, D.packs, n_packs, F);
   } else {
     if (M.n_compose > 0) {
       KTimer tm(P, FT_K_FACTOR_COMPOSE, s);
-      hipLaunchKernelGGL((k_factor_compose<N, J, R, T, FIB, NC>), dim3(factor_blocks(M.n_compose)), dim3(256), 0, s,
+      hipLaunchKernelGGL((k_factor_compose<N, J, R, T, FIB, NC>), block_grid(factor_blocks(M.n_compose)), dim3(256), 0, s,
                          D.compose, M.n_compose, F);
     }
     if (M.n_apply > 0) {
       KTimer tm(P, FT_K_FACTOR_APPLY, s);
-      hipLaunchKernelGGL((k_factor_apply<ITEM_CHAIN, N, J, R, T, FIB, NC>), dim3(apply_blocks), dim3(256), 0, s,
+      hipLaunchKernelGGL((k_factor_apply<ITEM_CHAIN, N, J, R, T, FIB, NC>), block_grid(apply_blocks), dim3(256), 0, s,
                          D.apply, n_apply, M.n_team, D.packs, n_packs, F);
     }
   }
