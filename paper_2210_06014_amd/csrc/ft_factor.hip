@@ -5,6 +5,7 @@ namespace ft {
 namespace {
 
 typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
 // Factor pass.  Each element x of a row, in order:
@@ -109,9 +110,17 @@ struct Slice {
 
 // Powers of rho that the blocks need, formed on the host in FP64.
 struct RhoPow {
-  double p[17];   // rho^nb
-  float inv[16];  // rho^-t
+  double p[17];                // rho^nb
+  float inv[16], inv_lo[16];   // rho^-t, to twice FP32's precision
 };
+
+// rho^-t x - u with one rounding (of the difference): x and rho^-t x are often
+// much larger than the residual, and an FP32 product would round it by theirs.
+// (With that product the error of A in relaxed passes of a learning regime was
+// a tenth above that of one step per element.)
+__device__ __forceinline__ float scaled_residual(float x, float inv, float inv_lo, float u) {
+  return fmaf(x, inv_lo, fmaf(x, inv, -u));
+}
 
 template <int J>
 struct Geo : JLayout<J> {
@@ -147,8 +156,23 @@ __device__ __forceinline__ float rotate_state(float v) {
   else if constexpr (J >= 16) return rotate_rows<12, 8, 4>(v);
   else return rotate_rows<14, 12, 10>(v);
 }
+template <int C1, int C2, int C3>
+__device__ __forceinline__ double rotate_rows(double v) {
+  float w[2];
+  __builtin_memcpy(w, &v, 8);
+  w[0] = rotate_rows<C1, C2, C3>(w[0]);
+  w[1] = rotate_rows<C1, C2, C3>(w[1]);
+  __builtin_memcpy(&v, w, 8);
+  return v;
+}
 template <int J>
-__device__ __forceinline__ float rotate_slots(float v) {
+__device__ __forceinline__ double rotate_state(double v) {
+  if constexpr (J >= 32) return rotate_rows<0, 8, 8>(v);
+  else if constexpr (J >= 16) return rotate_rows<12, 8, 4>(v);
+  else return rotate_rows<14, 12, 10>(v);
+}
+template <int J, class V>
+__device__ __forceinline__ V rotate_slots(V v) {
   if constexpr (J >= 32) return rotate_rows<0, 8, 8>(v);
   else return rotate_rows<12, 8, 4>(v);
 }
@@ -161,6 +185,29 @@ __device__ __forceinline__ float sum_halves(float v) {
 __device__ __forceinline__ float sum_rows(float v) {
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+__device__ __forceinline__ double sum_halves(double v) {
+  uint32_t w[2];
+  __builtin_memcpy(w, &v, 8);
+  const auto lo = __builtin_amdgcn_permlane32_swap(w[0], w[0], false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(w[1], w[1], false, false);
+  const uint32_t a[2] = {lo[0], hi[0]}, b[2] = {lo[1], hi[1]};
+  double x, y;
+  __builtin_memcpy(&x, a, 8);
+  __builtin_memcpy(&y, b, 8);
+  return x + y;
+}
+__device__ __forceinline__ double sum_rows(double v) {
+  uint32_t w[2];
+  __builtin_memcpy(w, &v, 8);
+  const auto lo = __builtin_amdgcn_permlane16_swap(w[0], w[0], false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(w[1], w[1], false, false);
+  const uint32_t a[2] = {lo[0], hi[0]}, b[2] = {lo[1], hi[1]};
+  double x, y;
+  __builtin_memcpy(&x, a, 8);
+  __builtin_memcpy(&y, b, 8);
+  return x + y;
 }
 
 // acc + sum_{k<K} src[lane k of the row] * v[k].  The trailing s_nop covers a
@@ -186,6 +233,27 @@ __device__ __forceinline__ float bsum(float src, const float* v) {
   return acc;
 }
 
+// the same in FP64 (a 64-bit DPP operand knows row_newbcast only, which is what is needed)
+#define FT_DOT64(n, op) "v_fmac_f64_dpp %0, %1, %" #op FT_BC(n)
+template <int K>
+__device__ __forceinline__ double bsum(double src, const double* v) {
+  double acc = 0.0;
+  if constexpr (K == 8) {
+    asm("s_nop 4\n\t" FT_DOT64(0, 2) FT_DOT64(1, 3) FT_DOT64(2, 4) FT_DOT64(3, 5) FT_DOT64(4, 6) FT_DOT64(5, 7)
+            FT_DOT64(6, 8) FT_DOT64(7, 9) FT_BSUM_END
+        : "+v"(acc)
+        : "v"(src), "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]));
+  } else if constexpr (K == 2) {
+    asm("s_nop 4\n\t" FT_DOT64(0, 2) FT_DOT64(1, 3) FT_BSUM_END : "+v"(acc) : "v"(src), "v"(v[0]), "v"(v[1]));
+  } else {
+    static_assert(K == 4, "2, 4 or 8 broadcasts");
+    asm("s_nop 4\n\t" FT_DOT64(0, 2) FT_DOT64(1, 3) FT_DOT64(2, 4) FT_DOT64(3, 5) FT_BSUM_END
+        : "+v"(acc)
+        : "v"(src), "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]));
+  }
+  return acc;
+}
+
 // Forward substitution: z_i += L[s] z_s for s = 0..14 in turn (L[s] = 0 in
 // lanes i <= s).  Each step reads the step before through DPP: two wait states.
 #define FT_SUB(n, op) "v_fmac_f32_dpp %0, %0, %" #op FT_BC(n) "s_nop 1\n\t"
@@ -197,6 +265,23 @@ __device__ __forceinline__ float forward_substitute(float z, const float (&L)[16
       : "v"(L[0]), "v"(L[1]), "v"(L[2]), "v"(L[3]), "v"(L[4]), "v"(L[5]), "v"(L[6]), "v"(L[7]), "v"(L[8]), "v"(L[9]),
         "v"(L[10]), "v"(L[11]), "v"(L[12]), "v"(L[13]), "v"(L[14]));
   return z;
+}
+
+// The same solution as r plus the rest that is returned here, with one rounding
+// of its size: a lane's sum above passes through up to 15 of them.  The rest,
+// L z, is small beside z, so it is summed again from the z found.
+#define FT_LZ(n, acc, op) "v_fmac_f32_dpp %" #acc ", %0, %" #op FT_BC(n)
+__device__ __forceinline__ float solve_rest(float r, const float (&L)[16]) {
+  float z = r, c0 = 0.f, c1 = 0.f;
+  asm("s_nop 4\n\t" FT_SUB(0, 3) FT_SUB(1, 4) FT_SUB(2, 5) FT_SUB(3, 6) FT_SUB(4, 7) FT_SUB(5, 8) FT_SUB(6, 9)
+          FT_SUB(7, 10) FT_SUB(8, 11) FT_SUB(9, 12) FT_SUB(10, 13) FT_SUB(11, 14) FT_SUB(12, 15) FT_SUB(13, 16)
+              FT_SUB(14, 17) FT_LZ(0, 1, 3) FT_LZ(1, 2, 4) FT_LZ(2, 1, 5) FT_LZ(3, 2, 6) FT_LZ(4, 1, 7) FT_LZ(5, 2, 8)
+                  FT_LZ(6, 1, 9) FT_LZ(7, 2, 10) FT_LZ(8, 1, 11) FT_LZ(9, 2, 12) FT_LZ(10, 1, 13) FT_LZ(11, 2, 14)
+                      FT_LZ(12, 1, 15) FT_LZ(13, 2, 16) FT_LZ(14, 1, 17)
+      : "+v"(z), "+v"(c0), "+v"(c1)
+      : "v"(L[0]), "v"(L[1]), "v"(L[2]), "v"(L[3]), "v"(L[4]), "v"(L[5]), "v"(L[6]), "v"(L[7]), "v"(L[8]), "v"(L[9]),
+        "v"(L[10]), "v"(L[11]), "v"(L[12]), "v"(L[13]), "v"(L[14]));
+  return c0 + c1;
 }
 
 // y[0..S-1] += (lane S's L[0..S-1]) * y[S]: one step of the rows of the inverse
@@ -367,7 +452,7 @@ __global__ __launch_bounds__(256) void k_fiber_g(const int32_t* __restrict__ fib
 // One block ready for its serial part, and (MAP) G by columns for the chunk map.
 template <int J, bool MAP>
 struct Block {
-  float Gu[Geo<J>::NG], Gr[Geo<J>::NS], L[16], xs;
+  float Gu[Geo<J>::NG], Gr[Geo<J>::NS], L[16], x;
   float Gc[MAP ? Geo<J>::JT : 1][4];  // G[4 g + v][jmap(jt, i)]
 };
 
@@ -376,6 +461,18 @@ struct Block {
 __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
+}
+
+// -gp tril(K, -1) of a block into LDS, by rows
+template <int J>
+__device__ __forceinline__ void store_l(const float (&G)[Geo<J>::NG], float gp, int i, int g, float* lds_l) {
+  floatx4 K = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < Geo<J>::NG; ++k) K = __builtin_amdgcn_mfma_f32_16x16x4f32(G[k], G[k], K, 0, 0, 0);
+  floatx4 Lw;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) Lw[v] = 4 * g + v < i ? -gp * K[v] : 0.f;
+  *reinterpret_cast<floatx4*>(lds_l + i * Geo<J>::LS + 4 * g) = Lw;
 }
 
 // G and K of a block into LDS: G by slots, and -gp tril(K, -1) by rows.
@@ -391,13 +488,7 @@ __device__ __forceinline__ void store_block(const float (&G)[Geo<J>::NG], float 
     for (int k = 0; k < Q::NG; k += 4)
       *reinterpret_cast<floatx4*>(grow + k) = floatx4{G[k], G[k + 1], G[k + 2], G[k + 3]};
   }
-  floatx4 K = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int k = 0; k < Q::NG; ++k) K = __builtin_amdgcn_mfma_f32_16x16x4f32(G[k], G[k], K, 0, 0, 0);
-  floatx4 Lw;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) Lw[v] = 4 * g + v < i ? -gp * K[v] : 0.f;
-  *reinterpret_cast<floatx4*>(lds_l + i * Q::LS + 4 * g) = Lw;
+  store_l<J>(G, gp, i, g, lds_l);
 }
 
 // The same out of LDS in the layouts of the serial part.  G of the state
@@ -443,25 +534,40 @@ __device__ __forceinline__ void load_block(const float* lds_g, const float* lds_
 }
 
 template <int J, bool MAP>
-__device__ __forceinline__ void prepare_block(const float (&G)[Geo<J>::NG], float x, float xscale, int nb, float gp,
-                                              int i, int g, WaveLds<J>& lds, Block<J, MAP>& blk) {
+__device__ __forceinline__ void prepare_block(const float (&G)[Geo<J>::NG], float x, int nb, float gp, int i, int g,
+                                              WaveLds<J>& lds, Block<J, MAP>& blk) {
   wave_lds_fence();
   store_block<J>(G, gp, i, g, lds.G, lds.L);
   wave_lds_fence();
   load_block<J, MAP>(lds.G, lds.L, i, g, blk);
-  blk.xs = i < nb ? x * xscale : 0.f;
+  blk.x = i < nb ? x : 0.f;
 }
 
-// The serial part of a block: a <- rho^nb (a + gp G^T e~).
+// The serial part of a block: a <- rho^nb (a + gp G^T e~); inv, inv_lo are
+// those of the lane's slot.  The rows of A take their increments in FP64 and an
+// e~ of one rounding: in FP32, as the state of a chunk map has them, the error of A over
+// rows of 700 elements in a learning regime (lr = 1e-2) is 3.7e-8 where one
+// step per element has 3.3e-8; so it is 3.3e-8.
 template <int J, bool MAP>
-__device__ __forceinline__ void step_block(const Block<J, MAP>& blk, double gp, double rho_nb, double& a) {
+__device__ __forceinline__ void step_block(const Block<J, MAP>& blk, float inv, float inv_lo, double gp,
+                                           double rho_nb, double& a) {
   using Q = Geo<J>;
   const float af = rotate_state<J>((float)a);
   const float u = sum_rows(sum_halves(bsum<Q::NG>(af, blk.Gu)));
-  const float e = rotate_slots<J>(forward_substitute(blk.xs - u, blk.L));
-  float d = sum_halves(bsum<Q::NS>(e, blk.Gr));
-  if constexpr (J < 32) d = sum_rows(d);
-  a = rho_nb * fma(gp, (double)d, a);
+  const float res = scaled_residual(blk.x, inv, inv_lo, u);
+  double d;
+  if constexpr (MAP) {
+    float f = sum_halves(bsum<Q::NS>(rotate_slots<J>(forward_substitute(res, blk.L)), blk.Gr));
+    if constexpr (J < 32) f = sum_rows(f);
+    d = (double)f;
+  } else {
+    double Gd[Q::NS];
+#pragma unroll
+    for (int k = 0; k < Q::NS; ++k) Gd[k] = (double)blk.Gr[k];
+    d = sum_halves(bsum<Q::NS>((double)rotate_slots<J>(res + solve_rest(res, blk.L)), Gd));
+    if constexpr (J < 32) d = sum_rows(d);
+  }
+  a = rho_nb * fma(gp, d, a);
 }
 
 // T = (I + gp tril(K, -1))^-1 of a block, as the left operand of T Y: lane
@@ -602,7 +708,7 @@ __device__ __forceinline__ void factor_item(const FItem& it, const FactorArgs<N,
   const int bs = F.block;
   const int jl = Q::jlane(i, g);
   const float gpf = (float)F.gp;
-  const float xscale = F.pw.inv[i];
+  const float inv = F.pw.inv[i], inv_lo = F.pw.inv_lo[i];
   double a = 0.0;
   if constexpr (!MAP) a = (double)F.Am[(int64_t)it.row * J + jl];
   floatx4 Nm[Q::JT][Q::JT];
@@ -634,7 +740,7 @@ __device__ __forceinline__ void factor_item(const FItem& it, const FactorArgs<N,
     if constexpr (KIND == ITEM_RELAXED)
 #pragma unroll
       for (int k = 0; k < Q::NG; ++k) gg = fmaf(G[k], G[k], gg);
-    prepare_block<J, MAP>(G, x, xscale, nb, gpf, i, g, lds, blk);
+    prepare_block<J, MAP>(G, x, nb, gpf, i, g, lds, blk);
   };
   form(it.start, cur);
   int64_t p = it.start;
@@ -642,7 +748,7 @@ __device__ __forceinline__ void factor_item(const FItem& it, const FactorArgs<N,
     // (a map's own products keep the matrix cores busy: its blocks are formed one after another, which
     // leaves registers for three wavefronts per SIMD)
     for (;;) {
-      step_block<J, MAP>(cur, F.gp, F.pw.p[min<int64_t>(bs, pe - p)], a);
+      step_block<J, MAP>(cur, inv, inv_lo, F.gp, F.pw.p[min<int64_t>(bs, pe - p)], a);
       map_block<J>(cur, lds, gpf, lane, Nm);
       p += bs;
       if (p >= pe) break;
@@ -654,18 +760,18 @@ __device__ __forceinline__ void factor_item(const FItem& it, const FactorArgs<N,
     Block<J, MAP> nxt;
     while (p + 2 * bs < pe) {
       form(p + bs, nxt);
-      step_block<J, MAP>(cur, F.gp, rb, a);
+      step_block<J, MAP>(cur, inv, inv_lo, F.gp, rb, a);
       form(p + 2 * bs, cur);
-      step_block<J, MAP>(nxt, F.gp, rb, a);
+      step_block<J, MAP>(nxt, inv, inv_lo, F.gp, rb, a);
       p += 2 * bs;
     }
     if (p + bs < pe) {
       form(p + bs, nxt);
-      step_block<J, MAP>(cur, F.gp, rb, a);
+      step_block<J, MAP>(cur, inv, inv_lo, F.gp, rb, a);
       cur = nxt;
       p += bs;
     }
-    step_block<J, MAP>(cur, F.gp, F.pw.p[pe - p], a);
+    step_block<J, MAP>(cur, inv, inv_lo, F.gp, F.pw.p[pe - p], a);
   }
 
   // lanes that hold a copy of the state's element jl write it once
@@ -700,17 +806,53 @@ __device__ __forceinline__ void factor_item(const FItem& it, const FactorArgs<N,
   }
 }
 
-// The head of a long row, by a workgroup: wavefronts 1 to 3 form its blocks in
-// turn (gathers, MFMA) and leave them in LDS, a round of three ahead of
-// wavefront 0, which only takes the serial parts.  A lone wavefront issues an
-// instruction about every five cycles, so a chain that also forms its blocks
+// A long row, or the head of one, by a workgroup: wavefronts 1 to 3 form its
+// blocks in turn (gathers, MFMA) and leave them in LDS, a round of three ahead
+// of wavefront 0, which only takes the serial parts.  A lone wavefront issues
+// an instruction about every five cycles, so a chain that also forms its blocks
 // takes 1900 cycles per block (J = 8) to 2400 (J = 32); the serial part alone
-// is a quarter of that, and the head of a long row is what a launch waits for.
+// is a third of that, and the head of a long row is what a launch waits for.
+// G and x are stored as FP64, so that the chain converts neither.  (T = (I + gp
+// tril(K, -1))^-1 formed by wavefronts 1 to 3 in place of the substitution is
+// slower where the launch is full of such rows: 1000 rows of 8000 elements,
+// J = 32, g shared, 318 us against 283; 240 with the sums of a block in FP32.)
 template <int J>
 struct __align__(16) TeamLds {
-  float G[2][3][16 * Geo<J>::GS];
+  static constexpr int GS = J + 2;  // row stride of G in doubles
+  double G[2][3][16 * GS];
+  double x[2][3][16];              // rho^-t x
   float L[2][3][16 * Geo<J>::LS];
-  float x[2][3][16];
+};
+
+template <int J>
+struct TeamBlock {
+  double Gu[Geo<J>::NG], Gr[Geo<J>::NS], x;
+  float L[16];
+  __device__ __forceinline__ void load(const TeamLds<J>& lds, int h, int q, int i, int g) {
+    using Q = Geo<J>;
+    const double* grow = lds.G[h][q] + i * TeamLds<J>::GS + Q::jbase(g);
+#pragma unroll
+    for (int k = 0; k < Q::NG; ++k) Gu[k] = grow[k];
+    const double* gcol = lds.G[h][q] + Q::sbase(g) * TeamLds<J>::GS + Q::jlane(i, g);
+#pragma unroll
+    for (int k = 0; k < Q::NS; ++k) Gr[k] = gcol[k * TeamLds<J>::GS];
+    const float* lrow = lds.L[h][q] + i * Q::LS;
+#pragma unroll
+    for (int s = 0; s < 16; s += 4) {
+      const floatx4 u = *reinterpret_cast<const floatx4*>(lrow + s);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) L[s + v] = u[v];
+    }
+    x = lds.x[h][q][i];
+  }
+  __device__ __forceinline__ void step(double gp, double rho_nb, double& a) const {
+    using Q = Geo<J>;
+    const double r = x - sum_rows(sum_halves(bsum<Q::NG>(rotate_state<J>(a), Gu)));
+    const double e = r + (double)solve_rest((float)r, L);
+    double d = sum_halves(bsum<Q::NS>(rotate_slots<J>(e), Gr));
+    if constexpr (J < 32) d = sum_rows(d);
+    a = rho_nb * fma(gp, d, a);
+  }
 };
 
 template <int N, int J, int R, class T, bool FIB, bool NC>
@@ -731,18 +873,15 @@ __device__ __forceinline__ void team_item(const FItem& it, const FactorArgs<N, J
     for (int r = 0; r <= rounds; ++r) {
       if (r > 0) {
         const int h = (r - 1) & 1, b0 = 3 * (r - 1);
-        Block<J, false> blk[2];
-        load_block<J, false>(lds.G[h][0], lds.L[h][0], i, g, blk[0]);
-        blk[0].xs = lds.x[h][0][i];
+        TeamBlock<J> blk[2];
+        blk[0].load(lds, h, 0, i, g);
         static_for<0, 3>([&](auto S) {
           constexpr int q = decltype(S)::value;
           if (b0 + q < nblk) {
-            if constexpr (q < 2) {  // (a slot past the last block holds an old one, which is not used)
-              load_block<J, false>(lds.G[h][q + 1], lds.L[h][q + 1], i, g, blk[(q + 1) & 1]);
-              blk[(q + 1) & 1].xs = lds.x[h][q + 1][i];
-            }
+            // (a slot past the last block holds an old one, which is not used)
+            if constexpr (q < 2) blk[(q + 1) & 1].load(lds, h, q + 1, i, g);
             const int64_t left = pe - it.start - (int64_t)(b0 + q) * bs;
-            step_block<J, false>(blk[q & 1], F.gp, left >= bs ? rb : F.pw.p[left], a);
+            blk[q & 1].step(F.gp, left >= bs ? rb : F.pw.p[left], a);
           }
         });
       }
@@ -762,9 +901,10 @@ __device__ __forceinline__ void team_item(const FItem& it, const FactorArgs<N, J
   src.gfib = F.gfib;
   src.nc = F.nc;
   src.init(F.Bm, lane);
-  const float gpf = (float)F.gp, xscale = F.pw.inv[i];
-  const int step = 3 * bs;
-  int64_t p = it.start + (int64_t)(wave - 1) * bs;
+  const float gpf = (float)F.gp;
+  const double inv = (double)F.pw.inv[i] + (double)F.pw.inv_lo[i];
+  const int step = 3 * bs, w = wave - 1;
+  int64_t p = it.start + (int64_t)w * bs;
   typename Src::Idx ix0, ix1;
   typename Src::Raw raw;
   src.index(min(p, pe - 1), pe, ix0);
@@ -772,15 +912,18 @@ __device__ __forceinline__ void team_item(const FItem& it, const FactorArgs<N, J
   src.index(min(p + step, pe - 1), pe, ix1);
   for (int r = 0; r <= rounds; ++r) {
     if (p < pe) {
-      const int nb = (int)min<int64_t>(bs, pe - p);
+      const int nb = (int)min<int64_t>(bs, pe - p), h = r & 1;
       float G[Q::NG];
       src.form(raw, nb, G);
       const float x = ix0.x;
       ix0 = ix1;
       src.gather(ix0, raw);
       src.index(min(p + 2 * step, pe - 1), pe, ix1);
-      store_block<J>(G, gpf, i, g, lds.G[r & 1][wave - 1], lds.L[r & 1][wave - 1]);
-      if (g == 0) lds.x[r & 1][wave - 1][i] = i < nb ? x * xscale : 0.f;
+      double* grow = lds.G[h][w] + i * TeamLds<J>::GS + Q::jbase(g);
+#pragma unroll
+      for (int k = 0; k < Q::NG; ++k) grow[k] = (double)G[k];
+      if (g == 0) lds.x[h][w][i] = i < nb ? (double)x * inv : 0.0;
+      store_l<J>(G, gpf, i, g, lds.L[h][w]);
       p += step;
     }
     __syncthreads();
@@ -790,7 +933,7 @@ __device__ __forceinline__ void team_item(const FItem& it, const FactorArgs<N, J
 // A pack: a block of 16 slots shared by whole short rows.  The rows' steps are
 // independent, so K is masked to pairs of one row; each slot reads its own
 // row's state, and the rows' sums of e~_t g_t are one product over the slots,
-// Delta^T = G^T (e~_s [row s = row t]).  (A row of five elements in a block of
+// Delta^T = G^T (e~_s [row s = row t]), in FP64 as the steps of a longer row.  (A row of five elements in a block of
 // its own costs as much as one of 16: order 4, 300k such rows, J = R = 32,
 // 554 -> 253 us per pass; Netflix-shaped 5M mode 0, J = R = 16: 279 -> 171.)  Rows share sums in
 // which another row's terms carry a factor 0, so a pack with a value that is
@@ -849,29 +992,30 @@ __device__ __forceinline__ bool pack_item(const Pack* __restrict__ pk, const Fac
     for (int v = 0; v < 4; ++v) L[s + v] = x[v];
   }
   // rho^-t and rho^count by the slot's place in its row: lane t holds the t-th power
-  const float xs = i < n ? ix.x * __shfl(F.pw.inv[i], at & 15) : 0.f;
+  const float inv = __shfl(F.pw.inv[i], at & 15), inv_lo = __shfl(F.pw.inv_lo[i], at & 15);
   const double rc = __shfl(F.pw.p[i < 15 ? i + 1 : 16], max((at >> 8) - 1, 0));
-  const float e = forward_substitute(xs - u, L);
+  const float res = scaled_residual(i < n ? ix.x : 0.f, inv, inv_lo, u);
+  const float e = res + solve_rest(res, L);
   if (__any(!(fabsf(e) <= 3.402823466e38f))) return false;
   const float er = rotate_rows<12, 8, 4>(e);  // broadcast v gives lane row g slot 4 g + v
-  floatx4 d[Q::JT];
+  doublex4 d[Q::JT];
 #pragma unroll
-  for (int jt = 0; jt < Q::JT; ++jt) d[jt] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int jt = 0; jt < Q::JT; ++jt) d[jt] = doublex4{0.0, 0.0, 0.0, 0.0};
   static_for<0, 4>([&](auto VV) {
     constexpr int v = decltype(VV)::value;
     const float ev = bcast16<v>(er);
-    const float em = rows[v] == row ? ev : 0.f;
+    const double em = rows[v] == row ? (double)ev : 0.0;
 #pragma unroll
     for (int jt = 0; jt < Q::JT; ++jt) {
-      const int j = Q::jmap(jt, i);
+      const int j = Q::jmap(jt, 4 * (i & 3) + (i >> 2));  // (row 4 v + g of an FP64 result is in lanes of row g)
       const float q = lds.G[(4 * g + v) * Q::GS + max(j, 0)];
-      d[jt] = __builtin_amdgcn_mfma_f32_16x16x4f32(j >= 0 ? q : 0.f, em, d[jt], 0, 0, 0);
+      d[jt] = __builtin_amdgcn_mfma_f64_16x16x4f64(j >= 0 ? (double)q : 0.0, em, d[jt], 0, 0, 0);
     }
   });
   if ((at & 255) == 0 && i < n) {
 #pragma unroll
     for (int k = 0; k < Q::NG; ++k)
-      arow[k] = (float)(rc * fma(F.gp, (double)d[k / Q::VJ][k % Q::VJ], (double)as[k]));
+      arow[k] = (float)(rc * fma(F.gp, d[k / Q::VJ][k % Q::VJ], (double)as[k]));
   }
   return true;
 }
@@ -1268,7 +1412,11 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
   F.block = F.rho >= 0.5 ? 16 : 1;
   F.pw.p[0] = 1.0;
   for (int k = 1; k <= 16; ++k) F.pw.p[k] = F.pw.p[k - 1] * F.rho;
-  for (int k = 0; k < 16; ++k) F.pw.inv[k] = k < F.block ? (float)(1.0 / F.pw.p[k]) : 0.f;
+  for (int k = 0; k < F.block; ++k) {
+    const double inv = 1.0 / F.pw.p[k];
+    F.pw.inv[k] = (float)inv;
+    F.pw.inv_lo[k] = (float)(inv - (double)F.pw.inv[k]);
+  }
   // the list of in-place items: n_team for a workgroup each (padded to a multiple of four), then one per wavefront,
   // the shortest rows as packs (or, where blocks are single elements, on their own)
   const int64_t n_packs = F.block == 16 ? M.n_packs : 0, n_apply = n_packs > 0 ? M.n_wave : M.n_apply;
