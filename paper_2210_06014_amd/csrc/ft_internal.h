@@ -209,6 +209,7 @@ constexpr int kSegLen = 512;     // max elements per segment (ft_plan::seg_len)
 constexpr int kShortSeg = 32;    // rows of at most this many elements may be listed as short
 constexpr int kMinShort = 16384; // a mode with fewer of them lists none (one launch instead of two)
 constexpr int kTeamRow = 1024;   // rows longer than this are updated by a workgroup, shorter ones by a wavefront
+constexpr int kTeamHeads = 512;  // so many heads of kTeamRow elements are updated by a workgroup each, more by a wavefront
 constexpr int kPackRow = 16;      // rows of at most this many elements share blocks of 16
 constexpr int kRelaxGroup = 256; // chunks per level-1 group of the relaxed merge
 

@@ -353,13 +353,19 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
   std::stable_sort(H.compose.begin(), H.compose.end(), [](const FItem& a, const FItem& b) { return a.len > b.len; });
   std::stable_sort(light.begin(), light.end(), [](const FItem& a, const FItem& b) { return a.len > b.len; });
   pad4(H.compose, ITEM_COMPOSE);
-  // heads, then short rows by descending length; a workgroup takes each item of the first part
-  H.apply = head;
+  // In-place items by descending length; a workgroup takes each item of the first part: rows and heads of more than
+  // kTeamRow elements, and heads of just so many (the default at J = 8 and of relaxed plans) where there are few.
+  // A workgroup's chain takes a third of the time of a wavefront's, but four wavefronts.  Netflix-shaped, 8M
+  // elements, us in the factor launches, workgroups against wavefronts: J = 16, heads of 128 749 and 657, of 1024 (1700
+  // a mode) 711 and 619; J = 8 528 and 445, 523 and 426; order 8 with 1M, heads of 1024 (100 a mode) 498 and 556.
+  const bool team_heads = hl > kTeamRow || (hl == kTeamRow && n_heavy <= kTeamHeads);
+  if (team_heads) H.apply = head;
   auto rest = std::find_if(light.begin(), light.end(), [](const FItem& a) { return a.len <= kTeamRow; });
   H.apply.insert(H.apply.end(), light.begin(), rest);
   M.n_team = (int64_t)H.apply.size();
   pad4(H.apply, ITEM_LIGHT);
   auto packed = std::find_if(rest, light.end(), [](const FItem& a) { return a.len <= kPackRow; });
+  if (!team_heads) H.apply.insert(H.apply.end(), head.begin(), head.end());
   H.apply.insert(H.apply.end(), rest, packed);
   pad4(H.apply, ITEM_LIGHT);
   M.n_wave = (int64_t)H.apply.size();
