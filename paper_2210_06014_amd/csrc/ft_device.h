@@ -71,6 +71,7 @@ __device__ __forceinline__ float group_sum(float v) {
 #define FT_BC(n) " row_newbcast:" #n " row_mask:0xf bank_mask:0xf\n\t"
 #define FT_DOT(n, op) "v_fmac_f32_dpp %0, %1, %" #op FT_BC(n)
 #define FT_AXPY(n, op) "v_fmac_f32_dpp %" #op ", %16, %17" FT_BC(n)
+#define FT_AXPY8(n, op) "v_fmac_f32_dpp %" #op ", %8, %9" FT_BC(n)
 
 // acc += sum_{i<16} src[lane i] * v[i]
 __device__ __forceinline__ void dot_bcast16(float& acc, float src, const float* v) {
@@ -97,10 +98,22 @@ __device__ __forceinline__ void axpy_bcast16(float* v, float src, float t) {
                  "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]), "+v"(v[13]), "+v"(v[14]), "+v"(v[15])
                : "v"(src), "v"(t));
 }
+// v[i] += src[lane i] * t, i < 8
+__device__ __forceinline__ void axpy_bcast8(float* v, float src, float t) {
+  asm volatile("s_nop 4\n\t" FT_AXPY8(0, 0) FT_AXPY8(1, 1) FT_AXPY8(2, 2) FT_AXPY8(3, 3) FT_AXPY8(4, 4)
+                   FT_AXPY8(5, 5) FT_AXPY8(6, 6) FT_AXPY8(7, 7)
+               : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7])
+               : "v"(src), "v"(t));
+}
 template <int K>
 __device__ __forceinline__ void dot_bcast(float& acc, float src, const float* v) {
   static_assert(K == 8 || K == 16, "row broadcasts cover 8 or 16 lanes");
   if constexpr (K == 16) dot_bcast16(acc, src, v); else dot_bcast8(acc, src, v);
+}
+template <int K>
+__device__ __forceinline__ void axpy_bcast(float* v, float src, float t) {
+  static_assert(K == 8 || K == 16, "row broadcasts cover 8 or 16 lanes");
+  if constexpr (K == 16) axpy_bcast16(v, src, t); else axpy_bcast8(v, src, t);
 }
 
 // Parameter storage: float (FP32) or uint16_t holding BF16 bits.  BF16 is

@@ -341,8 +341,8 @@ struct Source {
         for (int s = 0; s < 4; ++s) bn[k][s] = nc.B[k][(4 * g + s) * R + i];
   }
   // slot i of the block at position p0 of an item ending before pe (clamped to its last element)
-  __device__ __forceinline__ void index(int64_t p0, int64_t pe, Idx& a) const {
-    const int64_t p = min(p0 + i, pe - 1);
+  __device__ __forceinline__ void index(int64_t p0, int64_t pe, Idx& a) const { index_at(min(p0 + i, pe - 1), a); }
+  __device__ __forceinline__ void index_at(int64_t p, Idx& a) const {
     a.x = val[p];
     if constexpr (FIB) {
       a.o[0] = (uint32_t)fid[p];
@@ -672,9 +672,11 @@ struct FactorArgs {
   double rho, gp;
   RhoPow pw;
   int block;           // elements per block (16; 1 where rho^-15 would leave the FP32 range)
+  int quads;           // items taken four to a wavefront: kQuadChunks, kQuadRows
 };
 
 enum { ITEM_CHAIN, ITEM_RELAXED, ITEM_MAP };
+enum { kQuadChunks = 1, kQuadRows = 2 };
 
 // One work item on one wavefront.
 //  CHAIN: the row (or the head of a long row) is updated in place; a head
@@ -803,6 +805,139 @@ __device__ __forceinline__ void factor_item(const FItem& it, const FactorArgs<N,
     }
     if (writer) dst[J * J + jl] = (float)a;
     if (lane == 0) F.map_scale[it.slot] = pow(F.rho, (double)it.len);
+  }
+}
+
+// Four items on one wavefront (J <= 16), 16 lanes each, one step per element:
+//     Nm <- Nm - gp g (g + Nm^T g)^T,   a <- a + gp (rho^-t x - a.g) g,
+// a decaying by rho^16 at the end of a block (t: the step within it); lane l
+// of a row of 16 holds column l of Nm (MAP) and element l of a (FP64, MAP:
+// from a = 0).  Only where rho >= 1/2, as with blocks of 16.  G comes from the products that factor_item takes
+// it from, a chunk's block after the other, through LDS, so that g is the same
+// to the bit.  A step is 2 J row broadcasts and about 14 more instructions for
+// four chunks, where a block of 16 elements on the matrix cores costs one
+// chunk 20 of their instructions and 140 others, three quarters of them the
+// same in the four rows of lanes: more work per second, but a chunk takes
+// about twice as long.
+template <int J>
+struct __align__(16) QuadLds {
+  static constexpr int S = 16 * Geo<J>::GS + 16;  // one chunk's block; the 16 spread the rows over the banks
+  float G[4 * S];
+};
+
+template <int KIND, int N, int J, int R, class T, bool FIB, bool NC>
+__device__ __forceinline__ void quad_items(const FItem* __restrict__ items, int64_t k0, int64_t n_items,
+                                           const FactorArgs<N, J, R, T, FIB, NC>& F, QuadLds<J>& lds) {
+  static_assert(J <= 16, "a row of 16 lanes holds the state");
+  using Q = Geo<J>;
+  using Src = Source<N, J, R, T, FIB, NC>;
+  constexpr bool MAP = KIND == ITEM_MAP;
+  // all four gathers ahead of the steps where they fit in registers, else two at a time
+  constexpr bool PIPE = Src::NI * Src::RK * (int)sizeof(typename Src::E) <= 48;
+  constexpr int NR = PIPE ? 4 : 2;
+  if (k0 >= n_items) return;
+  const int lane = threadIdx.x & 63, l = lane & 15, row = lane >> 4;
+  FItem it{0, 0, 0, 0, 0};
+  if (k0 + row < n_items) it = items[k0 + row];
+  Src src;
+  src.idx = F.idx;
+  src.nnz = F.nnz;
+  src.val = F.val;
+  src.cp = F.cp;
+  src.fid = F.fid;
+  src.gfib = F.gfib;
+  src.nc = F.nc;
+  src.init(F.Bm, lane);
+  int most = it.len;
+  most = max(most, __shfl_xor(most, 16));
+  most = __builtin_amdgcn_readfirstlane(max(most, __shfl_xor(most, 32)));
+  double a = 0.0;
+  if constexpr (!MAP)
+    if (it.len > 0) a = (double)F.Am[(int64_t)it.row * J + l % J];
+  float Nc[MAP ? J : 1];
+#pragma unroll
+  for (int j = 0; j < (MAP ? J : 1); ++j) Nc[j] = 0.f;
+  float gg = 0.f;
+  const float gpf = (float)F.gp;
+  const double rhol = F.pw.p[l + 1];
+  // slot l of the block at t0 of this row's chunk (clamped to its last element; an empty item reads element 0)
+  auto index = [&](int t0, typename Src::Idx& ix) {
+    src.index_at(it.start + min(t0 + l, max(it.len - 1, 0)), ix);
+  };
+  auto gather = [&](const typename Src::Idx& ix, int q, typename Src::Raw& r) {
+    typename Src::Idx o;
+#pragma unroll
+    for (int k = 0; k < Src::NI; ++k) o.o[k] = (uint32_t)__shfl((int)ix.o[k], 16 * q + l);
+    src.gather(o, r);
+  };
+  typename Src::Idx ix0, ix1;
+  typename Src::Raw raw[NR];
+  index(0, ix0);
+#pragma unroll
+  for (int q = 0; q < NR; ++q) gather(ix0, q, raw[q]);
+  index(16, ix1);
+  for (int t0 = 0; t0 < most; t0 += 16) {
+    wave_lds_fence();
+    static_for<0, 4>([&](auto QQ) {
+      constexpr int q = decltype(QQ)::value;
+      float G[Q::NG];
+      src.form(raw[q % NR], min(max(__builtin_amdgcn_readlane(it.len, 16 * q) - t0, 0), 16), G);
+      if constexpr (q + NR < 4) gather(ix0, q + NR, raw[q % NR]);
+      if constexpr (KIND == ITEM_RELAXED) {
+        float z = 0.f;
+#pragma unroll
+        for (int k = 0; k < Q::NG; ++k) z = fmaf(G[k], G[k], z);
+        z = sum_rows(sum_halves(z));
+        gg += row == q ? z : 0.f;
+      }
+      float* grow = lds.G + q * QuadLds<J>::S + l * Q::GS + Q::jbase(row);
+#pragma unroll
+      for (int k = 0; k < Q::NG; k += 2) *reinterpret_cast<floatx2*>(grow + k) = floatx2{G[k], G[k + 1]};
+    });
+    const float x = ix0.x;
+    ix0 = ix1;
+#pragma unroll
+    for (int q = 0; q < NR; ++q) gather(ix0, q, raw[q]);
+    index(t0 + 32, ix1);
+    wave_lds_fence();
+    float gs[16];
+#pragma unroll
+    for (int s = 0; s < 16; ++s) gs[s] = lds.G[row * QuadLds<J>::S + s * Q::GS + l % J];
+    static_for<0, 16>([&](auto S) {
+      constexpr int s = decltype(S)::value;
+      const float g = gs[s];  // 0 past the end of the chunk
+      if constexpr (MAP) {
+        float h = g;
+        dot_bcast<J>(h, g, Nc);
+        axpy_bcast<J>(Nc, g, -gpf * h);
+      }
+      const float e = gpf * scaled_residual(bcast16<s>(x), F.pw.inv[s], F.pw.inv_lo[s], group_sum<J>((float)a * g));
+      a = fma((double)e, (double)g, a);
+    });
+    const int nb = it.len - t0;
+    const double part = __shfl(rhol, 16 * row + min(max(nb - 1, 0), 15));
+    a *= nb >= 16 ? F.pw.p[16] : nb > 0 ? part : 1.0;
+  }
+  if (it.len <= 0) return;
+  if constexpr (KIND == ITEM_CHAIN) {
+    float* dst = it.kind == ITEM_LIGHT || F.hvec == nullptr ? F.Am + (int64_t)it.row * J : F.hvec + (int64_t)it.slot * J;
+    if (l < J) dst[l] = (float)a;
+  } else if constexpr (KIND == ITEM_RELAXED) {
+    gg = group_sum<16>(gg);
+    const double own = pow(F.rho, (double)it.len);
+    const double after = pow(F.rho, (double)(F.row_ptr[it.row + 1] - (it.start + it.len)));
+    float* dst = F.maps + (int64_t)it.slot * (J + 1);
+    if (l < J) dst[l] = (float)(after * (a - own * (double)F.Am[(int64_t)it.row * J + l]));
+    if (l == 0) dst[J] = gg;
+  } else {
+    float* dst = F.maps + (int64_t)it.slot * (J * J + J);  // column-major
+    if (l < J) {
+#pragma unroll
+      for (int j = 0; j < J; j += 4)
+        *reinterpret_cast<floatx4*>(dst + l * J + j) = floatx4{Nc[j], Nc[j + 1], Nc[j + 2], Nc[j + 3]};
+      dst[J * J + l] = (float)a;
+    }
+    if (l == 0) F.map_scale[it.slot] = pow(F.rho, (double)it.len);
   }
 }
 
@@ -1020,20 +1155,50 @@ __device__ __forceinline__ bool pack_item(const Pack* __restrict__ pk, const Fac
   return true;
 }
 
-// Entry k of the in-place items that a wavefront takes: a row, or past them a pack.
-template <int N, int J, int R, class T, bool FIB, bool NC>
-__device__ __forceinline__ void wave_items(int64_t k, const FItem* __restrict__ items, int64_t n_items,
+// LDS of a workgroup: a part of its own for each wavefront (a workgroup at the
+// end of the rows has wavefronts with four rows beside others with a pack), or
+// all of it for a team.
+template <int J, bool QUAD>
+union SlotLds {
+  WaveLds<J> wave;
+  QuadLds<J> quad;
+};
+template <int J>
+union SlotLds<J, false> {
+  WaveLds<J> wave;
+};
+template <int J, bool QUAD = false>
+union FactorLds {
+  SlotLds<J, QUAD> slot[4];
+  TeamLds<J> team;
+};
+
+// Entry k of the in-place items that a wavefront takes, from item k0 on: a row
+// (or four), or past the rows a pack.
+template <bool QUAD, int N, int J, int R, class T, bool FIB, bool NC>
+__device__ __forceinline__ void wave_items(int64_t k, int64_t k0, const FItem* __restrict__ items, int64_t n_items,
                                            const Pack* __restrict__ packs, int64_t n_packs,
-                                           const FactorArgs<N, J, R, T, FIB, NC>& F, WaveLds<J>& lds) {
+                                           const FactorArgs<N, J, R, T, FIB, NC>& F, FactorLds<J, QUAD>& lds) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int64_t rows = n_items - k0;
+  if constexpr (QUAD) {
+    if (F.quads & kQuadRows) {
+      rows = (rows + 3) / 4;
+      if (k < rows) {
+        quad_items<ITEM_CHAIN>(items, k0 + 4 * k, n_items, F, lds.slot[wave].quad);
+        return;
+      }
+    }
+  }
   FItem it{0, 0, 0, 0, ITEM_LIGHT};
   const Pack* pk = nullptr;
   int t = 0;
-  if (k < n_items) {
-    it = items[k];
+  if (k < rows) {
+    it = items[k0 + k];
   } else {
-    if (k - n_items >= n_packs) return;
-    pk = packs + (k - n_items);
-    if (pack_item(pk, F, lds)) return;
+    if (k - rows >= n_packs) return;
+    pk = packs + (k - rows);
+    if (pack_item(pk, F, lds.slot[wave].wave)) return;
   }
   for (;;) {
     if (pk) {
@@ -1042,46 +1207,51 @@ __device__ __forceinline__ void wave_items(int64_t k, const FItem* __restrict__ 
       it.row = pk->row[t];
       t += it.len;
     }
-    factor_item<ITEM_CHAIN>(it, F, lds);
+    factor_item<ITEM_CHAIN>(it, F, lds.slot[wave].wave);
     if (!pk || t >= pk->n) return;
   }
 }
 
-template <int J>
-union FactorLds {
-  WaveLds<J> wave[4];
-  TeamLds<J> team;
-};
+// Chunks of a launch that a workgroup takes: one per wavefront, or four.
+template <int KIND, bool QUAD, int N, int J, int R, class T, bool FIB, bool NC>
+__device__ __forceinline__ void chunk_items(int64_t b, const FItem* __restrict__ items, int64_t n_items,
+                                            const FactorArgs<N, J, R, T, FIB, NC>& F, FactorLds<J, QUAD>& lds) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t k = b * 4 + wave;
+  if constexpr (QUAD) {
+    if (F.quads & kQuadChunks) {
+      quad_items<KIND>(items, 4 * k, n_items, F, lds.slot[wave].quad);
+      return;
+    }
+  }
+  if (k < n_items) factor_item<KIND>(items[k], F, lds.slot[wave].wave);
+}
 
-// Short rows and relaxed chunks: one item per wavefront; the hardware
-// dispatcher balances the items (the lists are sorted by length, so that a
-// workgroup's four end together).  The first `teams` workgroups take a head
-// each, the items after the padded list of heads follow.
-template <int KIND, int N, int J, int R, class T, bool FIB, bool NC = false>
+// In-place items alone: the first `teams` workgroups take a long row each, the
+// items after the padded list of those follow, one or four per wavefront; the
+// hardware dispatcher balances the items (the lists are sorted by length, so
+// that a workgroup's end together).
+template <bool QUAD, int N, int J, int R, class T, bool FIB, bool NC = false>
 __global__ __launch_bounds__(256) void k_factor_apply(const FItem* __restrict__ items, int64_t n_items, int64_t teams,
                                                       const Pack* __restrict__ packs, int64_t n_packs,
                                                       FactorArgs<N, J, R, T, FIB, NC> F) {
-  __shared__ FactorLds<J> lds;
+  __shared__ FactorLds<J, QUAD> lds;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t b = block_id();
-  if (KIND == ITEM_CHAIN && b < teams) {
+  if (b < teams) {
     team_item(items[b], F, lds.team);
     return;
   }
-  const int64_t k = (teams + 3) / 4 * 4 + (b - teams) * 4 + wave;
-  if constexpr (KIND == ITEM_CHAIN)
-    wave_items(k, items, n_items, packs, n_packs, F, lds.wave[wave]);
-  else if (k < n_items)
-    factor_item<KIND>(items[k], F, lds.wave[wave]);
+  wave_items((b - teams) * 4 + wave, (teams + 3) / 4 * 4, items, n_items, packs, n_packs, F, lds);
 }
 
-template <int N, int J, int R, class T, bool FIB, bool NC = false>
-__global__ __launch_bounds__(256, 3) void k_factor_compose(const FItem* __restrict__ items, int64_t n_items,
-                                                        FactorArgs<N, J, R, T, FIB, NC> F) {
-  __shared__ FactorLds<J> lds;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t k = block_id() * 4 + wave;
-  if (k < n_items) factor_item<ITEM_MAP>(items[k], F, lds.wave[wave]);
+// Chunks of long rows: their maps, or (RELAXED) their increments.
+template <int KIND, bool QUAD, int N, int J, int R, class T, bool FIB, bool NC = false>
+__global__ __launch_bounds__(256, KIND == ITEM_MAP ? 3 : 1) void k_factor_compose(const FItem* __restrict__ items,
+                                                                                  int64_t n_items,
+                                                                                  FactorArgs<N, J, R, T, FIB, NC> F) {
+  __shared__ FactorLds<J, QUAD> lds;
+  chunk_items<KIND>(block_id(), items, n_items, F, lds);
 }
 
 // The in-place items and the chunk maps of one exact factor pass in one
@@ -1090,23 +1260,21 @@ __global__ __launch_bounds__(256, 3) void k_factor_compose(const FItem* __restri
 // rows, the next map_blocks the chunk maps, the rest the short rows: the long
 // serial heads start at once and run while the maps keep the SIMDs busy, and
 // the short items fill in where the maps run out.
-template <int N, int J, int R, class T, bool FIB, bool NC = false>
+template <bool QUAD, int N, int J, int R, class T, bool FIB, bool NC = false>
 __global__ __launch_bounds__(256, 3) void k_factor_fused(int64_t teams, int64_t map_blocks,
                                                       const FItem* __restrict__ apply_items, int64_t n_apply,
                                                       const FItem* __restrict__ compose_items, int64_t n_compose,
                                                       const Pack* __restrict__ packs, int64_t n_packs,
                                                       FactorArgs<N, J, R, T, FIB, NC> F) {
-  __shared__ FactorLds<J> lds;
+  __shared__ FactorLds<J, QUAD> lds;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t b = block_id();
   if (b < teams) {
     team_item(apply_items[b], F, lds.team);
   } else if (b < teams + map_blocks) {
-    const int64_t k = (b - teams) * 4 + wave;
-    if (k < n_compose) factor_item<ITEM_MAP>(compose_items[k], F, lds.wave[wave]);
+    chunk_items<ITEM_MAP>(b - teams, compose_items, n_compose, F, lds);
   } else {
-    const int64_t k = (teams + 3) / 4 * 4 + (b - teams - map_blocks) * 4 + wave;
-    wave_items(k, apply_items, n_apply, packs, n_packs, F, lds.wave[wave]);
+    wave_items((b - teams - map_blocks) * 4 + wave, (teams + 3) / 4 * 4, apply_items, n_apply, packs, n_packs, F, lds);
   }
 }
 
@@ -1379,8 +1547,19 @@ __global__ __launch_bounds__(256) void k_relaxed_merge(const CItem* __restrict__
   }
 }
 
-// workgroups of four items, one per wavefront
-int64_t factor_blocks(int64_t n_items) { return (n_items + 3) / 4; }
+// workgroups for n items, one per wavefront or four
+int64_t item_blocks(int64_t n, bool quad) { return quad ? (n + 15) / 16 : (n + 3) / 4; }
+
+// CALL(true) or CALL(false): a kernel with the four-item paths, or without
+#define FT_QUAD(quad, J, CALL)                     \
+  do {                                             \
+    if constexpr (J <= 16) {                       \
+      if (quad) CALL(true);                        \
+      else CALL(false);                            \
+    } else {                                       \
+      CALL(false);                                 \
+    }                                              \
+  } while (0)
 
 template <int N, int J, int R, class T, bool FIB, bool NC = false>
 hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scratch& S, double lr, double lam,
@@ -1420,7 +1599,29 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
   // the list of in-place items: n_team for a workgroup each (padded to a multiple of four), then one per wavefront,
   // the shortest rows as packs (or, where blocks are single elements, on their own)
   const int64_t n_packs = F.block == 16 ? M.n_packs : 0, n_apply = n_packs > 0 ? M.n_wave : M.n_apply;
-  const int64_t apply_blocks = M.n_team + (n_apply - (M.n_team + 3) / 4 * 4) / 4 + (n_packs + 3) / 4;
+  const int64_t n_rows = n_apply - (M.n_team + 3) / 4 * 4;
+  if (F.block == 16) {
+    if (quad_chunks(N, J, P->relaxed, M.n_compose)) F.quads |= kQuadChunks;
+    if (quad_rows(N, J, P->relaxed, n_rows, M.row_elems, M.n_compose)) F.quads |= kQuadRows;
+  }
+  // (a launch of rows, or of chunks, alone needs the four-item paths for these only)
+  const int rows4 = F.quads & kQuadRows, chunks4 = F.quads & kQuadChunks;
+  const int64_t row_waves = rows4 ? (n_rows + 3) / 4 : n_rows;
+  const int64_t apply_blocks = M.n_team + (row_waves + n_packs + 3) / 4;
+  const int64_t compose_blocks = item_blocks(M.n_compose, chunks4);
+#define FT_APPLY(Q)                                                                                                  \
+  hipLaunchKernelGGL((k_factor_apply<Q, N, J, R, T, FIB, NC>), block_grid(apply_blocks), dim3(256), 0, s, D.apply, \
+                     n_apply, M.n_team, D.packs, n_packs, F)
+#define FT_RELAXED_CHUNKS(Q)                                                                                     \
+  hipLaunchKernelGGL((k_factor_compose<ITEM_RELAXED, Q, N, J, R, T, FIB, NC>), block_grid(compose_blocks),     \
+                     dim3(256), 0, s, D.compose, M.n_compose, F)
+#define FT_MAPS(Q)                                                                                               \
+  hipLaunchKernelGGL((k_factor_compose<ITEM_MAP, Q, N, J, R, T, FIB, NC>), block_grid(compose_blocks), dim3(256), \
+                     0, s, D.compose, M.n_compose, F)
+#define FT_FUSED(Q)                                                                                                 \
+  hipLaunchKernelGGL((k_factor_fused<Q, N, J, R, T, FIB, NC>), block_grid(apply_blocks + compose_blocks),         \
+                     dim3(256), 0, s, M.n_team, compose_blocks, D.apply, n_apply, D.compose, M.n_compose, D.packs, \
+                     n_packs, F)
   if (FIB) {
     KTimer tm(P, FT_K_FIBER_G, s);
     const int64_t per_block = 4 * 16 * kFiberBlocks;  // fibers of a workgroup
@@ -1436,13 +1637,11 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
       F.hvec = nullptr;
       if (M.n_apply > 0) {
         KTimer tm(P, FT_K_FACTOR_APPLY, s);
-        hipLaunchKernelGGL((k_factor_apply<ITEM_CHAIN, N, J, R, T, FIB>), block_grid(apply_blocks), dim3(256), 0, s,
-                           D.apply, n_apply, M.n_team, D.packs, n_packs, F);
+        FT_QUAD(rows4, J, FT_APPLY);
       }
       if (M.n_compose > 0) {
         KTimer tm(P, FT_K_FACTOR_COMPOSE, s);
-        hipLaunchKernelGGL((k_factor_apply<ITEM_RELAXED, N, J, R, T, FIB>), block_grid(factor_blocks(M.n_compose)),
-                           dim3(256), 0, s, D.compose, M.n_compose, 0, nullptr, 0, F);
+        FT_QUAD(chunks4, J, FT_RELAXED_CHUNKS);
       }
       if (M.n_relax > 0) {
         KTimer tm(P, FT_K_COMBINE, s);
@@ -1457,21 +1656,21 @@ hipError_t factor_launch(const ft_plan* P, int m, const ft_params* p, const Scra
   }
   if (M.n_compose > 0 && M.n_apply > 0 && P->fused) {
     KTimer tm(P, FT_K_FACTOR_FUSED, s);
-    const int64_t mb = factor_blocks(M.n_compose);
-    hipLaunchKernelGGL((k_factor_fused<N, J, R, T, FIB, NC>), block_grid(apply_blocks + mb), dim3(256), 0, s, M.n_team,
-                       mb, D.apply, n_apply, D.compose, M.n_compose, D.packs, n_packs, F);
+    FT_QUAD(F.quads, J, FT_FUSED);
   } else {
     if (M.n_compose > 0) {
       KTimer tm(P, FT_K_FACTOR_COMPOSE, s);
-      hipLaunchKernelGGL((k_factor_compose<N, J, R, T, FIB, NC>), block_grid(factor_blocks(M.n_compose)), dim3(256), 0, s,
-                         D.compose, M.n_compose, F);
+      FT_QUAD(chunks4, J, FT_MAPS);
     }
     if (M.n_apply > 0) {
       KTimer tm(P, FT_K_FACTOR_APPLY, s);
-      hipLaunchKernelGGL((k_factor_apply<ITEM_CHAIN, N, J, R, T, FIB, NC>), block_grid(apply_blocks), dim3(256), 0, s,
-                         D.apply, n_apply, M.n_team, D.packs, n_packs, F);
+      FT_QUAD(rows4, J, FT_APPLY);
     }
   }
+#undef FT_APPLY
+#undef FT_RELAXED_CHUNKS
+#undef FT_MAPS
+#undef FT_FUSED
   for (size_t L = 0; L < M.level_len.size(); ++L) {
     KTimer tm(P, FT_K_COMBINE, s);
     const int64_t nc = M.level_ncomp[L], nf = M.level_len[L] - nc;

@@ -146,6 +146,7 @@ struct ModeMeta {
   int64_t n_apply = 0;
   int64_t n_packs = 0;
   int64_t n_wave = 0;     // entries of the apply list before the rows that packs cover (a multiple of 4)
+  int64_t row_elems = 0;  // elements of the entries between those of a workgroup each and n_wave
   int64_t n_team = 0;     // in-place items (heads, then longer rows) that a workgroup takes each
   int64_t n_heavy = 0;
   int64_t n_maps = 0;     // COMPOSE items (unpadded)
@@ -211,6 +212,36 @@ constexpr int kMinShort = 16384; // a mode with fewer of them lists none (one la
 constexpr int kTeamRow = 1024;   // rows longer than this are updated by a workgroup, shorter ones by a wavefront
 constexpr int kTeamHeads = 512;  // so many heads of kTeamRow elements are updated by a workgroup each, more by a wavefront
 constexpr int kPackRow = 16;      // rows of at most this many elements share blocks of 16
+// Items that go four to a wavefront (quad_items in ft_factor.hip), J <= 16.
+//
+// Chunks: from the number on at which the longer time of a chunk is hidden; a
+// launch of few lasts as long as one chunk does (512 elements: 95 us against 45
+// at J = 16).  us per iteration in the factor launches, one to a wavefront
+// against four, at (chunks per mode): maps, J = 16, 264 and 303 (1900 to 3500),
+// 444 and 446 (3000 to 6500), 661 and 600 (5500 to 9500), 100M elements 7700
+// and 6960; maps, J = 8, 136 and 194 (700 to 1100), 270 and 219 (2100), 100M
+// 7700 and 4490; order 8, where more rows are gathered per element, 796 and
+// 1005 (2300), 1704 and 1765 (6500), 3240 and 3190 (14200).  Increments, J =
+// 16, 143 and 163 (2400 to 4100), 221 and 204 (4300 to 7400), J = 8 121 and
+// 136, 179 and 167 at the same, order 8 1206 and 1321 (6500), 3990 and 3799
+// (24000).
+inline bool quad_chunks(int N, int J, bool relaxed, int64_t n) {
+  if (J > 16) return false;
+  if (relaxed) return n >= (N > 4 ? 16384 : 4096);
+  return n >= (N > 4 ? 8192 : J >= 16 ? 4096 : 2048);
+}
+// Rows (and heads) of 17 to kTeamRow elements: beside maps that go four to a
+// wavefront too, unless they are so short that the start of an item counts
+// (Netflix-shaped, us per iteration in the factor launches, maps four to a
+// wavefront and rows one, or both: J = 16, 5M elements 457 and 441, 100M 7118 and
+// 6769, J = 8, 8M 439 and 410); and on their own where there are many long ones
+// (us per pass: 10,000 rows of 500 elements, J = 16 107 and 86, J = 8 87 and 74;
+// 100,000 of 100, J = 16 266 and 282; relaxed, 5M, J = 16 212 and 278).
+inline bool quad_rows(int N, int J, bool relaxed, int64_t n, int64_t elements, int64_t n_chunks) {
+  if (J > 16 || N > 4) return false;
+  if (!relaxed && quad_chunks(N, J, relaxed, n_chunks)) return n >= 2048 && elements >= 64 * n;
+  return n >= 8192 && elements >= 256 * n;
+}
 constexpr int kRelaxGroup = 256; // chunks per level-1 group of the relaxed merge
 
 // FT_RELAXED scratch in the map region: J + 1 floats per chunk slot, then

@@ -272,23 +272,26 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
     }
   }
 
-  // In-place length of a plan that leaves chunk and head to the library, J >= 16:
-  // a workgroup updates the in-place part of a long row, and a chunk map's
-  // element costs up to two and a half times of a chain's, so that part reaches
-  // past `head`, by whole chunks, to where the launch is estimated shortest: the
-  // longer of its longest chain (per element 35 ns beside other work, 20 alone;
-  // a quarter more at 100,000 elements) and of its work, in ps per chain and per
-  // map element 31 and 76 (45 and 90 with g formed per element) at J = 32, 19
-  // and 32 (23 and 36) at J = 16, there with 20 us for its ends.  A chunk's map
-  // is itself about 200 us of one wavefront's time; it starts beside the chains
-  // where these leave room (512 workgroups of the 768 to 1024 that are
-  // resident), after them otherwise.  Fitted to launches of Netflix-shaped
-  // tensors: the best length at J = 32 is 8192 to 12288 for 8M elements (500,
-  // 500, 560 us for modes 0 to 2, combine included, against 544, 542, 615 at
-  // 2048) and 32768 for 30M (1817 us, 2162 at 2048, 2239 at 65536), at J = 16
-  // 4096 for 5M and 24576 for 30M (893 us; 988 and 1599).  1000 rows of 8000
-  // elements, J = 32, g shared: 471 -> 252 us per pass (no maps).  At J = 8 a
-  // map element costs little more than a chain element.
+  // In-place length of a plan that leaves chunk and head to the library, J >= 16.
+  // J = 16 with enough chunks to take four of them to a wavefront: two chunks,
+  // because a map's element then costs no more than a chain's (100M elements,
+  // us per iteration in the factor launches, by in-place length: 1024 6862, 2048
+  // 7281, 12288 7334, 32768 7740; 5M 441, 5M by the estimate below 473).
+  // Otherwise a workgroup updates the in-place part of a long row, and a chunk
+  // map's element costs up to two and a half times of a chain's, so that part
+  // reaches past `head`, by whole chunks, to where the launch is estimated
+  // shortest: the longer of its longest chain (per element 35 ns beside other
+  // work; a quarter more at 100,000 elements) and of its work, in ps per chain
+  // and per map element 31 and 76 (45 and 90 with g formed per element) at J =
+  // 32, 19 and 32 (23 and 36) at J = 16, there with 20 us for its ends.  A
+  // chunk's map is itself about 200 us of one wavefront's time; it starts beside
+  // the chains where these leave room (512 workgroups of the 768 to 1024 that are
+  // resident), after them otherwise.  Netflix-shaped, J = 32, us per iteration
+  // in the factor launches by stated length: 8M elements 2048 1456, 4096 1410,
+  // 8192 1367, 12288 1434, this estimate 1376; 30M 2048 5482, 16384 4897, 32768
+  // 4735, 65536 6692, this estimate 4828.  1000 rows of 8000 elements, J = 32, g
+  // shared: 1393 at 2048, 1227 at 4096, 809 in one piece, as estimated.  At J =
+  // 8 a map element costs little more than a chain element.
   int64_t reach = M.head;
   if (P->desc.chunk == 0 && P->desc.head == 0 && !P->relaxed && P->J >= 16) {
     const bool shares_g = fiber_share(P->desc.flags, M.n_fibers, nnz);
@@ -296,20 +299,31 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
     const double step = 35e-3, ends = wide ? 0.0 : 20.0;  // us
     const double cc = wide ? (shares_g ? 31e-6 : 45e-6) : (shares_g ? 19e-6 : 23e-6);
     const double cm = wide ? (shares_g ? 76e-6 : 90e-6) : (shares_g ? 32e-6 : 36e-6);
-    int64_t maxL = 0, n_team = 0;
+    // the rows that chunks can come from, longest first, with the sum of those before each
+    const int64_t two = 2 * (int64_t)P->chunk;
+    std::vector<int64_t> lens;
+    int64_t n_team = 0, n_chunks = 0;
     for (int64_t i = 0; i < I; ++i) {
-      maxL = std::max(maxL, H.row_ptr[i + 1] - H.row_ptr[i]);
-      n_team += H.row_ptr[i + 1] - H.row_ptr[i] > kTeamRow;
+      const int64_t L = H.row_ptr[i + 1] - H.row_ptr[i];
+      n_team += L > kTeamRow;
+      if (L > two) {
+        n_chunks += (L - two + P->chunk - 1) / P->chunk;
+        lens.push_back(L);
+      }
     }
+    std::sort(lens.begin(), lens.end(), std::greater<int64_t>());
+    std::vector<int64_t> before(lens.size() + 1, 0);
+    for (size_t k = 0; k < lens.size(); ++k) before[k + 1] = before[k] + lens[k];
+    const int64_t maxL = lens.empty() ? 0 : lens[0];
+    const bool quads = quad_chunks(N, P->J, false, n_chunks);
+    if (quads) reach = two;
     double best = 0.0;
-    for (int64_t r = M.head;; r += std::max<int64_t>(P->chunk, r / 8 / P->chunk * P->chunk)) {
+    for (int64_t r = M.head; !quads; r += std::max<int64_t>(P->chunk, r / 8 / P->chunk * P->chunk)) {
       const double rc = (double)std::min(r, maxL), chain = step * rc * (1.0 + rc / 400e3);
       if (r > M.head && chain >= best) break;  // the chain only grows
-      double work = ends;
-      for (int64_t i = 0; i < I; ++i) {
-        const int64_t L = H.row_ptr[i + 1] - H.row_ptr[i];
-        work += cc * (double)std::min(L, r) + cm * (double)std::max<int64_t>(L - r, 0);
-      }
+      const auto longer = std::partition_point(lens.begin(), lens.end(), [&](int64_t L) { return L > r; });
+      const int64_t k = longer - lens.begin(), maps = before[k] - k * r;  // elements past r
+      const double work = ends + cc * (double)(nnz - maps) + cm * (double)maps;
       const double after = r < maxL && n_team > 512 ? 200.0 * (double)P->chunk / 1024 : 0.0;
       const double t = std::max(chain + after, work);
       if (r == M.head || t < best) {
@@ -369,6 +383,7 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
   H.apply.insert(H.apply.end(), rest, packed);
   pad4(H.apply, ITEM_LIGHT);
   M.n_wave = (int64_t)H.apply.size();
+  for (int64_t k = M.n_team; k < M.n_wave; ++k) M.row_elems += H.apply[k].len;
   H.apply.insert(H.apply.end(), packed, light.end());
   pad4(H.apply, ITEM_LIGHT);
   // packs of the rows of at most kPackRow elements: neighbours in the CSR

@@ -1,5 +1,5 @@
-"""Chunks of long rows taken four to a wavefront (J <= 16, many chunks): chunk lengths around the edges of a block,
-last chunks of one element, counts that leave the last wavefront's rows of lanes empty, both storages, shared and
+"""Chunks and rows taken four to a wavefront (J <= 16, many of them): lengths around the edges of a block, last chunks
+of one element, empty rows, counts that leave the last wavefront's rows of lanes empty, both storages, shared and
 per-element g, no C cache, relaxed plans, and a decay above one half.
 
 Against the oracle's pass from the same state (BF16: from the same C16 and B16); tolerance as in
@@ -71,6 +71,41 @@ def test_against_the_oracle(order, J, R, fibers, lr, lam, spare):
         assert ok, (storage, kw, err, bound)
         decayed = before * ((1.0 - lr * lam) ** lens)[:, None]
         assert not delta_ok(decayed[lens > 0], orc.A[0][lens > 0], before[lens > 0], rel=0.02)[0]
+
+
+@pytest.mark.parametrize("order,J,R", [(3, 8, 8), (3, 16, 16), (4, 8, 8)])
+@pytest.mark.parametrize("relaxed", [False, True])
+def test_rows(order, J, R, relaxed):
+    """Rows in one piece of 17 to 1024 elements: 300 on average (four to a wavefront on their own), and beside chunks."""
+    import torch
+
+    import paper_2210_06014_amd as ft
+
+    rng = np.random.default_rng(J)
+    lens = np.concatenate([rng.integers(17, 600, 9000), [17, 18, 31, 32, 33, 1023, 1024, 1025, 5000, 0, 3]])
+    rng.shuffle(lens)
+    dims = [lens.size] + [60] * (order - 1)
+    nnz = int(lens.sum())
+    c = np.stack([np.repeat(np.arange(lens.size), lens)] + [rng.integers(0, 60, nnz) for _ in range(order - 1)])
+    c = np.ascontiguousarray(c[:, rng.permutation(nnz)].astype(np.int32))
+    v = rng.integers(1, 6, nnz).astype(np.float32)
+    A = [(rng.normal(0, 1, (d, J)) / np.sqrt(J)).astype(np.float32) for d in dims]
+    B = [rng.normal(0, 1, (J, R)).astype(np.float32) for _ in dims]
+    for kw in (dict(head=1024), dict(head=300, chunk=40)):  # (the second: 60,000 chunks, heads beside shorter rows)
+        print(f"\n[quad rows] order {order} J {J} relaxed {relaxed} {kw}", flush=True)
+        plan, prm = gpu_setup(dims, J, R, c, v, A, B, relaxed=relaxed, **kw)
+        orc = oracle_model(dims, J, R, c, v, A, B)
+        before = orc.A[0].copy()
+        if relaxed:
+            orc.factor_pass_relaxed(0, 1e-3, 1e-2, kw["head"], kw.get("chunk", 512))
+        else:
+            orc.factor_pass(0, 1e-3, 1e-2)
+        ft.factor_pass(plan, prm, 0, 1e-3, 1e-2)
+        torch.cuda.synchronize()
+        got = to_np(prm.A[0])
+        assert np.array_equal(got[lens == 0], before[lens == 0])
+        ok, err, bound = delta_ok(got, orc.A[0], before)
+        assert ok, (kw, err, bound)
 
 
 @pytest.mark.parametrize("order,J,R", [(3, 8, 8), (3, 16, 16)])
