@@ -80,8 +80,7 @@ def algorithmic(w, nnz, row_counts, heads, fibers, relaxed=False, sp=4):
             c_share = 0.0
         out["factor_compose"][0] += comp * f_elem
         # executed on top: the chunk map's matrix part, a J x J matrix-vector
-        # product and a rank-1 update per element (4 J^2 flops).  An upper bound:
-        # the in-place part of a long row may reach past the head reported here
+        # product and a rank-1 update per element (4 J^2 flops)
         out["compose_executed"][0] += comp * (f_elem + (2 * J if relaxed else 4 * J * J))
         out["factor_compose"][1] += comp * e_bytes + c_share * comp / max(nnz, 1)
         out["factor_apply"][0] += app * f_elem
@@ -280,7 +279,7 @@ def rooflines(w, nnz, c, plan, prof, steps, storage, relaxed, counters_ok):
     counts = [np.bincount(c[m], minlength=w.dims[m]) for m in range(N)]
     infos = [plan.mode_info(m) for m in range(N)]
     fibers = [info["fibers"] if info["fiber_shared"] else None for info in infos]
-    heads = [info["head"] for info in infos]
+    heads = [info["in_place"] for info in infos]
     alg = algorithmic(w, nnz, counts, heads, fibers, relaxed, sp=2 if storage == "bf16" else 4)
     kernels = {}
     for k, (ms, n) in prof.items():
@@ -343,7 +342,7 @@ def leg(ft, w, c, plan, A, B, storage, args, nnz, relaxed=False):
             "rmse_end": rmse, "roofline": dom, "roofline_gather": gather, "passes": passes, "kernels": kernels,
             "fiber_shared_modes": [m for m in range(N) if fibers[m] is not None],
             "fibers_per_mode": [info["fibers"] for info in infos],
-            "heads_per_mode": [info["head"] for info in infos], "chunk": infos[0]["chunk"]}
+            "heads_per_mode": [info["in_place"] for info in infos], "chunk": infos[0]["chunk"]}
 
 
 def describe(w, nnz):

@@ -110,12 +110,13 @@ typedef struct {
                                    is not above the row length reached by the longest rows holding a
                                    quarter of its elements and whose serial chain a cost model of the
                                    launch (from the row lengths and whether g is shared per fiber)
-                                   expects to end within the launch.  ft_plan_mode_info reports the
-                                   value each mode uses.  Where chunk and head are both 0, J >= 16 and the
-                                   plan is not FT_RELAXED, the in-place part of a long row may reach
-                                   further, by whole chunks, where a second estimate (of the launch with
-                                   a workgroup per long row) has its chain end in time; ft_mode_info
-                                   counts the pieces that result */
+                                   expects to end within the launch.  ft_plan_mode_info reports this
+                                   value.  Where chunk and head are both 0, J >= 16 and the
+                                   plan is not FT_RELAXED, the in-place part of a long row is chosen by a
+                                   second estimate (of the launch with a workgroup per long row) and may
+                                   be longer, or, with many chunks at J = 16, two chunks;
+                                   ft_plan_in_place reports it, ft_mode_info counts the pieces that
+                                   result */
   int32_t fanin;                /* chunk maps folded per combine step (0 or above the maximum: 16); a row with
                                    at most fanin maps has them applied in sequence to its head's result */
   int32_t flags;                /* FT_KEEP_HOST | FT_WITH_PERM | FT_NO_FIBER_SHARE | FT_NO_C_CACHE | FT_RELAXED |
@@ -154,14 +155,14 @@ typedef struct {
   int64_t rows;          /* I_m */
   int64_t nonempty_rows; /* rows with at least one element */
   int64_t max_row;       /* largest row length */
-  int64_t light_rows;    /* rows updated in one piece (of at most `head` elements; see ft_desc.head) */
+  int64_t light_rows;    /* rows updated in one piece (of at most ft_plan_in_place elements) */
   int64_t heavy_rows;    /* longer rows: a head plus chunks */
   int64_t chunks;        /* pieces of heavy rows, heads included */
   int64_t segments;      /* pieces of rows used by the core, loss and gradient passes */
   int32_t combine_levels;
   int32_t fiber_shared;  /* 1 if the factor pass shares g per fiber in this mode */
   int64_t fibers;        /* mode-m fibers: distinct (i_n, n != m) */
-  int32_t head;          /* the plan's head length (ft_desc.head, or its default) */
+  int32_t head;          /* ft_desc.head, or its default (what the kernels use: ft_plan_in_place) */
   int32_t chunk;         /* the plan's chunk length (ft_desc.chunk, or its default) */
   int64_t runs;          /* runs of elements of a row sharing the index of mode m + 1 */
 } ft_mode_info;
@@ -209,6 +210,14 @@ ft_status ft_plan_upload(ft_plan* plan, void* d_workspace, size_t workspace_byte
 void ft_plan_destroy(ft_plan* plan);
 
 ft_status ft_plan_mode_info(const ft_plan* plan, int32_t mode, ft_mode_info* info);
+
+/*
+ * ft_plan_in_place -- elements of a long row of mode `mode` that are updated in
+ * place before its chunks (rows of at most so many are updated in one piece):
+ * ft_mode_info.head, or the estimated length where ft_desc.chunk and head are
+ * left to the library (see ft_desc.head).
+ */
+ft_status ft_plan_in_place(const ft_plan* plan, int32_t mode, int64_t* elements);
 
 /*
  * ft_plan_host_csr -- copy of the host CSR of one mode (needs FT_KEEP_HOST).

@@ -35,6 +35,7 @@ SYMBOLS = [
     "ft_plan_upload",
     "ft_plan_destroy",
     "ft_plan_mode_info",
+    "ft_plan_in_place",
     "ft_plan_host_csr",
     "ft_refresh",
     "ft_predict",
@@ -139,6 +140,7 @@ def load():
         "ft_plan_upload": ([vp, vp, ctypes.c_size_t, vp], i32),
         "ft_plan_destroy": ([vp], None),
         "ft_plan_mode_info": ([vp, i32, P(FtModeInfo)], i32),
+        "ft_plan_in_place": ([vp, i32, P(i64)], i32),
         "ft_plan_host_csr": ([vp, i32, i32, vp, vp, vp, vp], i32),
         "ft_refresh": ([vp, P(FtParams), i32, vp], i32),
         "ft_predict": ([vp, P(FtParams), vp, i64, vp, vp], i32),

@@ -96,7 +96,11 @@ class Plan:
     def mode_info(self, m: int) -> dict:
         info = FtModeInfo()
         check(self._lib.ft_plan_mode_info(self._h, int(m), ctypes.byref(info)))
-        return {k: getattr(info, k) for k, _ in FtModeInfo._fields_}
+        out = {k: getattr(info, k) for k, _ in FtModeInfo._fields_}
+        n = ctypes.c_int64()
+        check(self._lib.ft_plan_in_place(self._h, int(m), ctypes.byref(n)))
+        out["in_place"] = n.value  # elements of a long row updated before its chunks
+        return out
 
     def host_csr(self, m: int, factor_order: bool = False):
         """(row_ptr, idx [(N-1), nnz], vals, perm) of mode m (plan built with keep_host=True); with factor_order,

@@ -160,7 +160,8 @@ struct ModeMeta {
   int64_t n_relax = 0;         // FT_RELAXED level-2 items (heavy rows)
   int64_t n_fibers = 0;
   int64_t n_runs = 0;  // runs of equal column-0 index within rows
-  int64_t head = 0;    // elements of a long row updated in place before its chunk maps
+  int64_t head = 0;      // ft_desc.head or its default
+  int64_t in_place = 0;  // elements of a long row updated in place before its chunks
   bool use_fiber = false;
   ft_mode_info info{};
 };

@@ -338,6 +338,7 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
   // a longer row is a head item (its first `reach` elements, updated in
   // place) followed by chunk items whose maps the combine applies in order
   const int64_t chunk = P->chunk, hl = reach;
+  M.in_place = hl;
   std::vector<FItem> light, head;
   int64_t n_heavy = 0, n_maps = 0, max_row = 0, nonempty = 0;
   std::vector<int64_t> heavy_rows, heavy_base, heavy_nmaps;
@@ -821,6 +822,13 @@ extern "C" ft_status ft_plan_mode_info(const ft_plan* P, int32_t mode, ft_mode_i
   if (!P || !info) return fail(FT_ERR_ARG, "null argument");
   if (mode < 0 || mode >= P->N) return fail(FT_ERR_ARG, "mode out of range");
   *info = P->meta[mode].info;
+  return FT_OK;
+}
+
+extern "C" ft_status ft_plan_in_place(const ft_plan* P, int32_t mode, int64_t* elements) {
+  if (!P || !elements) return fail(FT_ERR_ARG, "null argument");
+  if (mode < 0 || mode >= P->N) return fail(FT_ERR_ARG, "mode out of range");
+  *elements = P->meta[mode].in_place;
   return FT_OK;
 }
 
