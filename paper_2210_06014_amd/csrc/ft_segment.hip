@@ -1058,8 +1058,9 @@ hipError_t reduce_partials(const ft_plan* P, const Scratch& S, int nparts, float
   return hipGetLastError();
 }
 
-int seg_blocks(const void* kernel, int64_t nseg) {
-  int64_t b = (nseg + 3) / 4;
+// workgroups for the work of `waves` wavefronts, at most those resident
+int seg_blocks(const void* kernel, int64_t waves) {
+  int64_t b = (waves + 3) / 4;
   b = std::min<int64_t>(b, std::min(kPartials, resident_blocks(kernel)));
   if (b < 1) b = 1;
   return (int)b;
@@ -1100,7 +1101,8 @@ hipError_t segsum_impl(const ft_plan* P, int m, const ft_params* p, float* parti
   // the two kernels' partials share the scratch: at most half of it each where both run
   const int most = n_short > 0 ? kPartials / 2 : kPartials;
   const int nb = M.n_long_segs > 0 || n_short == 0 ? std::min(most, seg_blocks(kern, M.n_long_segs)) : 0;
-  const int nbs = n_short > 0 ? std::min(most, seg_blocks(kshort, n_short)) : 0;
+  constexpr int per_wave = 64 * vpl<T>() / R;
+  const int nbs = n_short > 0 ? std::min(most, seg_blocks(kshort, (n_short + per_wave - 1) / per_wave)) : 0;
   *nblocks = nb + nbs;
   float* pshort = partials + (int64_t)nb * J * R;
   KTimer tm(P, FT_K_SEGSUM, s);
