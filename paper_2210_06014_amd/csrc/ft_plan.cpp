@@ -388,7 +388,10 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
   H.apply.insert(H.apply.end(), packed, light.end());
   pad4(H.apply, ITEM_LIGHT);
   // packs of the rows of at most kPackRow elements: neighbours in the CSR
-  // while they fit into 16 slots
+  // while they fit into 16 slots (two neighbouring packs hold more than 16)
+  int64_t short_elems = 0;
+  for (auto it = packed; it != light.end(); ++it) short_elems += it->len;
+  H.packs.reserve((size_t)std::min<int64_t>(light.end() - packed, short_elems / 8 + n_heavy + (packed - light.begin()) + 1));
   for (int64_t i = 0; i < I; ++i) {
     const int64_t s = H.row_ptr[i], L = H.row_ptr[i + 1] - s;
     if (L == 0 || L > kPackRow || L > hl) continue;
@@ -480,12 +483,15 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
   const int64_t seg_len = P->seg_len;
   H.seg_first.assign((size_t)I + 1, 0);
   std::vector<Seg> shorts;
-  int64_t n_short = 0;
+  int64_t n_short = 0, n_segs = 0;
   for (int64_t i = 0; i < I; ++i) {
     const int64_t L = H.row_ptr[i + 1] - H.row_ptr[i];
     n_short += L > 0 && L <= kShortSeg;
+    n_segs += (L + seg_len - 1) / seg_len;
   }
   const bool split = n_short >= kMinShort;
+  H.segs.reserve((size_t)n_segs);
+  if (split) shorts.reserve((size_t)n_short);
   for (int64_t i = 0; i < I; ++i) {
     int64_t s = H.row_ptr[i], L = H.row_ptr[i + 1] - s;
     H.seg_first[i] = (int64_t)H.segs.size();
@@ -497,10 +503,18 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
       H.segs.push_back(Seg{s + o, (int32_t)std::min<int64_t>(seg_len, L - o), (int32_t)i});
   }
   M.n_long_segs = (int64_t)H.segs.size();
-  std::stable_sort(shorts.begin(), shorts.end(), [](const Seg& a, const Seg& b) { return a.len > b.len; });
+  // (by descending length, rows of one length in order: a counting sort)
+  int64_t at[kShortSeg + 1] = {0};
+  for (const Seg& g : shorts) ++at[g.len];
+  for (int64_t len = kShortSeg, end = M.n_long_segs; len > 0; --len) {
+    const int64_t n = at[len];
+    at[len] = end;
+    end += n;
+  }
+  H.segs.resize((size_t)M.n_long_segs + shorts.size());
   for (const Seg& g : shorts) {
-    H.seg_first[g.row] = (int64_t)H.segs.size();
-    H.segs.push_back(g);
+    H.seg_first[g.row] = at[g.len];
+    H.segs[(size_t)at[g.len]++] = g;
   }
   H.seg_first[I] = (int64_t)H.segs.size();
 
