@@ -17,7 +17,7 @@
  *    ft_plan_upload (size from ft_plan_query), and each parameter set brings
  *    its own scratch buffer (ft_params.scratch, size from ft_plan_query).
  *    Both must be 256-byte aligned (torch allocations are).  The one device
- *    array of the library itself is the fixed 56 KiB static scratch of
+ *    array of the library itself is the fixed 36 KiB static scratch of
  *    ft_loss_noalloc.
  *  - Matrices are dense row-major FP32 in device memory owned by the caller
  *    (A(n): I_n x J, B(n): J x R, C(n): I_n x R).  Eq. (1) allows a J_n per
@@ -309,8 +309,8 @@ ft_status ft_loss(const ft_plan* plan, const ft_params* p, double lam_a, double 
  * or bring a scratch buffer: code under HIP graph capture, tight serving
  * loops, harnesses that forbid allocation.  Same kernels, launch grid and
  * result as ft_loss (bit for bit); ft_params.scratch may be NULL.  The FP64
- * partial sums live in a static device array of the library (56 KiB:
- * 2048 loss partials plus 2 FT_MAX_ORDER x 256 regulariser partials), held on
+ * partial sums live in a static device array of the library (36 KiB:
+ * 2048 loss partials plus FT_MAX_ORDER x 256 of the sums of squares), held on
  * every GPU the library runs on until the process ends and located on the
  * first call on each device (make that first call outside graph capture).
  * Nothing is allocated, freed or memset; kernel timing (ft_profile_enable) is

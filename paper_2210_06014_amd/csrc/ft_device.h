@@ -4,8 +4,8 @@
 //
 // Lane layouts:
 //  * factor pass: a wavefront owns one work item and takes it in blocks of 16
-//    elements (ft_factor.hip); values of other lanes are read with DPP
-//    row_newbcast and through LDS;
+//    elements, or four items of 16 lanes each (ft_factor.hip); values of other
+//    lanes are read with DPP row_newbcast and through LDS;
 //  * core, loss, gradient passes: a segment of a row per wavefront, R/4 lanes
 //    per element, each lane gathering a 16-byte slice of every C(n) row;
 //  * C refresh: v_mfma_f32_16x16x4_f32 tiles of 16 rows.
@@ -126,20 +126,7 @@ struct CPtrs {
   const T* p[N > 1 ? N - 1 : 1];
 };
 
-// four consecutive values starting at p (16-byte aligned for float, 8-byte for BF16)
-__device__ __forceinline__ floatx4 load4(const float* p) { return *reinterpret_cast<const floatx4*>(p); }
-__device__ __forceinline__ floatx4 load4(const uint16_t* p) {
-  const uint2 u = *reinterpret_cast<const uint2*>(p);
-  floatx4 r;
-  r[0] = __uint_as_float(u.x << 16);
-  r[1] = __uint_as_float(u.x & 0xFFFF0000u);
-  r[2] = __uint_as_float(u.y << 16);
-  r[3] = __uint_as_float(u.y & 0xFFFF0000u);
-  return r;
-}
-
-
-// The same w without the C cache (FastTucker's cost, kept for the Table 5
+// w without the C cache (FastTucker's cost, kept for the Table 5
 // comparison): each C(n) row is formed on use as A(n)[i, :] B(n).  Lane j
 // loads A(n)[i, j]; a row broadcast against the lane's column of B(n) then
 // gives C(n)[i, r] in lane r (J = R = 16).

@@ -27,25 +27,26 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 // them and 64 FMAs take the sum of their times, in one wavefront or in four),
 // so a block costs 24 MFMA (G and K at J = R = 32; 64 where a chunk map is
 // carried too) plus the VALU work of the serial part, which dominates at
-// J <= 16.  The bf16 MFMA would run beside the VALU, but it truncates the terms
-// of an instruction to the largest one's 24 bits: G from three bf16 parts per
-// value took a tenth off a launch and doubled the error of A.  One item per
-// wavefront, because a block's MFMA then serves one chain and the chain is 4
+// J <= 16; there many chunks go four to a wavefront instead (quad_items).  The
+// bf16 MFMA would run beside the VALU, but it truncates the terms of an
+// instruction to the largest one's 24 bits: G from three bf16 parts per value
+// took a tenth off a launch and doubled the error of A.  One item per wavefront
+// otherwise, because a block's MFMA then serves one chain and the chain is 4
 // times shorter than with an item per 16 lanes.  Against one step per element
-// on 16 lanes (g by row broadcasts), us per launch with the forms below:
-// Netflix-shaped 8M elements, J = R = 32, modes 0 to 2: 828, 1048, 1048 -> 370,
-// 505, 580; order 4 (3M, J = R = 32) 934 -> 253; order 6 (1M, BF16) 157 -> 56;
-// order 8 (1M, J = 8, R = 16) 334 -> 62; Netflix-shaped 5M, J = R = 16: 267 ->
-// 171.
+// on 16 lanes (g by row broadcasts), us per launch: Netflix-shaped 8M elements,
+// J = R = 32, modes 0 to 2: 828, 1048, 1048 -> 393, 500, 557; order 4 (3M, J = R = 32)
+// 934 -> 241; order 6 (1M, BF16) 157 -> 59; order 8 (1M, J = 8, R = 16) 334
+// -> 62; Netflix-shaped 5M, J = R = 16: 267 -> 154.
 //
 // Lane l = 16 g + i of the wavefront holds:
 //   Gu[k]  G[i][jbase(g) + k], k < J / 4   (as the MFMA that forms G leaves it,
 //          and as the operand of K = G G^T and of G N)
 //   Gr[k]  G[sbase(g) + k][j], j = the lane's state index (through LDS)
 //   L[s]   -gp K[i][s] for s < i, else 0   (through LDS, all rows of 16 alike)
-//   a      the row's element j = 16 (g % 2) + i (J = 32), i % J otherwise, FP64:
-//          the decay lr lam a is about a hundred ulps of a and nearly constant,
-//          so rounding the running row to FP32 would accumulate coherently.
+//   a      the row's element j = 16 (g % 2) + i (J = 32), i % J otherwise, FP64,
+//          as are its increments: the decay lr lam a is about a hundred ulps of
+//          a and nearly constant, so rounding the running row to FP32 would
+//          accumulate coherently.
 // Values of other lanes are read by DPP row broadcasts, so a state vector is
 // also kept rotated per row of 16: broadcast k then gives lane row g its
 // jbase(g) + k.  Slots past the end of an item hold x = 0 and G = 0.

@@ -123,8 +123,8 @@ struct ScratchOff {
   size_t maps = SIZE_MAX;       // float: chunk maps (J^2 + J each; FT_RELAXED: increments, then FP64 group records)
   size_t map_scale = SIZE_MAX;  // double: rho^length of each map
   size_t hvec = SIZE_MAX;       // float: head vectors of long rows (J each)
-  size_t partials = SIZE_MAX;   // float: per-workgroup J x R partial sums, then their folds
-  size_t dpartials = SIZE_MAX;  // double: per-workgroup FP64 loss partials, then the regulariser partials
+  size_t partials = SIZE_MAX;   // float: per-workgroup J x R partial sums
+  size_t dpartials = SIZE_MAX;  // double: per-workgroup FP64 loss partials, then those of the sums of squares of A(n)
   size_t tseg = SIZE_MAX;       // float: per-segment sums of the gradient pass (R each)
   size_t gfib = SIZE_MAX;       // float: the shared g of each fiber (J each)
 };
@@ -207,6 +207,7 @@ ft_status fail(ft_status s, const std::string& msg);
 
 // kernel launchers (ft_refresh.hip, ft_factor.hip, ft_segment.hip); return hipSuccess or the launch error
 constexpr int kPartials = 2048;  // max workgroups of the reduction kernels
+constexpr int kSumsqBlocks = 256;  // max workgroups per matrix of the sums of squares
 constexpr int kSegLen = 512;     // max elements per segment (ft_plan::seg_len)
 constexpr int kShortSeg = 32;    // rows of at most this many elements may be listed as short
 constexpr int kMinShort = 16384; // a mode with fewer of them lists none (one launch instead of two)

@@ -201,7 +201,10 @@ static ft_status build_mode(ft_plan* P, int m, const int32_t* coords, const floa
   //    shares g per fiber; a map step adds the J x J update.  Fitted to
   //    MI355X launch times of the Netflix-shaped tensors and the 1000^3
   //    density tensors: r_a = 2358 (J = 32), 3100 (J = 16) with g formed per
-  //    step, 1200 and 2000 with g read; r_s = 0.5 and 0.2 / 0.3.  This is
+  //    step, 1200 and 2000 with g read; r_s = 0.5 and 0.2 / 0.3.  (Fitted to
+  //    kernels that took every item a step per element on 16 lanes, and kept
+  //    as the reported default; the in-place length below, where chunk and
+  //    head are left to the library, is estimated for the present ones.)  This is
   //    what shortens the heads of tensors with few long rows (1000 rows of
   //    20000 elements: 5120 instead of 16384, 2.2 instead of 4.8 ms per pass).
   M.head = P->head;
@@ -609,7 +612,7 @@ static void layout(ft_plan* P) {
   so.map_scale = S.add((size_t)max_slots * sizeof(double));
   so.hvec = S.add((size_t)max_heavy * J * sizeof(float));
   so.partials = S.add((size_t)kPartials * J * R * sizeof(float));
-  so.dpartials = S.add(((size_t)kPartials + 2 * FT_MAX_ORDER * 256) * sizeof(double));
+  so.dpartials = S.add(((size_t)kPartials + FT_MAX_ORDER * kSumsqBlocks) * sizeof(double));
   so.tseg = S.add((size_t)max_segs * R * sizeof(float));
   so.gfib = S.add((size_t)max_fib * J * sizeof(float));
   P->scratch_bytes = S.bytes;
@@ -696,10 +699,9 @@ extern "C" ft_status ft_plan_create(ft_plan** out, const ft_desc* d, const int32
   // Default piece lengths.  Exact passes: a chunk map costs 4 J^2 flops per
   // element and a fold of maps J^3, while the serial in-place chains run
   // beside the maps in the same launch, so with J >= 32 longer chunks and
-  // far longer heads pay (measured on MI355X with the Netflix-shaped tensor:
-  // 32.7 ms per iteration with chunk 512 and head 1024, 26.7 with chunk 1024
-  // and head 24576); J = 16 gains less (11.4 ms with head 4096, 11.0 with
-  // 12288).  Each mode picks its head up to the cap (32 chunks at J >= 32,
+  // far longer heads pay (measured on MI355X with the Netflix-shaped tensor and
+  // a step per element: 32.7 ms per iteration with chunk 512 and head 1024,
+  // 26.7 with chunk 1024 and head 24576).  Each mode picks its head up to the cap (32 chunks at J >= 32,
   // 24 at J = 16, 2 below) from its row lengths, as build_mode describes.
   // Relaxed passes keep chunk 512 and head 1024: their chunks start from the
   // head's result, so a long head is serial time, and the chunk length is

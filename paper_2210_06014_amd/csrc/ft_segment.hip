@@ -955,8 +955,6 @@ __global__ __launch_bounds__(256) void k_sumsq(SumsqArgs a, double* __restrict__
   if (threadIdx.x == 0) dpart[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-constexpr int kSumsqBlocks = 256;  // workgroups per matrix, at most
-
 // Fixed-order FP64 sums of the partials and of the (small) B(n), strided per
 // thread, then a tree.
 __global__ __launch_bounds__(256) void k_loss_finish(const double* __restrict__ dpart, int n_sse,
@@ -1125,8 +1123,8 @@ hipError_t segsum_impl(const ft_plan* P, int m, const ft_params* p, float* parti
   return hipGetLastError();
 }
 
-// dpart: kPartials FP64 partials of the loss kernel, then 2 N kSumsqBlocks of
-// the regularisers.
+// dpart: kPartials FP64 partials of the loss kernel, then N kSumsqBlocks of
+// the A(n).
 template <int N, int J, int R, class T>
 hipError_t loss_impl(const ft_plan* P, const ft_params* p, double* dpart, double lam_a, double lam_b, double* out4,
                      float* xout, hipStream_t s) {
@@ -1305,17 +1303,17 @@ hipError_t launch_grad(const ft_plan* P, const ft_params* p, const Scratch& S, c
 }
 
 // Scratch of ft_loss_noalloc: the FP64 partials of the loss kernel (at most
-// kPartials workgroups) followed by those of the regulariser sums
-// (2 N kSumsqBlocks), in a device array that the library holds on every GPU
+// kPartials workgroups) followed by those of the sums of squares of A(n)
+// (N kSumsqBlocks), in a device array that the library holds on every GPU
 // it runs on until the process ends.  Host code uses the address looked up
 // per device below, never the array's name.
-constexpr size_t kNoAllocDoubles = (size_t)kPartials + 2 * FT_MAX_ORDER * kSumsqBlocks;
+constexpr size_t kNoAllocDoubles = (size_t)kPartials + FT_MAX_ORDER * kSumsqBlocks;
 static __device__ __align__(256) double scratch[kNoAllocDoubles];
 
 size_t noalloc_loss_capacity() { return sizeof(double) * kNoAllocDoubles; }
 
 size_t noalloc_loss_need(const ft_plan* P) {
-  return sizeof(double) * ((size_t)kPartials + 2 * (size_t)P->N * kSumsqBlocks);
+  return sizeof(double) * ((size_t)kPartials + (size_t)P->N * kSumsqBlocks);
 }
 
 namespace {
